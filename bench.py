@@ -106,8 +106,8 @@ def kernel_source_hash(method: str = "realspace") -> str:
     elif method == "unet":
         files = ["unet_internal.hpp", "unet_kernels.hip", "unet_host.hip"]
     else:
-        files = ["fft.hpp", "fft_kernels.hpp", "geom.hpp", "tomo_kernels.hip"] + \
-            sorted(f for f in os.listdir(csrc) if f.startswith("fft_sizes"))
+        files = ["fft.hpp", "fft_kernels.hpp", "axis_kernels.hpp", "geom.hpp", "tomo_kernels.hip"] + \
+            sorted(f for f in os.listdir(csrc) if f.startswith(("fft_sizes", "axis_sizes")))
     h = hashlib.sha256()
     for f in files:
         with open(os.path.join(csrc, f), encoding="utf-8") as fh:
@@ -116,6 +116,21 @@ def kernel_source_hash(method: str = "realspace") -> str:
                 if code:
                     h.update(code.encode() + b"\n")
     return h.hexdigest()[:16]
+
+
+def sliced(w, angle_batch: int = 0) -> bool:
+    """Whether tomo_reconstruct runs this workload by slices (no plane stacks): "planes" is then
+    the slice kernel (transforms along x and gridding) and "grid" the column kernel."""
+    return (w.geometry == "axis" and bool(w.ewald) and angle_batch == 0 and w.M <= 128 and w.n_vox <= w.M
+            and w.K <= w.M and (w.M - w.n_vox) % 2 == 0 and (w.M - w.K) % 2 == 0)
+
+
+def slice_bytes(kind: str, w) -> float:
+    """Compulsory HBM bytes of one step of the slice path: spectra as for the stacks but only the
+    row frequencies up to M/2; the slice kernel reads those; the column kernel writes the volume."""
+    half = (w.M // 2 + 1) * float(w.M)
+    return {"spectra": w.n_views * (4.0 * w.M * w.M + 32.0 * half), "planes": w.n_views * 16.0 * half + 4.0 * w.M * w.n_vox ** 2,
+            "grid": 4.0 * w.M * w.n_vox ** 2 + 4.0 * w.n_vox ** 3}[kind]
 
 
 def algorithmic_bytes(kind: str, w, nb: int, first_batch: bool, sbytes: int = 4, fourier_mode: int = 1,
@@ -153,10 +168,10 @@ def plane_flops(w, nb: int) -> float:
     return nb * npairs * 5.0 * n * np.log2(n)
 
 
-def path_bytes_per_update(w, sbytes: int) -> float:
+def path_bytes_per_update(w, sbytes: int, slices: bool = False) -> float:
     """Algorithmic HBM bytes of a whole reconstruction per voxel-angle update: per view the
-    image read and the plane stack written and read, plus the volume written once."""
-    per_view = 4.0 * w.M * w.M + 2.0 * sbytes * w.M * w.K * w.M
+    image read and (stack path) the plane stack written and read, plus the volume written once."""
+    per_view = 4.0 * w.M * w.M + (0.0 if slices else 2.0 * sbytes * w.M * w.K * w.M)
     return (w.n_views * per_view + 4.0 * w.n_vox ** 3) / (float(w.n_vox) ** 3 * w.n_views)
 
 
@@ -305,13 +320,16 @@ def main():
         plan.timing(False)
         k = plan.timing_read(reset=True)
         n_batches = -(-w.n_views // batch)
+        by_slices = not fourier and sliced(w, args.angle_batch)
         kernels = {}
         for kind, (tot, cnt) in k.items():
             if cnt == 0:
                 continue
             # bytes of all launches of one step (the first batch writes V without reading it)
             sb = 4 if args.plane_dtype == "f32" else 2
-            if kind == "spectra" or fourier:   # launches over all views per step
+            if by_slices:                      # one launch of each kind per step
+                per_launch = slice_bytes(kind, w)
+            elif kind == "spectra" or fourier:   # launches over all views per step
                 step_bytes = algorithmic_bytes(kind, w, w.n_views, True, sb, args.fourier_mode,
                                                plan.fourier_entries)
                 per_launch = step_bytes / cnt * args.steps
@@ -332,14 +350,23 @@ def main():
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": read_traffic(dom, src_hash, w.name, args.plane_dtype),
                     "ms_per_step_with_events": round(ms_timed, 4), "kernel_source_hash": src_hash}
+        if by_slices and dom == "planes":
+            # planes stay in LDS: the vector arithmetic bounds the slice kernel, not its bytes
+            fl = w.n_views * (plane_flops(w, 1) / 2 + 7.0 * w.n_vox ** 2 * w.M)
+            tf = fl / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
+            roofline.update(bound="fp32_vector", achieved=round(tf, 2), peak=FP32_UNPACKED_PEAK, unit="TFLOP/s",
+                            frac=round(tf / FP32_UNPACKED_PEAK, 4))
         if not fourier:
-            pb = path_bytes_per_update(w, sb)
+            pb = path_bytes_per_update(w, sb, by_slices)
             roofline["path"] = {"bytes_per_update": round(pb, 3), "achieved": round(pb * value / 1e9, 1),
                                 "frac": round(pb * value / 1e9 / HBM_PEAK_GBS, 4)}
         if "planes" in kernels:
             # the plane kernel's FFT arithmetic beside its bytes: it is bound by vector
             # arithmetic and LDS exchanges more than by its HBM writes
-            fl = sum(plane_flops(w, min(batch, w.n_views - b * batch)) for b in range(n_batches)) / n_batches
+            if by_slices:   # transforms along x only, and 7 operations per update for the interpolation
+                fl = w.n_views * (plane_flops(w, 1) / 2 + 7.0 * w.n_vox ** 2 * w.M)
+            else:
+                fl = sum(plane_flops(w, min(batch, w.n_views - b * batch)) for b in range(n_batches)) / n_batches
             tflops = fl / (kernels["planes"]["avg_ms"] * 1e-3) / 1e12
             kernels["planes"]["algorithmic_flops_per_launch"] = fl
             kernels["planes"]["TFLOPs"] = tflops
@@ -510,7 +537,9 @@ def run_batch(args):
             for kind, (ms_k, cnt) in pl.timing_read(reset=True).items():
                 if cnt == 0:
                     continue
-                if kind == "spectra":
+                if sliced(w):
+                    b = slice_bytes(kind, w)
+                elif kind == "spectra":
                     b = algorithmic_bytes(kind, w, w.n_views, True)
                 else:
                     b = sum(algorithmic_bytes(kind, w, min(pl.batch, w.n_views - i * pl.batch), i == 0)

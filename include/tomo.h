@@ -96,7 +96,8 @@ typedef struct {
   int32_t ewald;          /* 1: eq. (11) with depth planes; 0: eq. (13), one plane */
   int32_t weight_mode;    /* tomo_weight_mode */
   int32_t plane_dtype;    /* tomo_dtype of the plane stack */
-  int32_t angle_batch;    /* views per internal batch of tomo_reconstruct; 0 -> automatic */
+  int32_t angle_batch;    /* views per internal batch of tomo_reconstruct; 0 -> automatic (which for
+                             small single-axis scans needs no batches, see tomo_reconstruct) */
   int32_t fourier;        /* workspace of tomo_fourier_reconstruct (needs n_vox among the
                              FFT sizes below): 0 none; 1 the gridding operator, built here (8 bytes
                              per non-zero trilinear weight, at most 64 n M^2 bytes), used as a
@@ -173,7 +174,9 @@ tomo_status tomo_grid(tomo_plan_t plan, const void* d_planes, int32_t first, int
 
 /* Whole reconstruction: d_volume (device float32 [N][N][N]) is overwritten with
  * the sum over all n views, processed in internal batches of the plan's batch
- * size.  d_images: device float32 [n][M][M].  Synchronises the stream once at
+ * size; with angle_batch = 0, single-axis scans (ewald = 1, N and K at most M <= 128, M - N
+ * and M - K even) run slice by slice instead, without plane stacks and so without the
+ * rounding of 16-bit plane storage.  d_images: device float32 [n][M][M].  Synchronises the stream once at
  * the end to report TOMO_EDOMAIN. */
 tomo_status tomo_reconstruct(tomo_plan_t plan, const float* d_images, float* d_volume, void* stream);
 
@@ -227,10 +230,11 @@ tomo_status tomo_fourier_reconstruct_async(tomo_plan_t plan, const float* d_imag
 
 /* Per-kernel timing (tracing).  While enabled, every kernel launch of the plan is
  * bracketed by two HIP events recorded on the launch's stream.  Kinds:
- *   0 = contrast + DFT + filter (spectra), 1 = depth planes (inverse FFTs),
- *   2 = gridding, 3 = Fourier-space gridding (fourier = 1: operator gather with the
- *   normalisation; fourier = 2: bound, clear, splat), 4 = Fourier-space normalisation
- *   (fourier = 2 only) and inverse 3D FFT.
+ *   0 = contrast + DFT + filter (spectra), 1 = depth planes (inverse FFTs; by slices: the
+ *   transforms along x and the gridding), 2 = gridding (by slices: the transform along y),
+ *   3 = Fourier-space gridding (fourier = 1: operator gather with the normalisation;
+ *   fourier = 2: bound, clear, splat), 4 = Fourier-space normalisation (fourier = 2 only)
+ *   and inverse 3D FFT.
  * tomo_timing_read synchronises on the recorded events, adds their elapsed
  * times to the totals, and returns, per kind, total milliseconds and launch
  * counts since the last reset (reset != 0 clears them afterwards).  total_ms and

@@ -23,6 +23,7 @@ struct tomo_plan_s {
   int N = 0, M = 0, K = 0, n = 0, npairs = 0, batch = 0;
   int split = 1;                // block split of the detector-size FFT (M = P H for M > 200)
   bool axis_fast = false;
+  int axis_blocks = 0;          // view blocks of the single-axis slice kernels (0: plane stacks)
   int grid_rows = 8;            // gridding variant: 8 or 4 voxel rows per thread, 0 cubic tiles (params.tune)
   ViewGeom* d_geom = nullptr;   // [n]
   float4* d_filt = nullptr;     // [n][M][M]
@@ -412,11 +413,25 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   // and detector rows line up with voxel rows (M - N even).
   // (the LDS-fetch kernel moves 16-byte chunks: M a multiple of 4 FP32 or 8 16-bit values)
   const int vec = p->plane_dtype == TOMO_F32 ? 4 : 8;
-  bool axis = ((r.M - r.N) % 2 == 0) && (r.M % vec == 0);
+  bool axis = (r.M - r.N) % 2 == 0;
   for (int i = 0; i < r.n && axis; ++i)
     axis = geo[i].v[0] == 0.0 && geo[i].v[1] == 1.0 && geo[i].v[2] == 0.0 && geo[i].u[1] == 0.0 &&
            geo[i].d[1] == 0.0;
-  pl->axis_fast = axis;
+  pl->axis_fast = axis && r.M % vec == 0;
+  // Whole reconstructions of single-axis scans run without plane stacks where a slice fits in
+  // LDS and the caller left the batch to the library (an explicit angle_batch asks for stacks
+  // of that many views).  The partial volumes live in the stack workspace: as many view blocks
+  // as it holds, none if it holds not even one.
+  if (axis && p->ewald && p->angle_batch == 0 && tomo::axis_supported(r.M, r.N, r.K)) {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      cus = 256;
+      (void)hipGetLastError();
+    }
+    const size_t room = size_t(r.batch) * stack_view_bytes(r.M, r.K, p->plane_dtype) / tomo::axis_part_bytes(r.M, r.N);
+    pl->axis_blocks = int(std::min<size_t>(room, size_t(tomo::axis_blocks(r.M, r.n, cus))));
+  }
 
   // propagator table: (cos, sin)(pi lambda z'_p q^2), z'_p = (p - (K-1)/2) dx; twiddles
   std::vector<float2> prop(size_t(r.npairs) * r.M), twf(r.M), twi(r.M);
@@ -661,13 +676,15 @@ static tomo_status check_range(tomo_plan_t pl, int32_t first, int32_t nb) {
 }
 
 // Spectra of views [first, first+nb) into the plan's per-view slots of d_q.
-static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s) {
+// rows > 0: only their row frequencies [0, rows), without the FP16 plane scales.
+static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s,
+                               int rows = 0) {
   const size_t mm = size_t(pl->M) * pl->M;
-  float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
+  float* scale = pl->p.plane_dtype == TOMO_F16 && rows == 0 ? pl->d_scale + first : nullptr;
   hipError_t e = timed(pl, 0, s, [&] {
     return tomo::launch_spectra(pl->M, d_images, pl->d_filt + size_t(first) * mm, pl->d_tw_fwd,
                                 pl->d_q + size_t(first) * mm, pl->d_status, 1.0 / pl->p.i_in, scale, nb, s,
-                                pl->d_tw2_fwd, pl->d_l1part + size_t(pl->split * pl->split) * first);
+                                pl->d_tw2_fwd, pl->d_l1part + size_t(pl->split * pl->split) * first, rows);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   return TOMO_OK;
@@ -776,8 +793,21 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
   const size_t mm = size_t(pl->M) * pl->M;
   // spectra of all views in one launch (one workgroup per view), then per batch the
   // depth planes and the gridding
-  tomo_status st = run_spectra(pl, d_images, 0, pl->n, s);
+  tomo_status st = run_spectra(pl, d_images, 0, pl->n, s, pl->axis_blocks > 0 ? pl->M / 2 + 1 : 0);
   if (st != TOMO_OK) return st;
+  if (pl->axis_blocks > 0) {
+    float* part = static_cast<float*>(pl->d_stack);
+    hipError_t e = timed(pl, 1, s, [&] {
+      return tomo::launch_axis_slices(pl->M, pl->d_q, pl->d_prop, pl->d_tw_inv, pl->d_geom, part, pl->N, pl->K,
+                                      pl->npairs, pl->n, pl->axis_blocks, s);
+    });
+    if (e != hipSuccess) return dev_fail(pl, e, "slice kernel");
+    e = timed(pl, 2, s, [&] {
+      return tomo::launch_axis_columns(pl->M, part, pl->d_tw_inv, d_volume, pl->N, pl->axis_blocks, s);
+    });
+    if (e != hipSuccess) return dev_fail(pl, e, "column kernel");
+    return TOMO_OK;
+  }
   for (int first = 0; first < pl->n; first += pl->batch) {
     const int nb = std::min(pl->batch, pl->n - first);
     hipError_t e = timed(pl, 1, s, [&] {

@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "fft_kernels.hpp"
+#include "axis_kernels.hpp"
 #include "fft_sizes.hpp"
 #include "geom.hpp"
 #include "tomo_internal.hpp"
@@ -1312,11 +1313,11 @@ int fft_split(int M) {
 
 hipError_t launch_spectra(int M, const float* images, const float4* filt, const float2* tw_fwd,
                           float4* q, int* status, double inv_iin, float* scale, int nb, hipStream_t s,
-                          const float2* tw_half_fwd, float* l1part) {
+                          const float2* tw_half_fwd, float* l1part, int rows) {
   if (nb <= 0) return hipSuccess;
   const FftSize* f = fft_size(M);
   if (!f) return hipErrorInvalidValue;
-  return f->spectra(SpectraLaunch{images, filt, tw_fwd, tw_half_fwd, q, status, inv_iin, scale, l1part, nb, s});
+  return f->spectra(SpectraLaunch{images, filt, tw_fwd, tw_half_fwd, q, status, inv_iin, scale, l1part, nb, rows > 0 ? rows : M, s});
 }
 
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -1429,6 +1430,53 @@ hipError_t launch_grid(bool axis_fast, int dtype, const void* stack, const ViewG
     return grid_dtype<2>(axis_fast, dtype, stack, geom, scale, vol, N, M, K, nb, accumulate, flat, s);
   if (rows == 8) return grid_dtype<8>(axis_fast, dtype, stack, geom, scale, vol, N, M, K, nb, accumulate, flat, s);
   return hipErrorInvalidValue;
+}
+
+static const AxisSize* axis_size_of(int M) {
+  struct Group {
+    const AxisSize* sizes;
+    int count;
+  };
+  static const Group groups[] = {{kAxisSizesA, kAxisSizesACount}, {kAxisSizesB, kAxisSizesBCount},
+                                 {kAxisSizesC, kAxisSizesCCount}, {kAxisSizesD, kAxisSizesDCount}};
+  for (const Group& g : groups)
+    for (int i = 0; i < g.count; ++i)
+      if (g.sizes[i].M == M) return &g.sizes[i];
+  return nullptr;
+}
+
+bool axis_supported(int M, int N, int K) {
+  return axis_size_of(M) && N <= M && K <= M && (M - N) % 2 == 0 && (M - K) % 2 == 0;
+}
+
+size_t axis_part_bytes(int M, int N) {
+  const AxisSize* a = axis_size_of(M);
+  return a ? size_t(a->n_slices) * axis_slice_pitch(N) * sizeof(float) : 0;
+}
+
+int axis_blocks(int M, int n, int cus) {
+  const AxisSize* a = axis_size_of(M);
+  if (!a) return 0;
+  // One round of two workgroups per CU (what the LDS holds of the large sizes): 128^3 from 180
+  // views takes 337 us with 4 blocks (512 workgroups), 406 with 2 and 445 with 3.  More blocks
+  // fill small volumes' CUs further but add partial slices to sum: 64^3 from 90 views takes 36 +
+  // 6.6 us (slices + columns) with the 16 blocks of this rule, 49 + 5.4 with 8 and 35 + 8.0 with
+  // 24.  At least three views per block: below that the tables' set-up outweighs the split.
+  return std::max(1, std::min(n / 3, 2 * cus / a->units));
+}
+
+hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const float2* tw_inv, const ViewGeom* geom,
+                              float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s) {
+  const AxisSize* a = axis_size_of(M);
+  if (!a) return hipErrorInvalidValue;
+  return a->slices(AxisLaunch{q, prop, tw_inv, geom, part, nullptr, N, K, npairs, n, blocks, s});
+}
+
+hipError_t launch_axis_columns(int M, const float* part, const float2* tw_inv, float* vol, int N, int blocks,
+                               hipStream_t s) {
+  const AxisSize* a = axis_size_of(M);
+  if (!a) return hipErrorInvalidValue;
+  return a->columns(AxisLaunch{nullptr, nullptr, tw_inv, nullptr, const_cast<float*>(part), vol, N, 0, 0, 0, blocks, s});
 }
 
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab, float4* filt,
