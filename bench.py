@@ -121,7 +121,7 @@ def kernel_source_hash(method: str = "realspace") -> str:
 def sliced(w, angle_batch: int = 0) -> bool:
     """Whether tomo_reconstruct runs this workload by slices (no plane stacks): "planes" is then
     the slice kernel (transforms along x and gridding) and "grid" the column kernel."""
-    return (w.geometry == "axis" and bool(w.ewald) and angle_batch == 0 and w.M <= 128 and w.n_vox <= w.M
+    return (w.geometry == "axis" and bool(w.ewald) and angle_batch == 0 and w.M <= 192 and w.n_vox <= w.M
             and w.K <= w.M and (w.M - w.n_vox) % 2 == 0 and (w.M - w.K) % 2 == 0)
 
 

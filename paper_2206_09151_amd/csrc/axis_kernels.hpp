@@ -1,11 +1,11 @@
-// Whole single-axis reconstructions without plane stacks, for detector sizes up to 128.
+// Whole single-axis reconstructions without plane stacks, for detector sizes up to 192.
 //
 // With every view rotated about the volume's y axis and detector rows on voxel rows, the
 // gridding interpolates inside (plane, column) slices only, with the same weights in every
 // row.  It therefore commutes with the inverse transform along y: the slices can be gridded
 // row frequency by row frequency, and one inverse transform per voxel column of the finished
 // volume takes the place of one per column of every plane (half of the plane transforms), and
-// a row frequency's slice (at most 128 x 128 values) is small enough to stay in one CU's LDS
+// a row frequency's slice (at most 192 x 192 values) is small enough to stay in one CU's LDS
 // between its transforms along x and its gridding, so no plane is ever written to memory.
 //
 //   k_axis_slices  workgroup (row unit, block of views): per view, the transforms along x of one
@@ -13,7 +13,9 @@
 //                  the bilinear gather of the N x N voxels of the slice, summed over the block's
 //                  views in ascending order in registers; partial slices out.
 //   k_axis_columns sums the partial slices of the blocks in ascending order and runs the inverse
-//                  transform along y of every voxel column, two columns per complex transform.
+//                  transform along y of every voxel column, two columns per complex transform,
+//                  in FP64: errors of the views' transforms average out over the scan, those of
+//                  this one would not.
 //
 // The planes are real, so row frequencies 0 .. M/2 carry everything: M real slices, two for each
 // frequency r (the real and the imaginary part of its row transforms) and one each for 0 and, with
@@ -38,7 +40,9 @@
 // plane transforms and 386 us of gridding per reconstruction.  What moved it: rows of the spectrum
 // fetched into LDS one view ahead (650 -> 393 us; as scalar loads their latency was exposed on
 // every view), the four voxels of a quarter-turn orbit sharing one set of weights (393 -> 376),
-// two workgroups per CU (376 -> 337).
+// two workgroups per CU (376 -> 337).  From M = 135 on one workgroup fills a CU, and from 160 on
+// some of a thread's 40 to 60 transform and propagation values spill: 160^3 from 60 views takes
+// 391 us (plane stacks: 817 + 264), 192^3 869 us (882 + 474).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -57,6 +61,7 @@ constexpr int axis_pitch(int M) {
   // of an 8 x 8 patch meet 1.95 bank cycles per read at these residues in a count over a
   // half-turn, 2.4 at 15 and 17 and 4.4 at 1 and 31
   int p = (M + 2) | 1;
+  if (M == 192) return 195;                             // 197 cells would not fit in LDS
   while (p % 32 < 5 || p % 32 > 27 || (p % 32 > 13 && p % 32 < 19)) p += 2;
   return p;
 }
@@ -117,6 +122,13 @@ template <> struct AxisShape<108> : AxisShapeOf<108, 12, 9, true> {};
 template <> struct AxisShape<120> : AxisShapeOf<120, 15, 8, true> {};
 template <> struct AxisShape<125> : AxisShapeOf<125, 25, 5, true> {};
 template <> struct AxisShape<128> : AxisShapeOf<128, 16, 8, true> {};
+template <> struct AxisShape<135> : AxisShapeOf<135, 27, 5, true> {};
+template <> struct AxisShape<144> : AxisShapeOf<144, 18, 8, true> {};
+template <> struct AxisShape<150> : AxisShapeOf<150, 25, 6, true> {};
+template <> struct AxisShape<160> : AxisShapeOf<160, 20, 8, true> {};
+template <> struct AxisShape<162> : AxisShapeOf<162, 27, 6, true> {};
+template <> struct AxisShape<180> : AxisShapeOf<180, 30, 6, true> {};
+template <> struct AxisShape<192> : AxisShapeOf<192, 24, 8, true> {};
 
 // Partial slices: [block][2 PAIRS][pitch] float, pitch = N^2 rounded up to even.
 __host__ __device__ inline unsigned axis_slice_pitch(int N) { return (unsigned(N) * unsigned(N) + 1u) & ~1u; }
@@ -441,21 +453,22 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
 
 template <int M>
 __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* __restrict__ part,
-                                                                   const float2* __restrict__ tw,
                                                                    float* __restrict__ vol, int N, int blocks) {
   using S = AxisShape<M>;
   constexpr int R1 = S::R1, R2 = S::R2, E = S::E, CP = S::CP, CL = S::CL;
-  __shared__ float2 cells[CL * CP];
+  __shared__ double2 cells[CL * CP];
+  __shared__ double2 tw[M];                               // exp(+i 2 pi k / M)
   const int t = threadIdx.x, s = t / CL;
   const int nn = N * N;
   const int col = (blockIdx.x * CL + t % CL) * 2;       // flattened (z, x) column pair col, col + 1
   const bool live = col < nn;
   const unsigned pitch = axis_slice_pitch(N);
-  float2* mine = cells + (t % CL) * CP;
+  for (int i = t; i < M; i += S::CT) sincospi(2.0 * i / M, &tw[i].y, &tw[i].x);
+  double2* mine = cells + (t % CL) * CP;
   // sum of the blocks' partial slices, and the full spectrum a + i b of the column pair from the
   // half spectra a, b of its columns
   for (int r = s; r < S::PAIRS; r += S::CT / CL) {
-    float2 o = make_float2(0.0f, 0.0f), p = make_float2(0.0f, 0.0f);   // the columns' two slices of pair r
+    double2 o = make_double2(0.0, 0.0), p = make_double2(0.0, 0.0);   // the columns' two slices of pair r
     if (live) {
       const float2* src = reinterpret_cast<const float2*>(part + size_t(2 * r) * pitch + col);
       const size_t step = size_t(S::PAIRS) * pitch;
@@ -466,20 +479,20 @@ __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* 
       }
     }
     // odd N: the last pair has one column; odd M: pair 0 has one slice
-    if (col + 1 >= nn) o.y = p.y = 0.0f;
-    if (M % 2 != 0 && r == 0) p = make_float2(0.0f, 0.0f);
-    const float2 a = make_float2(o.x, p.x), b = make_float2(o.y, p.y);
+    if (col + 1 >= nn) o.y = p.y = 0.0;
+    if (M % 2 != 0 && r == 0) p = make_double2(0.0, 0.0);
+    const double2 a = make_double2(o.x, p.x), b = make_double2(o.y, p.y);
     if (r == 0) {
-      mine[0] = make_float2(a.x, b.x);
-      if (M % 2 == 0) mine[M / 2] = make_float2(a.y, b.y);
+      mine[0] = make_double2(a.x, b.x);
+      if (M % 2 == 0) mine[M / 2] = make_double2(a.y, b.y);
     } else {
-      mine[r] = make_float2(a.x - b.y, a.y + b.x);
-      mine[M - r] = make_float2(a.x + b.y, b.x - a.y);
+      mine[r] = make_double2(a.x - b.y, a.y + b.x);
+      mine[M - r] = make_double2(a.x + b.y, b.x - a.y);
     }
   }
   __syncthreads();
   const bool transforms = s < R2;
-  float2 x[S::XN];
+  double2 x[S::XN];
   if (transforms) {
 #pragma unroll
     for (int r = 0; r < R1; ++r) x[r] = mine[s + R2 * r];
@@ -503,7 +516,7 @@ __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* 
   for (int e = 0; e < E; ++e) {
     const int k = s * E + e;
     if (E * R2 > R1 && k >= R1) continue;
-    float2 y[R2];
+    double2 y[R2];
 #pragma unroll
     for (int rr = 0; rr < R2; ++rr) y[rr] = mine[k + R1 * rr];
     Dft<R2, true>::run(y);
@@ -512,10 +525,10 @@ __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* 
       const int iy = k + R1 * k2 - off;
       if (unsigned(iy) >= unsigned(N)) continue;
       if (pair) {
-        *reinterpret_cast<float2*>(va + iy * N) = y[k2];
+        *reinterpret_cast<float2*>(va + iy * N) = make_float2(float(y[k2].x), float(y[k2].y));
       } else {
-        va[iy * N] = y[k2].x;
-        if (second) vb[iy * N] = y[k2].y;
+        va[iy * N] = float(y[k2].x);
+        if (second) vb[iy * N] = float(y[k2].y);
       }
     }
   }
@@ -551,7 +564,7 @@ hipError_t axis_slices(const AxisLaunch& a) {
 template <int M>
 hipError_t axis_columns(const AxisLaunch& a) {
   const unsigned pairs = (unsigned(a.N) * unsigned(a.N) + 1u) / 2u;
-  hipLaunchKernelGGL(k_axis_columns<M>, dim3((pairs + AxisShape<M>::CL - 1u) / AxisShape<M>::CL), dim3(AxisShape<M>::CT), 0, a.s, a.part, a.tw,
+  hipLaunchKernelGGL(k_axis_columns<M>, dim3((pairs + AxisShape<M>::CL - 1u) / AxisShape<M>::CL), dim3(AxisShape<M>::CT), 0, a.s, a.part,
                      a.vol, a.N, a.blocks);
   return hipGetLastError();
 }
@@ -562,7 +575,7 @@ __host__ AxisSize axis_size() {
   return AxisSize{M, S::UNITS, 2 * S::PAIRS, S::LDS, S::NW, &axis_slices<M>, &axis_columns<M>};
 }
 
-extern const AxisSize kAxisSizesA[], kAxisSizesB[], kAxisSizesC[], kAxisSizesD[];
-extern const int kAxisSizesACount, kAxisSizesBCount, kAxisSizesCCount, kAxisSizesDCount;
+extern const AxisSize kAxisSizesA[], kAxisSizesB[], kAxisSizesC[], kAxisSizesD[], kAxisSizesE[];
+extern const int kAxisSizesACount, kAxisSizesBCount, kAxisSizesCCount, kAxisSizesDCount, kAxisSizesECount;
 
 }  // namespace tomo

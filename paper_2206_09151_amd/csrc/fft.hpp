@@ -45,34 +45,48 @@ struct StaticFor {
   }
 };
 
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ float2 cmul(float2 a, float2 b) {
-  return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+// Complex arithmetic and codelets serve float2 and double2 alike.
+template <class V>
+using Real = decltype(V::x);
+template <class V>
+__device__ __forceinline__ V cmake(Real<V> x, Real<V> y) {
+  V v;
+  v.x = x;
+  v.y = y;
+  return v;
 }
-__device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
+template <class V>
+__device__ __forceinline__ V cadd(V a, V b) { return cmake<V>(a.x + b.x, a.y + b.y); }
+template <class V>
+__device__ __forceinline__ V csub(V a, V b) { return cmake<V>(a.x - b.x, a.y - b.y); }
+template <class V>
+__device__ __forceinline__ V cmul(V a, V b) {
+  return cmake<V>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+template <class V>
+__device__ __forceinline__ V cscale(V a, Real<V> s) { return cmake<V>(a.x * s, a.y * s); }
 // multiply by -i (FWD) or +i (INV): the quarter turn of the transform's kernel
-template <bool INV>
-__device__ __forceinline__ float2 qturn(float2 a) {
-  return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
+template <bool INV, class V>
+__device__ __forceinline__ V qturn(V a) {
+  return INV ? cmake<V>(-a.y, a.x) : cmake<V>(a.y, -a.x);
 }
 
 // v * exp(sgn * i*2*pi*K/R), sgn = -1 forward, +1 inverse; exact for multiples of a quarter turn.
-template <int R, int K, bool INV>
-__device__ __forceinline__ float2 rot(float2 v) {
+template <int R, int K, bool INV, class V>
+__device__ __forceinline__ V rot(V v) {
   constexpr int k = ((K % R) + R) % R;
   if constexpr (k == 0) {
     return v;
   } else if constexpr (4 * k == R) {
     return qturn<INV>(v);
   } else if constexpr (2 * k == R) {
-    return make_float2(-v.x, -v.y);
+    return cmake<V>(-v.x, -v.y);
   } else if constexpr (4 * k == 3 * R) {
     return qturn<!INV>(v);
   } else {
-      constexpr float c = float(ce_cos_turn(k, R));
-      constexpr float s = float(INV ? ce_sin_turn(k, R) : -ce_sin_turn(k, R));
-      return make_float2(v.x * c - v.y * s, v.x * s + v.y * c);
+      constexpr Real<V> c = Real<V>(ce_cos_turn(k, R));
+      constexpr Real<V> s = Real<V>(INV ? ce_sin_turn(k, R) : -ce_sin_turn(k, R));
+      return cmake<V>(v.x * c - v.y * s, v.x * s + v.y * c);
   }
 }
 
@@ -83,13 +97,15 @@ struct Dft;
 
 template <bool INV>
 struct Dft<1, INV> {
-  __device__ __forceinline__ static void run(float2*) {}
+  template <class V>
+  __device__ __forceinline__ static void run(V*) {}
 };
 
 template <bool INV>
 struct Dft<2, INV> {
-  __device__ __forceinline__ static void run(float2* x) {
-    float2 a = x[0], b = x[1];
+  template <class V>
+  __device__ __forceinline__ static void run(V* x) {
+    V a = x[0], b = x[1];
     x[0] = cadd(a, b);
     x[1] = csub(a, b);
   }
@@ -97,12 +113,13 @@ struct Dft<2, INV> {
 
 template <bool INV>
 struct Dft<3, INV> {
-  __device__ __forceinline__ static void run(float2* x) {
-    constexpr float h = 0.86602540378443864676f;  // sin(2 pi / 3)
-    float2 t1 = cadd(x[1], x[2]);
-    float2 t2 = csub(x[1], x[2]);
-    float2 m = make_float2(x[0].x - 0.5f * t1.x, x[0].y - 0.5f * t1.y);
-    float2 r = qturn<INV>(cscale(t2, h));  // -+ i * sin(2pi/3) * (x1 - x2)
+  template <class V>
+  __device__ __forceinline__ static void run(V* x) {
+    constexpr Real<V> h = Real<V>(0.86602540378443864676);  // sin(2 pi / 3)
+    V t1 = cadd(x[1], x[2]);
+    V t2 = csub(x[1], x[2]);
+    V m = cmake<V>(x[0].x - Real<V>(0.5) * t1.x, x[0].y - Real<V>(0.5) * t1.y);
+    V r = qturn<INV>(cscale(t2, h));  // -+ i * sin(2pi/3) * (x1 - x2)
     x[0] = cadd(x[0], t1);
     x[1] = cadd(m, r);
     x[2] = csub(m, r);
@@ -111,9 +128,10 @@ struct Dft<3, INV> {
 
 template <bool INV>
 struct Dft<4, INV> {
-  __device__ __forceinline__ static void run(float2* x) {
-    float2 a = cadd(x[0], x[2]), b = csub(x[0], x[2]);
-    float2 c = cadd(x[1], x[3]), d = qturn<INV>(csub(x[1], x[3]));
+  template <class V>
+  __device__ __forceinline__ static void run(V* x) {
+    V a = cadd(x[0], x[2]), b = csub(x[0], x[2]);
+    V c = cadd(x[1], x[3]), d = qturn<INV>(csub(x[1], x[3]));
     x[0] = cadd(a, c);
     x[2] = csub(a, c);
     x[1] = cadd(b, d);
@@ -123,17 +141,18 @@ struct Dft<4, INV> {
 
 template <bool INV>
 struct Dft<5, INV> {
-  __device__ __forceinline__ static void run(float2* x) {
-    constexpr float c1 = float(ce_cos_turn(1, 5)), c2 = float(ce_cos_turn(2, 5));
-    constexpr float s1 = float(ce_sin_turn(1, 5)), s2 = float(ce_sin_turn(2, 5));
-    float2 a1 = cadd(x[1], x[4]), a2 = cadd(x[2], x[3]);
-    float2 b1 = csub(x[1], x[4]), b2 = csub(x[2], x[3]);
-    float2 m1 = make_float2(x[0].x + c1 * a1.x + c2 * a2.x, x[0].y + c1 * a1.y + c2 * a2.y);
-    float2 m2 = make_float2(x[0].x + c2 * a1.x + c1 * a2.x, x[0].y + c2 * a1.y + c1 * a2.y);
+  template <class V>
+  __device__ __forceinline__ static void run(V* x) {
+    constexpr Real<V> c1 = Real<V>(ce_cos_turn(1, 5)), c2 = Real<V>(ce_cos_turn(2, 5));
+    constexpr Real<V> s1 = Real<V>(ce_sin_turn(1, 5)), s2 = Real<V>(ce_sin_turn(2, 5));
+    V a1 = cadd(x[1], x[4]), a2 = cadd(x[2], x[3]);
+    V b1 = csub(x[1], x[4]), b2 = csub(x[2], x[3]);
+    V m1 = cmake<V>(x[0].x + c1 * a1.x + c2 * a2.x, x[0].y + c1 * a1.y + c2 * a2.y);
+    V m2 = cmake<V>(x[0].x + c2 * a1.x + c1 * a2.x, x[0].y + c2 * a1.y + c1 * a2.y);
     // qturn applies the transform's sign of i
-    float2 n1 = qturn<INV>(make_float2(s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y));
-    float2 n2 = qturn<INV>(make_float2(s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y));
-    x[0] = make_float2(x[0].x + a1.x + a2.x, x[0].y + a1.y + a2.y);
+    V n1 = qturn<INV>(cmake<V>(s1 * b1.x + s2 * b2.x, s1 * b1.y + s2 * b2.y));
+    V n2 = qturn<INV>(cmake<V>(s2 * b1.x - s1 * b2.x, s2 * b1.y - s1 * b2.y));
+    x[0] = cmake<V>(x[0].x + a1.x + a2.x, x[0].y + a1.y + a2.y);
     x[1] = cadd(m1, n1);
     x[4] = csub(m1, n1);
     x[2] = cadd(m2, n2);
@@ -151,11 +170,12 @@ struct Dft {
   static constexpr int A = first_factor(R);
   static constexpr int B = R / A;
   static_assert(A * B == R && A > 1 && B > 1, "only 2,3,5-smooth radices");
-  __device__ __forceinline__ static void run(float2* x) {
-    float2 t[R];
+  template <class V>
+  __device__ __forceinline__ static void run(V* x) {
+    V t[R];
     StaticFor<0, A>::run([&](auto ca) {
       constexpr int a = decltype(ca)::value;
-      float2 s[B];
+      V s[B];
 #pragma unroll
       for (int b = 0; b < B; ++b) s[b] = x[a + A * b];
       Dft<B, INV>::run(s);
@@ -166,7 +186,7 @@ struct Dft {
     });
 #pragma unroll
     for (int kb = 0; kb < B; ++kb) {
-      float2 s[A];
+      V s[A];
 #pragma unroll
       for (int a = 0; a < A; ++a) s[a] = t[a * B + kb];
       Dft<A, INV>::run(s);

@@ -803,7 +803,7 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
     });
     if (e != hipSuccess) return dev_fail(pl, e, "slice kernel");
     e = timed(pl, 2, s, [&] {
-      return tomo::launch_axis_columns(pl->M, part, pl->d_tw_inv, d_volume, pl->N, pl->axis_blocks, s);
+      return tomo::launch_axis_columns(pl->M, part, d_volume, pl->N, pl->axis_blocks, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "column kernel");
     return TOMO_OK;

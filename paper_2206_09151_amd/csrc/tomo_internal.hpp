@@ -47,7 +47,7 @@ hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, 
 constexpr int kGridTilt8 = -8, kGridTilt4 = -4, kGridTilt2 = -2;
 hipError_t launch_grid(bool axis_fast, int dtype, const void* stack, const ViewGeom* geom, const float* scale,
                        float* vol, int N, int M, int K, int nb, int accumulate, int flat, hipStream_t s, int rows);
-// Single-axis reconstruction from the spectra without plane stacks (axis_kernels.hpp): M up to 128,
+// Single-axis reconstruction from the spectra without plane stacks (axis_kernels.hpp): M up to 192,
 // N <= M and K <= M, M - N and M - K even.  part: `blocks` partial volumes of axis_part_bytes each.
 bool axis_supported(int M, int N, int K);
 size_t axis_part_bytes(int M, int N);
@@ -55,8 +55,7 @@ size_t axis_part_bytes(int M, int N);
 int axis_blocks(int M, int n, int cus);
 hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const float2* tw_inv, const ViewGeom* geom,
                               float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s);
-hipError_t launch_axis_columns(int M, const float* part, const float2* tw_inv, float* vol, int N, int blocks,
-                               hipStream_t s);
+hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s);
 // Plan-time tables.
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab,
                                float4* filt, hipStream_t s);

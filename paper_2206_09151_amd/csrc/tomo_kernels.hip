@@ -1438,7 +1438,8 @@ static const AxisSize* axis_size_of(int M) {
     int count;
   };
   static const Group groups[] = {{kAxisSizesA, kAxisSizesACount}, {kAxisSizesB, kAxisSizesBCount},
-                                 {kAxisSizesC, kAxisSizesCCount}, {kAxisSizesD, kAxisSizesDCount}};
+                                 {kAxisSizesC, kAxisSizesCCount}, {kAxisSizesD, kAxisSizesDCount},
+                                 {kAxisSizesE, kAxisSizesECount}};
   for (const Group& g : groups)
     for (int i = 0; i < g.count; ++i)
       if (g.sizes[i].M == M) return &g.sizes[i];
@@ -1457,12 +1458,23 @@ size_t axis_part_bytes(int M, int N) {
 int axis_blocks(int M, int n, int cus) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return 0;
-  // One round of two workgroups per CU (what the LDS holds of the large sizes): 128^3 from 180
-  // views takes 337 us with 4 blocks (512 workgroups), 406 with 2 and 445 with 3.  More blocks
-  // fill small volumes' CUs further but add partial slices to sum: 64^3 from 90 views takes 36 +
-  // 6.6 us (slices + columns) with the 16 blocks of this rule, 49 + 5.4 with 8 and 35 + 8.0 with
-  // 24.  At least three views per block: below that the tables' set-up outweighs the split.
-  return std::max(1, std::min(n / 3, 2 * cus / a->units));
+  // Workgroups (units x blocks) run in rounds of at most two per CU, each over its block's views
+  // (and about two views' time of set-up); every block adds a partial volume to sum, a fifth of a
+  // view's time.  Measured: 128^3 from 180 views takes 337 us with the 4 blocks of this rule (512
+  // workgroups), 406 with 2 and 445 with 3; 64^3 from 90 views 36 + 6.6 us (slices + columns) with
+  // its 16, 49 + 5.4 with 8 and 35 + 8.0 with 24.  At least three views per block.
+  const int slots = cus * std::max(1, std::min(2, 160 * 1024 / a->lds));
+  int best = 1;
+  double least = 0.0;
+  for (int b = 1; b <= std::max(1, n / 3); ++b) {
+    const int rounds = (a->units * b + slots - 1) / slots;
+    const double cost = rounds * double((n + b - 1) / b + 2) + 0.2 * b;
+    if (b == 1 || cost < least) {
+      least = cost;
+      best = b;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const float2* tw_inv, const ViewGeom* geom,
@@ -1472,11 +1484,10 @@ hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const 
   return a->slices(AxisLaunch{q, prop, tw_inv, geom, part, nullptr, N, K, npairs, n, blocks, s});
 }
 
-hipError_t launch_axis_columns(int M, const float* part, const float2* tw_inv, float* vol, int N, int blocks,
-                               hipStream_t s) {
+hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return hipErrorInvalidValue;
-  return a->columns(AxisLaunch{nullptr, nullptr, tw_inv, nullptr, const_cast<float*>(part), vol, N, 0, 0, 0, blocks, s});
+  return a->columns(AxisLaunch{nullptr, nullptr, nullptr, nullptr, const_cast<float*>(part), vol, N, 0, 0, 0, blocks, s});
 }
 
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab, float4* filt,

@@ -14,7 +14,7 @@ from test_gpu_parity import assert_close
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-SIZES = [m for m in _problems.smooth_sizes() if m <= 128]
+SIZES = [m for m in _problems.smooth_sizes() if m <= 192]
 
 
 def _problem(m, n_vox, k, n):
