@@ -128,9 +128,9 @@ typedef struct {
  *   out    receives the plan; untouched on error.
  * Supported: M every 2^a 3^b 5^c in [16, 256] (others: TOMO_EUNSUPPORTED); N in [2, 1024];
  * K in [1, 2N]; with fourier = 1 or 2 also N = 2^a 3^b 5^c in [16, 256].  Single-axis
- * plans whose stack rows are whole 16-byte chunks (M a multiple of 4, or of 8 for 16-bit
- * planes, and M - N even) use the single-axis gridding kernel; the others use the
- * general-frame kernels (the cubic-tile kernel when M is not such a multiple). */
+ * plans with M - N even use the single-axis gridding kernels (16-bit planes of odd M only
+ * without curvature); the others use the general-frame kernels (the cubic-tile kernel when
+ * stack rows are not whole 16-byte chunks: M not a multiple of 4, or of 8 for 16-bit planes). */
 tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* vaxes,
                       const double* dist, void* stream, tomo_plan_t* out);
 

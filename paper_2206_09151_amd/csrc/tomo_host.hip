@@ -411,13 +411,16 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   if (p->weight_mode == TOMO_RAMP_AXIS) axis_weights(dirs, r.n, geo);
   // Single-axis gather path: every v is exactly the y axis and u, d lie in the xz plane,
   // and detector rows line up with voxel rows (M - N even).
-  // (the LDS-fetch kernel moves 16-byte chunks: M a multiple of 4 FP32 or 8 16-bit values)
+  // (the LDS-fetch kernels move 16-byte chunks -- M a multiple of 4 FP32 or 8 16-bit values -- or,
+  // for single-axis plans, dwords: every M for FP32, even M for 16-bit stacks; a single plane per
+  // view is fetched value by value)
   const int vec = p->plane_dtype == TOMO_F32 ? 4 : 8;
   bool axis = (r.M - r.N) % 2 == 0;
   for (int i = 0; i < r.n && axis; ++i)
     axis = geo[i].v[0] == 0.0 && geo[i].v[1] == 1.0 && geo[i].v[2] == 0.0 && geo[i].u[1] == 0.0 &&
            geo[i].d[1] == 0.0;
-  pl->axis_fast = axis && r.M % vec == 0;
+  pl->axis_fast = axis && (p->plane_dtype == TOMO_F32 || r.M % 2 == 0 || !p->ewald);
+  if (pl->axis_fast && p->ewald && r.M % vec != 0) pl->grid_rows = 4;   // the dword fetch has one shape
   // Whole reconstructions of single-axis scans run without plane stacks where a slice fits in
   // LDS and the caller left the batch to the library (an explicit angle_batch asks for stacks
   // of that many views).  The partial volumes live in the stack workspace: as many view blocks
@@ -589,8 +592,9 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   if ((p->tune == 2 || r.M % vec != 0) && !pl->axis_fast) pl->grid_rows = 0;
   if (p->tune >= 3 && !pl->axis_fast && r.M % vec == 0)
     pl->grid_rows = p->tune == 3 ? tomo::kGridTilt4 : p->tune == 4 ? tomo::kGridTilt8 : tomo::kGridTilt2;
-  if (p->tune == 5 && pl->axis_fast) pl->grid_rows = 2;
-  if (p->tune == 1) {
+  if (p->tune == 5 && pl->axis_fast && r.M % vec == 0) pl->grid_rows = 2;
+  // (without depth planes or with the dword fetch a single-axis plan has one kernel)
+  if (p->tune == 1 && !(pl->axis_fast && (!p->ewald || r.M % vec != 0))) {
     // time the gridding variants on a full batch of (zero) stacks and keep the fastest; results
     // do not depend on the choice.  Each timed launch follows a plane-kernel launch that writes
     // the batch's stacks, as in a reconstruction, so that the caches hold what they hold then

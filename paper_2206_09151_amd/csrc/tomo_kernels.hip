@@ -110,6 +110,10 @@ __device__ __forceinline__ int opaque(int v) {
 // (50.8 against 47.2 us per 32-view launch).  A 16-bit tap pair (lc, lc + 1) is the 32-bit
 // window at bit 16 (lc & 1) of the two dwords from element 2 (lc >> 1); FP16 values are
 // unscaled through the interpolation weights (the per-view scale is a power of two).
+//
+// CH: bytes per fetched slot.  Stack rows that are not whole 16-byte chunks are fetched dword by
+// dword (CH = 4) into boxes of the same pitches: 28 us per 16-view BF16 launch at N = 96, M = 100,
+// where the general-frame cubic tiles, which served those rows before, took 182 us.
 template <class InT>
 struct DmaBox;
 template <>
@@ -127,23 +131,25 @@ struct DmaBox<__half> {
 typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr unsigned kOutOfRange = 0x80000000u;      // beyond every buffer range: reads as zero
 
-template <int YB, class InT>
+template <int YB, class InT, int CH>
 __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ stack,
                                                        const ViewGeom* __restrict__ geom,
                                                        const float* __restrict__ scale,
                                                        float* __restrict__ vol, int N, int M, int K, int nb,
-                                                       int accumulate, int flat, double hm, double hk) {
-  constexpr int VEC = DmaBox<InT>::VEC, BOXW = DmaBox<InT>::BOXW, QN = BOXW / VEC;
+                                                       int accumulate, double hm, double hk) {
   constexpr int ES = int(sizeof(InT));                  // bytes per stored value
-  constexpr int QP = ES == 2 ? QN + 1 : QN;             // 16-byte slots per staged (row, plane)
-  constexpr int PITCH = QP * 4;                         // dwords per staged (row, plane)
+  constexpr int VEC = CH / ES;                          // values per chunk (slot) of CH bytes
+  constexpr int BOXW = CH == 16 ? DmaBox<InT>::BOXW : 28;
+  constexpr int PITCH = ES == 2 ? 20 : 28;              // dwords per staged (row, plane)
+  constexpr int QP = PITCH * 4 / CH;                    // slots per staged (row, plane)
+  constexpr int DW = CH / 4;                            // dwords per slot
   constexpr int NE = YB * AX_BOXH * QP;                 // slots per staged view
   constexpr int PER = (NE + 255) / 256;                 // loads per thread per view
   // 16-bit values: one dword of padding, the pair read may touch the dword after a row's last
   constexpr int PAD = ES == 2 ? 4 : 0;
   constexpr bool ONE_BOX = YB >= 4 && ES == 4;
-  __shared__ __attribute__((aligned(16))) unsigned box0[NE * 4 + PAD];
-  __shared__ __attribute__((aligned(16))) unsigned box1[ONE_BOX ? 4 : NE * 4 + PAD];
+  __shared__ __attribute__((aligned(16))) unsigned box0[NE * DW + PAD];
+  __shared__ __attribute__((aligned(16))) unsigned box1[ONE_BOX ? 4 : NE * DW + PAD];
   const int ntx = (N + GT - 1) / GT;
   const int tiles = ntx * ntx;
   const int wg = blockIdx.x, xcd = wg & 7, k = wg >> 3;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
   const double rx = ix - c, rz = iz - c;
   const int rowoff = (M - N) / 2;
   const size_t view_sz = size_t(K) * M * M;
-  const int wbase = (threadIdx.x & ~63) * 4;            // this wave's first dword in a box, per load
+  const int wbase = (threadIdx.x & ~63) * DW;           // this wave's first dword in a box, per load
   const int lane = threadIdx.x & 63;
 
   // Box origins: lane l of every wave computes the origin of view obase + l (FP64, from
@@ -183,9 +189,9 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
         const double pmin = fmin(g.d[0] * ax, g.d[0] * bx) + fmin(g.d[2] * az, g.d[2] * bz) + hk;
         const double pmax = fmax(g.d[0] * ax, g.d[0] * bx) + fmax(g.d[2] * az, g.d[2] * bz) + hk;
         cc = int(floor(cmin)) & ~(VEC - 1);
-        pp = flat ? 0 : int(floor(pmin));
+        pp = int(floor(pmin));
         ww = min(BOXW, (int(floor(cmax)) - cc + 3 + VEC - 1) & ~(VEC - 1));
-        hh = flat ? 2 : min(AX_BOXH, int(floor(pmax)) - pp + 3);
+        hh = min(AX_BOXH, int(floor(pmax)) - pp + 3);
       }
       lane_c0 = cc;
       lane_p0 = pp;
@@ -208,13 +214,17 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
     const int e = threadIdx.x + 256 * i;
     const int q = e % QP, pl = (e / QP) % AX_BOXH, j = e / (QP * AX_BOXH);
     const int row = y0 + j + rowoff;
-    cq[i] = VEC * q;                                    // the spare slot (q = QN) has cq = BOXW >= cw
+    cq[i] = VEC * q;                                    // spare slots have cq >= BOXW >= cw
     cpl[i] = pl;
     crow[i] = (e < NE && y0 + j < N && unsigned(row) < unsigned(M)) ? row * K : -1;
     cfo[i] = rows_in ? unsigned((row * K + pl) * M + VEC * q) * unsigned(ES) : kOutOfRange;
   }
   // slot i exists for every thread below the last load; in the last one only below NE
   auto has = [&](int i) { return NE % 256 == 0 || i < PER - 1 || int(threadIdx.x) + 256 * i < NE; };
+  auto fetch_slot = [&](const __amdgpu_buffer_rsrc_t& rs, unsigned* to, unsigned ofs, int base) {
+    if constexpr (CH == 16) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)to, 16, int(ofs), base, 0, 0);
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)to, 4, int(ofs), base, 0, 0);
+  };
   auto load = [&](int n, int c0, int p0, int cw, int bh, unsigned* dst) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<InT*>(stack + size_t(n) * view_sz), short(0), int(view_sz * ES), 0x00020000);
@@ -224,8 +234,7 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
 #pragma unroll
       for (int i = 0; i < PER; ++i)
         if (has(i) && cpl[i] < bh && cq[i] < cw)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i + wbase), 16,
-                                                   int(cfo[i]), so, 0, 0);
+          fetch_slot(rs, dst + 256 * DW * i + wbase, cfo[i], so);
     } else {
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
@@ -233,8 +242,7 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
           const int pp = p0 + cpl[i], cc = c0 + cq[i];
           const bool ok = crow[i] >= 0 && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
           const unsigned off = ok ? unsigned((crow[i] + pp) * M + cc) * unsigned(ES) : kOutOfRange;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i + wbase), 16, int(off), 0,
-                                                   0, 0);
+          fetch_slot(rs, dst + 256 * DW * i + wbase, off, 0);
         }
       }
     }
@@ -260,11 +268,8 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
   auto interp = [&](const unsigned* bx, int cb, int pb, int n) {
     if (live) {
       const ViewGeom& g = geom[n];
-      // flat (one plane, K = 1): a zero depth direction gives fp = 0 (hk = 0, origin plane
-      // 0), so lp = 0 and tz = 0, and the second plane's taps (zero-filled) get weight 0
-      const double d0 = flat ? 0.0 : g.d[0], d2 = flat ? 0.0 : g.d[2];
       const double fc = fmax(g.u[0] * rx + g.u[2] * rz + (hm - cb), 0.0);
-      const double fp = fmax(d0 * rx + d2 * rz + (hk - pb), 0.0);
+      const double fp = fmax(g.d[0] * rx + g.d[2] * rz + (hk - pb), 0.0);
       // fc, fp >= 0: truncation is the floor, fract the remainder (exact in FP64)
       const int lc = int(fc), lp = int(fp);
       float tx = float(__builtin_amdgcn_fract(fc));
@@ -335,6 +340,137 @@ __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ s
     }
   }
   if (!live) return;
+#pragma unroll
+  for (int j = 0; j < YB; ++j) {
+    const int iy = y0 + j;
+    if (iy < N) {
+      float* dst = vol + (size_t(iz) * N + iy) * N + ix;
+      *dst = accumulate ? *dst + acc[j] : acc[j];
+    }
+  }
+}
+
+// Single-axis views without depth planes (one plane per view, linear in the detector column): the
+// footprint of a 16 x 16 (x, z) tile is a run of at most 26 columns of each of its YB rows.  Every
+// thread fetches one value per view (row t % YB, column t / YB of the view's window of 256 / YB
+// columns, zero outside the stack), VB views ahead of their use; in LDS the YB rows of a column lie
+// side by side, so a voxel column's taps are 2 YB consecutive values, read 16 bytes at a time, and
+// the column coordinate and its weights are computed once for the YB rows.  Two LDS buffers of VB
+// views alternate, one barrier per VB views.  Lanes are laid out in 4 x 2 blocks of voxels, whose
+// taps fall into at most five adjacent columns.
+// Bound by LDS reads (8 bytes per update) and vector issue (about 5 instructions per update): 60 us
+// for 180 views at 128^3 (6.3e12 updates/s); staged as a general (plane, column) box, whose second
+// plane is empty, with one row per read, it took 222 us.
+template <int YB, class InT>
+__global__ __launch_bounds__(256) void k_grid_axis_flat(const InT* __restrict__ stack,
+                                                        const ViewGeom* __restrict__ geom,
+                                                        const float* __restrict__ scale,
+                                                        float* __restrict__ vol, int N, int M, int nb,
+                                                        int accumulate, double hm) {
+  constexpr int VB = 4, W = 256 / YB;                   // views per round, columns per window
+  constexpr int ES = int(sizeof(InT));
+  static_assert(YB == 8, "a window of 32 columns holds the 26 of a footprint");
+  __shared__ __attribute__((aligned(16))) float win[2][VB][W * YB];
+  const int ntx = (N + GT - 1) / GT;
+  const int tiles = ntx * ntx;
+  const int wg = blockIdx.x, xcd = wg & 7, k = wg >> 3;
+  const int yblk = xcd + 8 * (k / tiles), tile = k % tiles;
+  const int y0 = yblk * YB;
+  if (y0 >= N) return;                                  // uniform
+  const int tx0 = (tile % ntx) * GT, tz0 = (tile / ntx) * GT;
+  const int t = threadIdx.x, lane = t & 63;
+  const int ix = tx0 + (t & 3) + 4 * ((t >> 3) & 3);
+  const int iz = tz0 + ((t >> 2) & 1) + 2 * (t >> 5);
+  const double c = 0.5 * (N - 1);
+  const double rx = ix - c, rz = iz - c;
+  // this thread's value of a view: row y0 + t % YB, column c0 + t / YB of the stack
+  const int row = y0 + t % YB + (M - N) / 2, wc = t / YB;
+  const bool row_ok = y0 + t % YB < N && unsigned(row) < unsigned(M);
+  const unsigned row_ofs = unsigned(row) * unsigned(M) * unsigned(ES);
+  const size_t view_sz = size_t(M) * M;
+
+  // window origins, one view per lane (FP64, from the tile corners)
+  int obase = -64, lane_c0 = 0;
+  auto origin = [&](int n) {
+    if (n >= obase + 64) {
+      obase = n;
+      const int v = n + lane;
+      if (v < nb) {
+        const int t0 = opaque(tx0), z0 = opaque(tz0);
+        const double ax = t0 - c, bx = t0 + GT - 1 - c, az = z0 - c, bz = z0 + GT - 1 - c;
+        const ViewGeom& g = geom[v];
+        lane_c0 = int(floor(fmin(g.u[0] * ax, g.u[0] * bx) + fmin(g.u[2] * az, g.u[2] * bz) + hm));
+      }
+    }
+    return __builtin_amdgcn_readlane(lane_c0, n - obase);
+  };
+  int corg[2][VB];                                      // origins of the views in flight and in use
+  float buf[VB];
+  auto fetch = [&](int n0, int (&org)[VB]) {
+#pragma unroll
+    for (int i = 0; i < VB; ++i) {
+      buf[i] = 0.0f;
+      org[i] = 0;
+      if (n0 + i < nb) {                                // uniform
+        org[i] = origin(n0 + i);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<InT*>(stack + size_t(n0 + i) * view_sz), short(0), int(view_sz * ES), 0x00020000);
+        const int cc = org[i] + wc;
+        const unsigned ofs = row_ok && unsigned(cc) < unsigned(M) ? row_ofs + unsigned(cc) * unsigned(ES) : kOutOfRange;
+        if constexpr (ES == 4) {
+          buf[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, int(ofs), 0, 0));
+        } else {
+          const unsigned short h = __builtin_amdgcn_raw_buffer_load_b16(rs, int(ofs), 0, 0);
+          if constexpr (std::is_same<InT, __half>::value) buf[i] = __half2float(__ushort_as_half(h));
+          else buf[i] = __uint_as_float(unsigned(h) << 16);
+        }
+      }
+    }
+  };
+  float acc[YB];
+#pragma unroll
+  for (int j = 0; j < YB; ++j) acc[j] = 0.0f;
+  // coordinates as 1.5 2^20 + value: integer part in the high word, fraction in units of 2^-32 below
+  constexpr double kBias = 1572864.0;
+  constexpr unsigned kBiasHi = 0x41380000u;
+  const int rounds = (nb + VB - 1) / VB;
+  fetch(0, corg[0]);
+  for (int r = 0; r < rounds; ++r) {
+    float (*dst)[W * YB] = win[r & 1];
+#pragma unroll
+    for (int i = 0; i < VB; ++i) {
+      dst[i][t] = buf[i];
+      corg[1][i] = corg[0][i];
+    }
+    __syncthreads();
+    if (r + 1 < rounds) fetch((r + 1) * VB, corg[0]);
+#pragma unroll
+    for (int i = 0; i < VB; ++i) {
+      const int n = r * VB + i;
+      if (n >= nb) break;                               // uniform
+      const ViewGeom& g = geom[n];
+      const double fc = g.u[0] * rx + g.u[2] * rz + (hm + kBias);
+      const unsigned long long b = __double_as_longlong(fc);
+      float tx = float(unsigned(b)) * 0x1p-32f, ux = 1.0f - tx;
+      if constexpr (std::is_same<InT, __half>::value) {
+        const float inv = 1.0f / scale[n];              // exact: the scale is a power of two
+        ux *= inv;
+        tx *= inv;
+      }
+      // voxels past the volume's edge may lie past the window: any column of it serves them
+      const unsigned lc = min(unsigned(b >> 32) - (kBiasHi + unsigned(corg[1][i])), unsigned(W - 2));
+      const float4* tap = reinterpret_cast<const float4*>(&dst[i][lc * YB]);
+#pragma unroll
+      for (int h = 0; h < YB / 4; ++h) {
+        const float4 a0 = tap[h], a1 = tap[h + YB / 4];
+        acc[4 * h + 0] = fmaf(tx, a1.x, fmaf(ux, a0.x, acc[4 * h + 0]));
+        acc[4 * h + 1] = fmaf(tx, a1.y, fmaf(ux, a0.y, acc[4 * h + 1]));
+        acc[4 * h + 2] = fmaf(tx, a1.z, fmaf(ux, a0.z, acc[4 * h + 2]));
+        acc[4 * h + 3] = fmaf(tx, a1.w, fmaf(ux, a0.w, acc[4 * h + 3]));
+      }
+    }
+  }
+  if (ix >= N || iz >= N) return;
 #pragma unroll
   for (int j = 0; j < YB; ++j) {
     const int iy = y0 + j;
@@ -1335,14 +1471,24 @@ static hipError_t grid_impl(bool axis_fast, const void* stack, const ViewGeom* g
   const dim3 grid((N + GT - 1) / GT, (N + GT - 1) / GT, (N + kYB - 1) / kYB);
   const InT* st = static_cast<const InT*>(stack);
   if (axis_fast) {
-    // flat grid: (x, z) tiles x row blocks, row blocks padded to a multiple of 8 (one XCD each).
-    // Supported sizes (M a multiple of 16, K <= 2 N <= 512) always meet the kernel's conditions.
-    if (M % DmaBox<InT>::VEC != 0 || size_t(K) * M * M * sizeof(InT) > size_t(0x7fffffff))
-      return hipErrorInvalidValue;
+    // flat grid: (x, z) tiles x row blocks, row blocks padded to a multiple of 8 (one XCD each)
+    if (size_t(K) * M * M * sizeof(InT) > size_t(0x7fffffff)) return hipErrorInvalidValue;
     const int tiles = int(grid.x * grid.y);
-    const int yblocks8 = int((grid.z + 7) / 8 * 8);
-    hipLaunchKernelGGL((k_grid_axis_dma<kYB, InT>), dim3(unsigned(tiles * yblocks8)), dim3(256), 0, s, st, geom,
-                       scale, vol, N, M, K, nb, accumulate, flat, 0.5 * (M - 1), 0.5 * (K - 1));
+    const auto blocks = [&](int rows) { return dim3(unsigned(tiles * (((N + rows - 1) / rows + 7) / 8 * 8))); };
+    if (flat) {
+      hipLaunchKernelGGL((k_grid_axis_flat<8, InT>), blocks(8), dim3(256), 0, s, st, geom, scale, vol, N, M, nb,
+                         accumulate, 0.5 * (M - 1));
+    } else if (M % DmaBox<InT>::VEC == 0) {
+      hipLaunchKernelGGL((k_grid_axis_dma<kYB, InT, 16>), blocks(kYB), dim3(256), 0, s, st, geom, scale, vol, N, M, K,
+                         nb, accumulate, 0.5 * (M - 1), 0.5 * (K - 1));
+    } else if (M % (4 / int(sizeof(InT))) == 0) {
+      // rows that are not whole 16-byte chunks: the box is fetched dword by dword, four rows
+      // (the slots of eight would take 84 registers)
+      hipLaunchKernelGGL((k_grid_axis_dma<4, InT, 4>), blocks(4), dim3(256), 0, s, st, geom, scale, vol, N, M, K, nb,
+                         accumulate, 0.5 * (M - 1), 0.5 * (K - 1));
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else if constexpr (kYB >= 4) {
     const int tiles = int(grid.x * grid.y);
     const int yblocks8 = int((grid.z + 7) / 8 * 8);

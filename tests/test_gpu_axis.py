@@ -70,3 +70,36 @@ def test_other_shapes_stay_on_the_general_path(n_vox, m, k):
     got, _ = _run(pb)
     ref = _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
     assert_close(got, ref, 1e-5, (n_vox, m, k))
+
+
+BOUND = {0: 1e-5, 1: 3 * 2.0 ** -9, 2: 3 * 2.0 ** -11}
+
+
+@pytest.mark.parametrize("m,n_vox", [(25, 25), (27, 21), (45, 45), (50, 46), (54, 54), (100, 96)])
+@pytest.mark.parametrize("dtype", [0, 1, 2], ids=["f32", "bf16", "fp16"])
+def test_stack_gridding_of_rows_that_are_not_whole_chunks(m, n_vox, dtype):
+    """Plane stacks whose rows are not whole 16-byte chunks (fetched dword by dword; 16-bit rows of
+    odd M stay on the general kernels): batches of three views."""
+    pb = _problem(m, n_vox, min(n_vox, 40), 7)
+    got, _ = _run(pb, angle_batch=3, plane_dtype=dtype)
+    ref = _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
+    if dtype == 0:
+        assert_close(got, ref, 1e-5, (m, dtype))
+    else:
+        assert np.linalg.norm(got - ref) <= BOUND[dtype] * np.linalg.norm(ref), (m, dtype)
+
+
+@pytest.mark.parametrize("m,n_vox,n", [(16, 16, 5), (25, 25, 70), (32, 30, 9), (64, 64, 4), (45, 45, 1), (32, 48, 6)])
+@pytest.mark.parametrize("dtype", [0, 1, 2], ids=["f32", "bf16", "fp16"])
+def test_flat_gridding_matches_oracle(m, n_vox, n, dtype):
+    """Without curvature (one plane per view): ragged tiles and row blocks, odd detectors, a volume
+    wider than the detector, view counts around the rounds of four and more than the 64 window
+    origins formed at once."""
+    pb = _problem(m, n_vox, 1, n)
+    pb.ewald = 0
+    got, _ = _run(pb, plane_dtype=dtype)
+    ref = _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
+    if dtype == 0:
+        assert_close(got, ref, 1e-5, (m, n, dtype))
+    else:
+        assert np.linalg.norm(got - ref) <= BOUND[dtype] * np.linalg.norm(ref), (m, n, dtype)
