@@ -106,7 +106,7 @@ def kernel_source_hash(method: str = "realspace") -> str:
     elif method == "unet":
         files = ["unet_internal.hpp", "unet_kernels.hip", "unet_host.hip"]
     else:
-        files = ["fft.hpp", "fft_kernels.hpp", "axis_kernels.hpp", "geom.hpp", "tomo_kernels.hip"] + \
+        files = ["fft.hpp", "fft_kernels.hpp", "axis_kernels.hpp", "spectra_kernels.hpp", "geom.hpp", "tomo_kernels.hip"] + \
             sorted(f for f in os.listdir(csrc) if f.startswith(("fft_sizes", "axis_sizes")))
     h = hashlib.sha256()
     for f in files:
@@ -126,10 +126,11 @@ def sliced(w, angle_batch: int = 0) -> bool:
 
 
 def slice_bytes(kind: str, w) -> float:
-    """Compulsory HBM bytes of one step of the slice path: spectra as for the stacks but only the
-    row frequencies up to M/2; the slice kernel reads those; the column kernel writes the volume."""
+    """Compulsory HBM bytes of one step of the slice path: the images read and half of their spectra
+    written; those and half of the filter read by the slice kernel, which writes one partial volume;
+    the column kernel reads it and writes the volume."""
     half = (w.M // 2 + 1) * float(w.M)
-    return {"spectra": w.n_views * (4.0 * w.M * w.M + 32.0 * half), "planes": w.n_views * 16.0 * half + 4.0 * w.M * w.n_vox ** 2,
+    return {"spectra": w.n_views * (4.0 * w.M * w.M + 8.0 * half), "planes": w.n_views * 24.0 * half + 4.0 * w.M * w.n_vox ** 2,
             "grid": 4.0 * w.M * w.n_vox ** 2 + 4.0 * w.n_vox ** 3}[kind]
 
 

@@ -26,7 +26,7 @@
 //       Y_j / M^2 = (1-i)/2 (cos(phi_j) Q1 + i sin(phi_j) Q2), and the slice's cells are complex
 //       (the constant is applied to the sums);
 //   real cells: a workgroup takes one slice; its spectrum row is the even or odd part of Q over
-//       +-r, a lane transforms the planes j and K-1-j together,
+//       the rows +-r, a lane transforms the planes j and K-1-j together,
 //       Y_j + i Y_{K-1-j} = cos(phi_j) Q1 + sin(phi_j) Q2, and the cells are real.
 // Complex cells compute a voxel's weights once for two slices, real cells need half the LDS: at
 // M = 128 two workgroups share a CU and fill each other's barriers (337 us for 180 views, against
@@ -49,6 +49,7 @@
 #include <type_traits>
 
 #include "fft.hpp"
+#include "spectra_kernels.hpp"
 #include "tomo_internal.hpp"
 
 namespace tomo {
@@ -83,7 +84,9 @@ struct AxisShapeOf {
   static constexpr int CB = REAL ? 4 : 8;             // bytes per cell
   // two zero planes on either side; REAL: one more for the unused half of an odd K's middle pair
   static constexpr int CELLS = (M + 4 + (REAL ? 1 : 0)) * P + 4;
-  static constexpr int LDS = CELLS * CB + (REAL ? 3 : 2) * M * 16;
+  static constexpr int HALF = M / 2 + 1;
+  static constexpr int QN = REAL ? HALF : 2 * M;      // values of the spectrum row(s) transformed next
+  static constexpr int LDS = CELLS * CB + QN * 16;
   static constexpr int XW = ((M + 1) / 2 + 7) / 8;
   static constexpr int VPT = (XW * XW + NW - 1) / NW;  // voxel orbits per thread (8 x 8 patches per wave)
   // registers for as many workgroups per CU as their LDS allows, where the values leave room
@@ -144,9 +147,9 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
   constexpr bool EVEN = M % 2 == 0, REAL = S::REAL;
   using Cell = std::conditional_t<REAL, float, float2>;
   __shared__ Cell cells[S::CELLS];
-  // the spectrum row(s) of one view: the row transformed next, and (REAL) two buffers of the row
-  // that it is made from
-  __shared__ __attribute__((aligned(16))) float4 qrow[(REAL ? 3 : 2) * M];
+  // the spectrum row transformed next: REAL the slice's part of rows +-r, kx <= M/2; else row r
+  // (pair 0: rows 0 and M/2)
+  __shared__ __attribute__((aligned(16))) float4 qrow[S::QN];
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int unit = int(blockIdx.x % S::UNITS), block = int(blockIdx.x / S::UNITS);
@@ -246,33 +249,18 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
   // plane K-1-j (the middle pair of an odd K has one plane: the other half goes to the spare row)
   Cell* mine = cells + (j + 2) * P + 2;
   Cell* mine2 = cells + ((K - 1 - j == j ? K + 2 : K - 1 - j) + 2) * P + 2;
-  // rows of the spectrum fetched straight into LDS (lane l's 16 bytes land 16 l bytes after the
-  // wave's base) while earlier views are being worked on
-  auto fetch_row = [&](int v, int r, float4* dst) {
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float4*>(q + size_t(v) * M * M),
-                                                                        short(0), M * M * 16, 0x00020000);
-    if (t < M)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t*)(dst + 64 * w), 16, t * 16, r * M * 16, 0, 0);
+  // rows fetched straight into LDS (lane l's 16 bytes land 16 l bytes after the wave's base) while
+  // the view before is in its second stage
+  constexpr int LEN = REAL ? S::HALF : M, ROWS = REAL ? 2 * S::PAIRS : M / 2 + 1;
+  auto fetch_row = [&](int v, int r, int to) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float4*>(q + size_t(v) * ROWS * LEN), short(0), ROWS * LEN * 16, 0x00020000);
+    if (t < LEN)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t*)(qrow + to + 64 * w), 16, t * 16, r * LEN * 16, 0, 0);
   };
-  float4* raw = qrow + M;
   auto fetch = [&](int v) {
-    if constexpr (REAL) {
-      fetch_row(v, row, raw + (v & 1) * M);
-    } else {
-      fetch_row(v, row, qrow);
-      if (EVEN && row == 0) fetch_row(v, M / 2, raw);
-    }
-  };
-  // REAL: the slice's part of row r, (Q(r, k) + Q(-r, k)) / 2 or (Q(r, k) - Q(-r, k)) / 2i, with
-  // Q1(-r, k) = i conj Q1(r, -k) and Q2(-r, k) = -i conj Q2(r, -k) (F_h G is Hermitian, F_a G
-  // anti-Hermitian)
-  auto combine = [&](int v) {
-    if (t < M) {
-      const float4* src = raw + (v & 1) * M;
-      const float4 a = src[t], b = src[t == 0 ? 0 : M - t];
-      qrow[t] = part2 ? make_float4(0.5f * (a.y - b.x), -0.5f * (a.x - b.y), 0.5f * (a.w + b.z), -0.5f * (a.z + b.w))
-                      : make_float4(0.5f * (a.x + b.y), 0.5f * (a.y + b.x), 0.5f * (a.z - b.w), 0.5f * (a.w - b.z));
-    }
+    fetch_row(v, REAL ? slice : row, 0);
+    if (!REAL && EVEN && row == 0) fetch_row(v, M / 2, M);
   };
   // barriers: one waits for the fetches too, the other leaves them in flight
   auto barrier = [&]() {
@@ -288,14 +276,18 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
     __builtin_amdgcn_s_waitcnt(0xc07f);                   // lgkmcnt(0)
     barrier();
   };
-  if (n0 < n1) {
-    fetch(n0);
-    full_sync();
-    if constexpr (REAL) {
-      combine(n0);
-      if (n0 + 1 < n1) fetch(n0 + 1);
-    }
-  }
+  // (Q1, Q2) at the thread's input kx = s + R2 r.  REAL: those above M/2 from the mirror image; the
+  // side is known at compile time but for the middle r of an odd R1.  (Two addresses with constant
+  // offsets up: kx, and M - kx counted from the last r.)
+  const float4* base = qrow + s;
+  const float4* above = qrow + (M - s - R2 * (R1 - 1));
+  auto input = [&](int r) {
+    if (!REAL || 2 * r + 1 < R1) return base[R2 * r];     // kx < R2 (r + 1) <= M/2
+    if (2 * r + 1 > R1) return q_mirror(above[R2 * (R1 - 1 - r)]);   // kx >= R2 r >= M/2
+    if (2 * (s + R2 * r) <= M) return base[R2 * r];       // uniform
+    return q_mirror(above[R2 * (R1 - 1 - r)]);
+  };
+  if (n0 < n1) fetch(n0);
   full_sync();
 
   for (int v = n0; v < n1; ++v) {
@@ -303,10 +295,9 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
     float2 x[S::XN];
     const ViewGeom& g = geom[v];
     const double u0 = g.u[0], u2 = g.u[2], d0 = g.d[0], d2 = g.d[2];
-    const float4* qr = qrow + s;
 #pragma unroll
     for (int r = 0; r < R1; ++r) {
-      const float4 a = qr[R2 * r];
+      const float4 a = input(r);
       if constexpr (REAL) {
         x[r] = make_float2(ph[r].x * a.x + ph[r].y * a.z, ph[r].x * a.y + ph[r].y * a.w);
         asm volatile("" : "+v"(x[r].x), "+v"(x[r].y));    // formed here: sunk past the barrier, the row values would spill
@@ -314,12 +305,11 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
       else x[r] = make_float2(ph[r].x * a.x - ph[r].y * a.w, ph[r].x * a.y + ph[r].y * a.z);
     }
     if (!REAL && EVEN && row == 0) {                      // uniform: frequency M/2 joins as imaginary part
-      const float4* qh = qr + M;
       float2 st = ph_half;
       asm volatile("" : "+v"(st.x), "+v"(st.y));          // formed here: kept over the views it would spill
 #pragma unroll
       for (int r = 0; r < R1; ++r) {
-        const float4 a = qh[R2 * r];
+        const float4 a = base[M + R2 * r];
         const float cc = ph[r].x * st.x - ph[r].y * st.y;
         const float ss = ph[r].y * st.x + ph[r].x * st.y;
         x[r].x -= cc * a.y + ss * a.z;
@@ -329,13 +319,8 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
     Dft<R1, true>::run(x);
 #pragma unroll
     for (int k = 1; k < R1; ++k) x[k] = cmul(x[k], tw[(s * k) % M]);
-    if constexpr (REAL) full_sync();                  // the next view's rows have landed,
-    else light_sync();                                    // the previous view's taps and this row are read
-    if constexpr (REAL) {
-      if (v + 1 < n1) combine(v + 1);
-    } else {
-      if (v + 1 < n1) fetch(v + 1);
-    }
+    light_sync();                                         // the previous view's taps and this row are read
+    if (v + 1 < n1) fetch(v + 1);
     if (plane) {
 #pragma unroll
       for (int k = 0; k < R1; ++k) {
@@ -376,9 +361,6 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
       }
     }
     full_sync();
-    if constexpr (REAL) {
-      if (v + 2 < n1) fetch(v + 2);
-    }
     // ---- bilinear gather of the slice
     unsigned wr = __builtin_amdgcn_readfirstlane(wraps);
     asm volatile("" : "+s"(wr));                          // tested bit by bit: sixteen kept conditions would spill
@@ -547,6 +529,8 @@ struct AxisLaunch {
 };
 struct AxisSize {
   int M, units, n_slices, lds, waves;
+  hipError_t (*spectra)(const float* images, const float4* filt, float2* z, float4* q, int* status, double inv_iin,
+                        int nb, hipStream_t s);
   hipError_t (*slices)(const AxisLaunch&);
   hipError_t (*columns)(const AxisLaunch&);
 };
@@ -572,7 +556,8 @@ hipError_t axis_columns(const AxisLaunch& a) {
 template <int M>
 __host__ AxisSize axis_size() {
   using S = AxisShape<M>;
-  return AxisSize{M, S::UNITS, 2 * S::PAIRS, S::LDS, S::NW, &axis_slices<M>, &axis_columns<M>};
+  return AxisSize{M, S::UNITS, 2 * S::PAIRS, S::LDS, S::NW, &half_spectra<M, S::REAL ? kSlices : kRows>,
+                  &axis_slices<M>, &axis_columns<M>};
 }
 
 extern const AxisSize kAxisSizesA[], kAxisSizesB[], kAxisSizesC[], kAxisSizesD[], kAxisSizesE[];

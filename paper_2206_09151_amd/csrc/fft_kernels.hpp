@@ -115,7 +115,7 @@ __global__ __launch_bounds__(Shape<M>::T) void k_spectra(const float* __restrict
                                                          const float4* __restrict__ filt,
                                                          const float2* __restrict__ tw_fwd,
                                                          float4* __restrict__ q, int* __restrict__ status,
-                                                         double inv_iin, float* __restrict__ scale, int rows) {
+                                                         double inv_iin, float* __restrict__ scale) {
   using S = Shape<M>;
   __shared__ float2 lds[kSplitSpectra<M> ? (S::LDS_SPLIT_FLOATS + 1) / 2 : S::LDS_ELEMS];
   __shared__ float red[(S::T + 63) / 64];
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(Shape<M>::T) void k_spectra(const float* __restrict
   float l1 = 0.0f;
 #pragma unroll
   for (int e = 0; e < S::E; ++e) {
-    if (!S::has_s(sg * S::E + e) || ky >= rows) continue;
+    if (!S::has_s(sg * S::E + e)) continue;
 #pragma unroll
     for (int k2 = 0; k2 < S::R2; ++k2) {
       const int kx = sg * S::E + e + S::R1 * k2;
@@ -643,7 +643,6 @@ struct SpectraLaunch {
   float* scale;            // FP16 planes: per-view scale out, else null
   float* l1part;           // split sizes with FP16 planes: [nb][P^2] partial bounds
   int nb;
-  int rows;                // row frequencies [0, rows) of q are wanted (direct sizes; split sizes write all M)
   hipStream_t s;
 };
 struct PlanesLaunch {
@@ -661,7 +660,7 @@ struct PlanesLaunch {
 template <int M>
 hipError_t spectra_direct(const SpectraLaunch& a) {
   hipLaunchKernelGGL(k_spectra<M>, dim3(a.nb), dim3(Shape<M>::T), 0, a.s, a.images, a.filt, a.tw, a.q, a.status,
-                     a.inv_iin, a.scale, a.rows);
+                     a.inv_iin, a.scale);
   return hipGetLastError();
 }
 

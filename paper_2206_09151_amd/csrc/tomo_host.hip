@@ -680,15 +680,13 @@ static tomo_status check_range(tomo_plan_t pl, int32_t first, int32_t nb) {
 }
 
 // Spectra of views [first, first+nb) into the plan's per-view slots of d_q.
-// rows > 0: only their row frequencies [0, rows), without the FP16 plane scales.
-static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s,
-                               int rows = 0) {
+static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s) {
   const size_t mm = size_t(pl->M) * pl->M;
-  float* scale = pl->p.plane_dtype == TOMO_F16 && rows == 0 ? pl->d_scale + first : nullptr;
+  float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
   hipError_t e = timed(pl, 0, s, [&] {
     return tomo::launch_spectra(pl->M, d_images, pl->d_filt + size_t(first) * mm, pl->d_tw_fwd,
                                 pl->d_q + size_t(first) * mm, pl->d_status, 1.0 / pl->p.i_in, scale, nb, s,
-                                pl->d_tw2_fwd, pl->d_l1part + size_t(pl->split * pl->split) * first, rows);
+                                pl->d_tw2_fwd, pl->d_l1part + size_t(pl->split * pl->split) * first);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   return TOMO_OK;
@@ -795,13 +793,16 @@ tomo_status tomo_sync(tomo_plan_t pl, void* stream) {
 // Every kernel of one reconstruction, enqueued on s (no synchronisation).
 static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, float* d_volume, hipStream_t s) {
   const size_t mm = size_t(pl->M) * pl->M;
-  // spectra of all views in one launch (one workgroup per view), then per batch the
-  // depth planes and the gridding
-  tomo_status st = run_spectra(pl, d_images, 0, pl->n, s, pl->axis_blocks > 0 ? pl->M / 2 + 1 : 0);
-  if (st != TOMO_OK) return st;
+  // by slices: the half spectra of all views, every slice's row transforms and gridding, and the
+  // transforms along y; otherwise the filtered spectra of all views in one launch, then per batch
+  // the depth planes and the gridding
   if (pl->axis_blocks > 0) {
     float* part = static_cast<float*>(pl->d_stack);
-    hipError_t e = timed(pl, 1, s, [&] {
+    hipError_t e = timed(pl, 0, s, [&] {
+      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_filt, pl->d_q, pl->d_status, 1.0 / pl->p.i_in, pl->n, s);
+    });
+    if (e != hipSuccess) return dev_fail(pl, e, "spectra kernels");
+    e = timed(pl, 1, s, [&] {
       return tomo::launch_axis_slices(pl->M, pl->d_q, pl->d_prop, pl->d_tw_inv, pl->d_geom, part, pl->N, pl->K,
                                       pl->npairs, pl->n, pl->axis_blocks, s);
     });
@@ -812,6 +813,8 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
     if (e != hipSuccess) return dev_fail(pl, e, "column kernel");
     return TOMO_OK;
   }
+  tomo_status st = run_spectra(pl, d_images, 0, pl->n, s);
+  if (st != TOMO_OK) return st;
   for (int first = 0; first < pl->n; first += pl->batch) {
     const int nb = std::min(pl->batch, pl->n - first);
     hipError_t e = timed(pl, 1, s, [&] {

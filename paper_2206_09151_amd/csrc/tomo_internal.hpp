@@ -29,11 +29,10 @@ int fft_split(int M);
 // g = ln(I/I_in) -> 2D DFT -> (G1 G, G2 G) for nb views.  filt, q: [nb][M][M] float4.
 // scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb].
 // Split sizes (P > 1) also need the H-point twiddles, H = M / P (tw_half_fwd), and a
-// [nb][P^2] scratch for the block bounds (l1part, FP16 only).  rows > 0: only row frequencies
-// [0, rows) of q are needed (without scale).
+// [nb][P^2] scratch for the block bounds (l1part, FP16 only).
 hipError_t launch_spectra(int M, const float* images, const float4* filt, const float2* tw_fwd,
                           float4* q, int* status, double inv_iin, float* scale, int nb, hipStream_t s,
-                          const float2* tw_half_fwd, float* l1part, int rows = 0);
+                          const float2* tw_half_fwd, float* l1part);
 // Plane pairs (p, K-1-p), p < npairs, of nb views -> stack [nb][M][K][M] of dtype
 // (0 FP32, 1 BF16, 2 FP16 scaled by scale[view]).
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -53,8 +52,11 @@ bool axis_supported(int M, int N, int K);
 size_t axis_part_bytes(int M, int N);
 // Number of view blocks for n views on a device of `cus` compute units (at least 1).
 int axis_blocks(int M, int n, int cus);
-hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const float2* tw_inv, const ViewGeom* geom,
-                              float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s);
+// Filtered spectra of nb views into work (16 M^2 bytes per view), in the slices' layout.
+hipError_t launch_axis_spectra(int M, const float* images, const float4* filt, float4* work, int* status,
+                               double inv_iin, int nb, hipStream_t s);
+hipError_t launch_axis_slices(int M, const float4* work, const float2* prop, const float2* tw_inv,
+                              const ViewGeom* geom, float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s);
 hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s);
 // Plan-time tables.
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab,

@@ -1449,11 +1449,11 @@ int fft_split(int M) {
 
 hipError_t launch_spectra(int M, const float* images, const float4* filt, const float2* tw_fwd,
                           float4* q, int* status, double inv_iin, float* scale, int nb, hipStream_t s,
-                          const float2* tw_half_fwd, float* l1part, int rows) {
+                          const float2* tw_half_fwd, float* l1part) {
   if (nb <= 0) return hipSuccess;
   const FftSize* f = fft_size(M);
   if (!f) return hipErrorInvalidValue;
-  return f->spectra(SpectraLaunch{images, filt, tw_fwd, tw_half_fwd, q, status, inv_iin, scale, l1part, nb, rows > 0 ? rows : M, s});
+  return f->spectra(SpectraLaunch{images, filt, tw_fwd, tw_half_fwd, q, status, inv_iin, scale, l1part, nb, s});
 }
 
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -1623,11 +1623,22 @@ int axis_blocks(int M, int n, int cus) {
   return best;
 }
 
-hipError_t launch_axis_slices(int M, const float4* q, const float2* prop, const float2* tw_inv, const ViewGeom* geom,
-                              float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s) {
+hipError_t launch_axis_spectra(int M, const float* images, const float4* filt, float4* work, int* status,
+                               double inv_iin, int nb, hipStream_t s) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return hipErrorInvalidValue;
-  return a->slices(AxisLaunch{q, prop, tw_inv, geom, part, nullptr, N, K, npairs, n, blocks, s});
+  // the slices' half rows (at most M + 1 rows of M/2 + 1) at the front of the views' 16 M^2 bytes,
+  // the row pairs' spectra (4 M (M + 1) bytes at most) at their end
+  const size_t mm = size_t(M) * M, pairs = size_t((M + 1) / 2) * M;
+  float2* z = reinterpret_cast<float2*>(work + size_t(nb) * mm) - size_t(nb) * pairs;
+  return a->spectra(images, filt, z, work, status, inv_iin, nb, s);
+}
+
+hipError_t launch_axis_slices(int M, const float4* work, const float2* prop, const float2* tw_inv,
+                              const ViewGeom* geom, float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s) {
+  const AxisSize* a = axis_size_of(M);
+  if (!a) return hipErrorInvalidValue;
+  return a->slices(AxisLaunch{work, prop, tw_inv, geom, part, nullptr, N, K, npairs, n, blocks, s});
 }
 
 hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s) {
