@@ -435,6 +435,7 @@ __global__ __launch_bounds__(AxisShape<M>::T, AxisShape<M>::WAVES) void k_axis_s
 
 template <int M>
 __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* __restrict__ part,
+                                                                   const double2* __restrict__ twiddles,
                                                                    float* __restrict__ vol, int N, int blocks) {
   using S = AxisShape<M>;
   constexpr int R1 = S::R1, R2 = S::R2, E = S::E, CP = S::CP, CL = S::CL;
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(AxisShape<M>::CT) void k_axis_columns(const float* 
   const int col = (blockIdx.x * CL + t % CL) * 2;       // flattened (z, x) column pair col, col + 1
   const bool live = col < nn;
   const unsigned pitch = axis_slice_pitch(N);
-  for (int i = t; i < M; i += S::CT) sincospi(2.0 * i / M, &tw[i].y, &tw[i].x);
+  for (int i = t; i < M; i += S::CT) tw[i] = make_double2(twiddles[i].x, -twiddles[i].y);
   double2* mine = cells + (t % CL) * CP;
   // sum of the blocks' partial slices, and the full spectrum a + i b of the column pair from the
   // half spectra a, b of its columns
@@ -521,6 +522,7 @@ struct AxisLaunch {
   const float4* q;
   const float2* prop;
   const float2* tw;
+  const double2* tw64;     // k_axis_columns: [M] exp(-i 2 pi k / M)
   const ViewGeom* geom;
   float* part;
   float* vol;
@@ -529,8 +531,7 @@ struct AxisLaunch {
 };
 struct AxisSize {
   int M, units, n_slices, lds, waves;
-  hipError_t (*spectra)(const float* images, const float4* filt, float2* z, float4* q, int* status, double inv_iin,
-                        int nb, hipStream_t s);
+  hipError_t (*spectra)(const SpectraLaunch&);
   hipError_t (*slices)(const AxisLaunch&);
   hipError_t (*columns)(const AxisLaunch&);
 };
@@ -549,7 +550,7 @@ template <int M>
 hipError_t axis_columns(const AxisLaunch& a) {
   const unsigned pairs = (unsigned(a.N) * unsigned(a.N) + 1u) / 2u;
   hipLaunchKernelGGL(k_axis_columns<M>, dim3((pairs + AxisShape<M>::CL - 1u) / AxisShape<M>::CL), dim3(AxisShape<M>::CT), 0, a.s, a.part,
-                     a.vol, a.N, a.blocks);
+                     a.tw64, a.vol, a.N, a.blocks);
   return hipGetLastError();
 }
 

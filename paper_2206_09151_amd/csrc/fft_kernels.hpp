@@ -1,20 +1,15 @@
-// Spectra and depth-plane kernels of the reconstruction for every supported detector
-// size M (all 2,3,5-smooth M in [16, 256]), as templates; each size is instantiated in
-// exactly one of the fft_sizes_*.hip translation units, which register a launcher for
-// it in the size table of tomo_kernels.hip.
+// Depth-plane kernels of the reconstruction for every supported detector
+// size M (all 2,3,5-smooth M in [16, 256]), as templates; each size is instantiated, with its
+// spectra kernels (spectra_kernels.hpp), in exactly one of the fft_sizes_*.hip translation units,
+// which register a launcher for it in the size table of tomo_kernels.hip.
 //
-//   k_spectra   per view: g = ln(I/I_in) (eq. 4 left side), 2D DFT (F2 of Section 2,
-//               kernel exp(-i 2 pi r.q)), multiplied by the plan's filter table so
-//               that the Hermitian split needed below is ready:
-//                 Q1 = (1+i) F_h G / M^2,   Q2 = -(1+i) F_a G / M^2,
-//               F = C W H (eq. 11), F_h / F_a its Hermitian / anti-Hermitian parts.
 //   k_planes    per view and plane pair (j, K-1-j): the planes' spectra are
 //               Y_j = Herm[F e^{-i phi_j} G], phi_j = pi lambda z'_j q^2 (eq. 3 on the
 //               paraboloid of eqs. 8/10).  Since z'_{K-1-j} = -z'_j,
 //                 Y_j + i Y_{K-1-j} = cos(phi_j) Q1 + sin(phi_j) Q2,
 //               and one complex inverse 2D FFT yields plane j (real part) and plane
 //               K-1-j (imaginary part).  Writes the stack [view][row][plane][col].
-//   k_spectra_split / k_planes_split: the same as P^2 independent H x H transforms,
+//   k_planes_split: the same as P^2 independent H x H transforms,
 //               M = P H: for M > 200, whose M x M block does not fit in one CU's LDS, and
 //               for 162, 180 and 200, whose direct transforms would need R1 = 27 to 40
 //               values per thread in registers and spill at the 1000-thread workgroup.
@@ -28,6 +23,7 @@
 #include <type_traits>
 
 #include "fft.hpp"
+#include "spectra_kernels.hpp"
 
 namespace tomo {
 
@@ -68,13 +64,10 @@ template <> struct Shape<150> : Fft2Shape<150, 30, 5> {};
 template <> struct Shape<160> : Fft2Shape<160, 40, 4> {};
 template <> struct Shape<192> : Fft2Shape<192, 48, 4> {};
 
-// Exchanges through half-size LDS (real, then imaginary parts): in the plane kernels
-// where the full block would leave room for only one workgroup per CU (two fit then),
-// in the spectra kernel only where the full block would not fit in one CU's LDS.
+// Exchanges through half-size LDS (real, then imaginary parts) where the full block would
+// leave room for only one workgroup per CU (two fit then).
 template <int M>
 constexpr bool kSplit = (Shape<M>::LDS_BYTES > 80 * 1024);
-template <int M>
-constexpr bool kSplitSpectra = (Shape<M>::LDS_BYTES > 160 * 1024);
 
 // ------------------------------------------------------------------ plane storage types
 // FP32, BF16 (round to nearest even), FP16 (per-view power-of-two scale).
@@ -95,77 +88,6 @@ template <>
 __device__ __forceinline__ float from_store<__hip_bfloat16>(__hip_bfloat16 v) { return __bfloat162float(v); }
 template <>
 __device__ __forceinline__ float from_store<__half>(__half v) { return __half2float(v); }
-
-// Filtered spectrum (Q1, Q2) of one coefficient: the filter table entry f times G.
-__device__ __forceinline__ float4 filtered(const float4 f, const float2 gg) {
-  float4 o;
-  o.x = f.x * gg.x - f.y * gg.y;
-  o.y = f.x * gg.y + f.y * gg.x;
-  o.z = f.z * gg.x - f.w * gg.y;
-  o.w = f.z * gg.y + f.w * gg.x;
-  return o;
-}
-
-// FP16 plane scale: the power of two that puts a view's spectral bound at 2^14.
-__device__ __forceinline__ float fp16_scale(float l1) { return l1 > 0.0f ? exp2f(14.0f - ceilf(log2f(l1))) : 1.0f; }
-
-// ------------------------------------------------------------------ K1: spectra
-template <int M>
-__global__ __launch_bounds__(Shape<M>::T) void k_spectra(const float* __restrict__ images,
-                                                         const float4* __restrict__ filt,
-                                                         const float2* __restrict__ tw_fwd,
-                                                         float4* __restrict__ q, int* __restrict__ status,
-                                                         double inv_iin, float* __restrict__ scale) {
-  using S = Shape<M>;
-  __shared__ float2 lds[kSplitSpectra<M> ? (S::LDS_SPLIT_FLOATS + 1) / 2 : S::LDS_ELEMS];
-  __shared__ float red[(S::T + 63) / 64];
-  const int t = threadIdx.x;
-  const int view = blockIdx.x;
-  const int line = t % M, r = t / M;
-  const float* img = images + size_t(view) * M * M;
-  float2 x[S::XN];
-  int bad = 0;
-#pragma unroll
-  for (int m = 0; m < S::R1; ++m) {
-    const float iv = img[(r + S::R2 * m) * M + line];
-    const bool ok = (iv > 0.0f) && (iv < INFINITY);
-    bad |= !ok;
-    // contrast in FP64, rounded once: ln(I/I_in) of an FP32 intensity near I_in
-    const double g = ok ? log(double(iv) * inv_iin) : 0.0;
-    x[m] = make_float2(float(g), 0.0f);
-  }
-  if (bad) atomicOr(status, 1);
-  if constexpr (kSplitSpectra<M>) fft2_block_split<S, false>(x, reinterpret_cast<float*>(lds), tw_fwd);
-  else fft2_block<S, false>(x, lds, tw_fwd);
-  const int sg = t % S::R2, ky = t / S::R2;
-  const size_t row = (size_t(view) * M + ky) * M;
-  float l1 = 0.0f;
-#pragma unroll
-  for (int e = 0; e < S::E; ++e) {
-    if (!S::has_s(sg * S::E + e)) continue;
-#pragma unroll
-    for (int k2 = 0; k2 < S::R2; ++k2) {
-      const int kx = sg * S::E + e + S::R1 * k2;
-      const float4 o = filtered(filt[row + kx], x[e * S::R2 + k2]);
-      q[row + kx] = o;
-      l1 += fabsf(o.x) + fabsf(o.y) + fabsf(o.z) + fabsf(o.w);
-    }
-  }
-  if (scale) {
-    // FP16 plane storage: every plane value of this view is bounded by
-    // sum_k |cos Q1 + sin Q2| <= sum_k (|Q1| + |Q2|) <= l1; scale by the power of two that
-    // puts this bound at 2^14 (exact scaling, values stay below the FP16 maximum).
-    // Fixed-order reduction: wave sums, then the wave partials in order.
-    for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
-    if ((t & 63) == 0) red[t >> 6] = l1;
-    __syncthreads();
-    if (t == 0) {
-      float tot = 0.0f;
-      for (int w = 0; w < (S::T + 63) / 64; ++w) tot += red[w];
-      scale[view] = fp16_scale(tot);
-    }
-  }
-}
 
 // ------------------------------------------------------------------ K3: planes
 // Workgroup -> (view, pair) mapping keeps all pairs of one view on one XCD
@@ -405,90 +327,6 @@ __device__ __forceinline__ float2 split_coef(const float2* __restrict__ tw, int 
   else return tw[H * k];
 }
 
-// g = ln(I/I_in) of an M x M image -> filtered spectra (Q1, Q2) at the block's output
-// positions; l1part[view][block] = partial spectral bound for the FP16 scale.
-template <int H, int P>
-__global__ __launch_bounds__(Shape<H>::T) void k_spectra_split(const float* __restrict__ images,
-                                                              const float4* __restrict__ filt,
-                                                              const float2* __restrict__ tw_m,
-                                                              const float2* __restrict__ tw_h,
-                                                              float4* __restrict__ q, int* __restrict__ status,
-                                                              double inv_iin, float* __restrict__ l1part) {
-  using S = Shape<H>;
-  constexpr int M = P * H;
-  __shared__ float2 lds[(S::LDS_SPLIT_FLOATS + 1) / 2];
-  __shared__ float red[(S::T + 63) / 64];
-  const int t = threadIdx.x;
-  const int view = int(blockIdx.x / (P * P));
-  const unsigned blk = blockIdx.x % (P * P);
-  const int p1 = int(blk / P), p2 = int(blk % P);
-  const int n2 = t % H;
-  int r_;   // uniform across a wave when H is a multiple of the wave size
-  if constexpr (H % 64 == 0) r_ = __builtin_amdgcn_readfirstlane(t / H);
-  else r_ = t / H;
-  const int r = r_;
-  const float* img = images + size_t(view) * M * M;
-  float2 x[S::XN];
-  int bad = 0;
-#pragma unroll
-  for (int m = 0; m < S::R1; ++m) {
-    const int n1 = r + S::R2 * m;
-    float2 acc = make_float2(0.0f, 0.0f);
-#pragma unroll
-    for (int a = 0; a < P; ++a) {
-#pragma unroll
-      for (int b = 0; b < P; ++b) {
-        const float iv = img[(n1 + H * a) * M + n2 + H * b];
-        const bool ok = (iv > 0.0f) && (iv < INFINITY);
-        bad |= !ok;
-        const float g = ok ? float(log(double(iv) * inv_iin)) : 0.0f;
-        const float2 w = split_coef<P>(tw_m, H, (a * p1 + b * p2) % P);
-        acc.x += w.x * g;
-        acc.y += w.y * g;
-      }
-    }
-    const int ti = p1 * n1 + p2 * n2;   // < 2M
-    x[m] = cmul(acc, tw_m[ti >= M ? ti - M : ti]);
-  }
-  if (bad) atomicOr(status, 1);
-  fft2_block_split<S, false>(x, reinterpret_cast<float*>(lds), tw_h);
-  const int sg = t % S::R2, yy = t / S::R2;
-  const int ky = P * yy + p1;
-  const size_t row = (size_t(view) * M + ky) * M;
-  float l1 = 0.0f;
-#pragma unroll
-  for (int e = 0; e < S::E; ++e) {
-    if (!S::has_s(sg * S::E + e)) continue;
-#pragma unroll
-    for (int k2 = 0; k2 < S::R2; ++k2) {
-      const int kx = P * (sg * S::E + e + S::R1 * k2) + p2;
-      const float4 o = filtered(filt[row + kx], x[e * S::R2 + k2]);
-      q[row + kx] = o;
-      l1 += fabsf(o.x) + fabsf(o.y) + fabsf(o.z) + fabsf(o.w);
-    }
-  }
-  if (l1part) {
-    for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
-    if ((t & 63) == 0) red[t >> 6] = l1;
-    __syncthreads();
-    if (t == 0) {
-      float tot = 0.0f;
-      for (int w = 0; w < (S::T + 63) / 64; ++w) tot += red[w];
-      l1part[blockIdx.x] = tot;
-    }
-  }
-}
-
-// FP16 plane scale of each view from its P^2 block bounds (fixed summation order).
-template <int P>
-__global__ void k_scale_split(const float* __restrict__ l1part, float* __restrict__ scale, int nb) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nb) return;
-  float tot = 0.0f;
-  for (int b = 0; b < P * P; ++b) tot += l1part[P * P * v + b];
-  scale[v] = fp16_scale(tot);
-}
-
 // Input of block (P1, P2) of a 2 x 2 split (M = 2H) at the thread's R1 points: per point
 // the four propagated quadrant values (a, b) enter with sign (-1)^(a P1 + b P2).  The block is
 // a template argument, so the signs fold into the FMAs; the quadrants come by buffer loads whose
@@ -631,20 +469,7 @@ __global__ __launch_bounds__(Shape<H>::T, H == 128 ? 8 : 1) void k_planes_split(
 }
 
 // ------------------------------------------------------------------ launchers
-// Arguments of one spectra / planes launch, whatever the size.
-struct SpectraLaunch {
-  const float* images;
-  const float4* filt;
-  const float2* tw;        // M-point forward twiddles
-  const float2* tw_h;      // H-point forward twiddles (split sizes)
-  float4* q;
-  int* status;
-  double inv_iin;
-  float* scale;            // FP16 planes: per-view scale out, else null
-  float* l1part;           // split sizes with FP16 planes: [nb][P^2] partial bounds
-  int nb;
-  hipStream_t s;
-};
+// Arguments of one planes launch, whatever the size.
 struct PlanesLaunch {
   int dtype;               // 0 FP32, 1 BF16, 2 FP16
   const float4* q;
@@ -656,13 +481,6 @@ struct PlanesLaunch {
   const float* scale;
   hipStream_t s;
 };
-
-template <int M>
-hipError_t spectra_direct(const SpectraLaunch& a) {
-  hipLaunchKernelGGL(k_spectra<M>, dim3(a.nb), dim3(Shape<M>::T), 0, a.s, a.images, a.filt, a.tw, a.q, a.status,
-                     a.inv_iin, a.scale);
-  return hipGetLastError();
-}
 
 template <int M, class OutT>
 hipError_t planes_direct_t(const PlanesLaunch& a, const float* scale) {
@@ -709,16 +527,6 @@ hipError_t planes_rows(const PlanesLaunch& a) {
   }
 }
 
-template <int H, int P>
-hipError_t spectra_split(const SpectraLaunch& a) {
-  hipLaunchKernelGGL((k_spectra_split<H, P>), dim3(P * P * a.nb), dim3(Shape<H>::T), 0, a.s, a.images, a.filt, a.tw,
-                     a.tw_h, a.q, a.status, a.inv_iin, a.scale ? a.l1part : nullptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !a.scale) return e;
-  hipLaunchKernelGGL(k_scale_split<P>, dim3((a.nb + 255) / 256), dim3(256), 0, a.s, a.l1part, a.scale, a.nb);
-  return hipGetLastError();
-}
-
 template <int H, int P, class OutT>
 hipError_t planes_split_t(const PlanesLaunch& a, const float* scale) {
   // eight XCD columns; for nb = 1, 2, 4 the kernel deals each view's (pair, block) units over
@@ -741,32 +549,37 @@ hipError_t planes_split(const PlanesLaunch& a) {
   }
 }
 
-// A size's launchers, threads per workgroup and block split (P = 1: direct).  The tables
+// A size's launchers and the block split of its plane transform (P = 1: none).  The tables
 // of these are host data, filled at load time (not constant-initialised, so that the
 // device compilation does not take them, and the host launchers they point to, along).
 struct FftSize {
-  int M, P, threads;
-  hipError_t (*spectra)(const SpectraLaunch&);
+  int M, P;
+  hipError_t (*spectra)(const SpectraLaunch&);           // (Q1, Q2)
+  hipError_t (*spectra_complex)(const SpectraLaunch&);   // times a complex filter
   hipError_t (*planes)(const PlanesLaunch&);
 };
 
 template <int M>
-__host__ FftSize direct_size() {
-  return FftSize{M, 1, Shape<M>::T, &spectra_direct<M>, &planes_direct<M>};
+__host__ FftSize size_of(int P, hipError_t (*planes)(const PlanesLaunch&)) {
+  return FftSize{M, P, &half_spectra<M, kFull>, &half_spectra<M, kComplex>, planes};
 }
-// Direct spectra, row-split planes (the plan's tables are those of a direct size).
+template <int M>
+__host__ FftSize direct_size() {
+  return size_of<M>(1, &planes_direct<M>);
+}
+// Row-split planes (the plan's tables are those of a direct size).
 template <int M>
 __host__ FftSize rows_size() {
-  return FftSize{M, 1, Shape<M>::T, &spectra_direct<M>, &planes_rows<M>};
+  return size_of<M>(1, &planes_rows<M>);
 }
-// P x P block spectra (H = M / P), row-split planes.
+// Row-split planes of a size whose direct shape does not exist (H = M / P).
 template <int H, int P>
 __host__ FftSize split_rows_size() {
-  return FftSize{P * H, P, Shape<H>::T, &spectra_split<H, P>, &planes_rows<P * H>};
+  return size_of<P * H>(P, &planes_rows<P * H>);
 }
 template <int H, int P>
 __host__ FftSize split_size() {
-  return FftSize{P * H, P, Shape<H>::T, &spectra_split<H, P>, &planes_split<H, P>};
+  return size_of<P * H>(P, &planes_split<H, P>);
 }
 
 }  // namespace tomo

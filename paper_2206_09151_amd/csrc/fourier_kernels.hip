@@ -42,7 +42,7 @@
 namespace tomo {
 
 // ------------------------------------------------------------------ filter table
-__global__ void k_ffilter(FilterArgs fa, const ViewGeom* __restrict__ geom, int eq12, float4* __restrict__ filt) {
+__global__ void k_ffilter(FilterArgs fa, const ViewGeom* __restrict__ geom, int eq12, float2* __restrict__ filt) {
   const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const size_t per = size_t(fa.M) * fa.M;
   if (i >= per * fa.n_views) return;
@@ -65,7 +65,7 @@ __global__ void k_ffilter(FilterArgs fa, const ViewGeom* __restrict__ geom, int 
     fr = hr * sc - hi * ss;
     fi = hr * ss + hi * sc;
   }
-  filt[i] = make_float4(float(fr), float(fi), 0.0f, 0.0f);
+  filt[i] = make_float2(float(fr), float(fi));
 }
 
 // ------------------------------------------------------------------ accumulator scale
@@ -89,14 +89,14 @@ __global__ void k_fclear(ulonglong2* __restrict__ acc, size_t count) {
 
 // ------------------------------------------------------------------ splat
 __global__ __launch_bounds__(256) void k_fsplat(FilterArgs fa, const ViewGeom* __restrict__ geom,
-                                                const float4* __restrict__ q, const double* __restrict__ fix,
+                                                const float2* __restrict__ q, const double* __restrict__ fix,
                                                 unsigned long long* __restrict__ acc, int P) {
   const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const size_t per = size_t(fa.M) * fa.M;
   if (i >= per * fa.n_views) return;
   const int n = int(i / per);
   const int ky = int((i % per) / fa.M), kx = int(i % fa.M);
-  const float4 val = q[i];
+  const float2 val = q[i];
   const double unit = fix[0];
   const double vr = double(val.x) * unit, vi = double(val.y) * unit;
   double p[3];
@@ -268,7 +268,7 @@ __device__ __forceinline__ void gather_vertex(size_t cell, const unsigned* __res
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = ent[j + u];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) s[u] = q2[2 * size_t(v[u].x)];
+    for (int u = 0; u < 4; ++u) s[u] = q2[v[u].x];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const double w = double(__int_as_float(v[u].y));
@@ -278,7 +278,7 @@ __device__ __forceinline__ void gather_vertex(size_t cell, const unsigned* __res
   }
   for (; j < e; ++j) {
     const int2 v = ent[j];
-    const float2 s = q2[2 * size_t(v.x)];
+    const float2 s = q2[v.x];
     const double w = double(__int_as_float(v.y));
     re += w * double(s.x);
     im += w * double(s.y);
@@ -290,7 +290,7 @@ __device__ __forceinline__ void gather_strided(unsigned b, unsigned e, int lane,
                                                const float2* __restrict__ q2, double& re, double& im) {
   for (unsigned j = b + lane; j < e; j += 64) {
     const int2 v = ent[j];
-    const float2 s = q2[2 * size_t(v.x)];
+    const float2 s = q2[v.x];
     const double w = double(__int_as_float(v.y));
     re += w * double(s.x);
     im += w * double(s.y);
@@ -308,7 +308,7 @@ constexpr unsigned kHeavy = 48;
 // of the wave (lane-strided partial sums, then a fixed butterfly), one pair after the
 // other; the rest sequentially by their owner.  Both orders are fixed: deterministic.
 __global__ __launch_bounds__(256) void k_fgather(FourierNormArgs a, const unsigned* __restrict__ row_ptr,
-                                                 const int2* __restrict__ ent, const float4* __restrict__ q,
+                                                 const int2* __restrict__ ent, const float2* __restrict__ q2,
                                                  const unsigned long long* __restrict__ smat,
                                                  float2* __restrict__ grid) {
   const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -321,7 +321,6 @@ __global__ __launch_bounds__(256) void k_fgather(FourierNormArgs a, const unsign
   const bool mirror_in = mx < N && my < N && mz < N;
   const size_t mi = (size_t(mz) * N + my) * N + mx;
   const bool owner = i < n3 && !(mirror_in && mi < i);
-  const float2* q2 = reinterpret_cast<const float2*>(q);
   unsigned bk = 0, ek = 0, bm = 0, em = 0;
   if (owner) {
     const size_t ck = (size_t(jz) * P + jy) * P + jx, cm = (size_t(mz) * P + my) * P + mx;
@@ -494,14 +493,14 @@ __global__ __launch_bounds__(Axis<N>::T) void k_fft_axis(float2* __restrict__ da
 // ------------------------------------------------------------------ launchers
 bool fourier_grid_supported(int N) { return launch_fourier_fft3(N, nullptr, nullptr, nullptr, nullptr) != hipErrorInvalidValue; }
 
-hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int eq12, float4* filt,
+hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int eq12, float2* filt,
                                  hipStream_t s) {
   const size_t total = size_t(fa.M) * fa.M * fa.n_views;
   hipLaunchKernelGGL(k_ffilter, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, fa, geom, eq12, filt);
   return hipGetLastError();
 }
 
-hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float4* q, const float* view_scale,
+hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* view_scale,
                                 double* fix, unsigned long long* acc, int P, hipStream_t s) {
   hipLaunchKernelGGL(k_fbound, dim3(1), dim3(64), 0, s, view_scale, fa.n_views, fix);
   hipError_t e = hipGetLastError();
@@ -547,7 +546,7 @@ static hipError_t fft3_impl(float2* grid, float* vol, const float2* tw, hipStrea
 }
 
 hipError_t launch_fourier_gather(const FourierNormArgs& a, const unsigned* row_ptr, const int2* ent,
-                                 const float4* q, const unsigned long long* smat, float2* grid, hipStream_t s) {
+                                 const float2* q, const unsigned long long* smat, float2* grid, hipStream_t s) {
   const size_t n3 = size_t(a.N) * a.N * a.N;
   hipLaunchKernelGGL(k_fgather, dim3(unsigned((n3 + 255) / 256)), dim3(256), 0, s, a, row_ptr, ent, q, smat, grid);
   return hipGetLastError();

@@ -12,11 +12,17 @@
 // two roundings instead of one per butterfly (128^3 from 180 views by slices: relative error 1.5e-7
 // instead of 2.9e-7).
 //
-// Bound at M = 128, 180 views (14 + 14 us): k_rows_fwd by its logarithms and transforms (5.6
-// workgroups of two waves per CU), k_cols_fwd by its 60 MB of traffic.  The whole-image kernel takes 33 us for the same rows, and 71 instead of 25
-// at M = 160 with 60 views, which keep 60 CUs busy.
+// Bound at M = 128, 180 views (16 us, and 11 by slices / 21 for the whole filtered plane): k_rows_fwd
+// by its logarithms and transforms (5.6 workgroups of two waves per CU), k_cols_fwd by its 60 MB (106
+// MB) of traffic, and small launches by the latency of their loads, which every thread of a workgroup
+// shares (transforming threads alone: 10 instead of 6 us for 60 views at M = 48).  The whole-image
+// kernel took 47 us (33 when only half of the rows were wanted), 71 instead of 25 at M = 160 with 60
+// views, 229 instead of 97 at M = 256 with 96, and 12 as now at M = 48 with 60.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "fft.hpp"
 #include "tomo_internal.hpp"
@@ -35,7 +41,7 @@ struct FwdShapeOf {
   static constexpr int HALF = M / 2 + 1;               // columns
   static constexpr int G = (HALF + 15) / 16;           // column groups per view (at most 9)
   static constexpr int C = (HALF + G - 1) / G;         // columns per group
-  static constexpr int CT = C * R2;                    // threads of k_cols_fwd
+  static constexpr int CT = C * R2 <= 256 ? 256 : 512; // threads of k_cols_fwd (C R2 of them transform)
   static constexpr int P = M | 1;                      // LDS pitch of a line (double2)
   static_assert(R1 * R2 == M && R1 >= R2, "shape");
 };
@@ -161,6 +167,7 @@ __device__ __forceinline__ double log_positive(double x) {
 
 template <int M>
 __global__ __launch_bounds__(FwdShape<M>::RT) void k_rows_fwd(const float* __restrict__ images,
+                                                              const double2* __restrict__ twiddles,
                                                               float2* __restrict__ z, int* __restrict__ status,
                                                               double inv_iin, int nb) {
   using S = FwdShape<M>;
@@ -169,11 +176,7 @@ __global__ __launch_bounds__(FwdShape<M>::RT) void k_rows_fwd(const float* __res
   int view, part;
   if (!view_part<S::WPV>(nb, view, part)) return;      // whole workgroup
   const int t = threadIdx.x;
-  for (int i = t; i < M; i += S::RT) {
-    double sn, cs;
-    sincospi(2.0 * i / M, &sn, &cs);
-    tw[i] = make_double2(cs, -sn);
-  }
+  for (int i = t; i < M; i += S::RT) tw[i] = twiddles[i];
   // contrast of the workgroup's rows, by every thread in memory order: row 2 p + 1 is the imaginary
   // part of line p (odd M: the last line has none)
   const int row0 = 2 * S::PB * part, rows = min(2 * S::PB, M - row0);
@@ -222,26 +225,34 @@ __device__ __forceinline__ float4 q_filtered(float4 f, double2 g) {
 
 // What k_cols_fwd writes (q [view] of 16 M^2 bytes and more, see the launchers):
 //   kFull    q[ky][kx]: the filtered spectrum, both halves.
+//   kComplex q[ky][kx] as float2: G times a complex filter (the Fourier-space form's), both halves.
 //   kSlices  q[2 r + c][kx <= M/2], r <= M/2: the even (c = 0) and odd (c = 1) part of the rows +-r,
 //            (Q(r) + Q(-r)) / 2 and (Q(r) - Q(-r)) / 2i; pair r = 0 holds rows 0 and (even M) M/2.
 //   kRows    q[ky][kx], ky <= M/2.
-enum ColsOut { kFull, kSlices, kRows };
+// l1 (kFull, kComplex; or NULL): [view][G] sums of the output's magnitudes (fixed order), from which
+// k_plane_scale forms a view's power-of-two scale.
+enum ColsOut { kFull, kComplex, kSlices, kRows };
+template <ColsOut OUT>
+using QValue = std::conditional_t<OUT == kComplex, float2, float4>;
+__device__ __forceinline__ float2 q_filtered(float2 f, double2 g) {
+  return make_float2(float(f.x * g.x - f.y * g.y), float(f.x * g.y + f.y * g.x));
+}
+__device__ __forceinline__ float q_magnitude(float2 a) { return fabsf(a.x) + fabsf(a.y); }
+__device__ __forceinline__ float q_magnitude(float4 a) { return fabsf(a.x) + fabsf(a.y) + fabsf(a.z) + fabsf(a.w); }
 
 template <int M, ColsOut OUT>
 __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __restrict__ z,
-                                                              const float4* __restrict__ filt,
-                                                              float4* __restrict__ q, int nb) {
+                                                              const double2* __restrict__ twiddles,
+                                                              const QValue<OUT>* __restrict__ filt,
+                                                              QValue<OUT>* __restrict__ q,
+                                                              float* __restrict__ l1, int nb) {
   using S = FwdShape<M>;
   __shared__ double2 cells[S::C * S::P];
   __shared__ double2 tw[M];
   int view, part;
   if (!view_part<S::G>(nb, view, part)) return;        // whole workgroup
   const int t = threadIdx.x;
-  for (int i = t; i < M; i += S::CT) {
-    double sn, cs;
-    sincospi(2.0 * i / M, &sn, &cs);
-    tw[i] = make_double2(cs, -sn);
-  }
+  for (int i = t; i < M; i += S::CT) tw[i] = twiddles[i];
   const float2* zv = z + size_t(view) * S::PAIRS * M;
   const int k0 = part * S::C;
 #pragma unroll 4
@@ -254,33 +265,54 @@ __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __re
   }
   __syncthreads();
   {
+    const bool transforms = t < S::C * S::R2;
     const int cl = t % S::C, r = t / S::C;
     double2* mine = cells + cl * S::P;
     double2 x[S::XN];
+    if (transforms) {
 #pragma unroll
-    for (int m = 0; m < S::R1; ++m) x[m] = mine[r + S::R2 * m];
-    fwd_line<S>(x, mine, r, tw, true);
+      for (int m = 0; m < S::R1; ++m) x[m] = mine[r + S::R2 * m];
+    }
+    fwd_line<S>(x, mine, r, tw, transforms);
     __syncthreads();
-    put_line<S>(x, mine, r);
+    if (transforms) put_line<S>(x, mine, r);
   }
   __syncthreads();
   // filtered outputs, neighbouring columns side by side
-  const float4* fv = filt + size_t(view) * M * M;
+  const QValue<OUT>* fv = filt + size_t(view) * M * M;
   const int cols = min(S::C, S::HALF - k0);
-  if constexpr (OUT == kFull) {
-    float4* qv = q + size_t(view) * M * M;
+  if constexpr (OUT == kFull || OUT == kComplex) {
+    QValue<OUT>* qv = q + size_t(view) * M * M;
+    float sum = 0.0f;
+#pragma unroll 4
     for (int i = t; i < M * S::C; i += S::CT) {
       const int ky = i / S::C, cl = i % S::C, k = k0 + cl;
       if (cl >= cols) continue;
       const double2 g = cells[cl * S::P + ky];
-      qv[ky * M + k] = q_filtered(fv[ky * M + k], g);
+      const QValue<OUT> a = q_filtered(fv[ky * M + k], g);
+      qv[ky * M + k] = a;
+      sum += q_magnitude(a);
       if (k > 0 && 2 * k < M) {
         const int o = (ky == 0 ? 0 : M - ky) * M + M - k;
-        qv[o] = q_filtered(fv[o], make_double2(g.x, -g.y));
+        const QValue<OUT> b = q_filtered(fv[o], make_double2(g.x, -g.y));
+        qv[o] = b;
+        sum += q_magnitude(b);
+      }
+    }
+    if (l1) {
+      __shared__ float red[(S::CT + 63) / 64];
+      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+      if ((t & 63) == 0) red[t >> 6] = sum;
+      __syncthreads();
+      if (t == 0) {
+        float tot = 0.0f;
+        for (int w = 0; w < (S::CT + 63) / 64; ++w) tot += red[w];
+        l1[view * S::G + part] = tot;
       }
     }
   } else {
     float4* qv = q + size_t(view) * (OUT == kRows ? S::HALF * M : 2 * S::PAIRS * S::HALF);
+#pragma unroll 2
     for (int i = t; i < S::PAIRS * S::C; i += S::CT) {
       const int r = i / S::C, cl = i % S::C, k = k0 + cl;
       if (cl >= cols) continue;
@@ -312,14 +344,57 @@ __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __re
   }
 }
 
+// FP16 plane scale: the power of two that puts a view's spectral bound at 2^14.
+__device__ __forceinline__ float fp16_scale(float l1) { return l1 > 0.0f ? exp2f(14.0f - ceilf(log2f(l1))) : 1.0f; }
+
+// Every plane value of a view is bounded by sum_k |cos Q1 + sin Q2| <= sum_k (|Q1| + |Q2|): scale by
+// the power of two that puts this bound at 2^14 (exact scaling, below the FP16 maximum).
+template <int G>
+__global__ void k_plane_scale(const float* __restrict__ l1, float* __restrict__ scale, int nb) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= nb) return;
+  float tot = 0.0f;
+  for (int g = 0; g < G; ++g) tot += l1[G * v + g];
+  scale[v] = fp16_scale(tot);
+}
+
+// Spectra of nb views.  z: the row pairs' spectra, room for `room` views of (M + 1) / 2 M float2 (the
+// views are taken in turns of that many).  scale (kFull, kComplex; or NULL): per-view power-of-two
+// scale out, with l1 [nb][G].
+struct SpectraLaunch {
+  const float* images;
+  const double2* tw;       // [M] exp(-i 2 pi k / M)
+  const void* filt;
+  void* q;
+  float2* z;
+  size_t room;
+  int* status;
+  double inv_iin;
+  float* scale;
+  float* l1;
+  int nb;
+  hipStream_t s;
+};
+
 template <int M, ColsOut OUT>
-hipError_t half_spectra(const float* images, const float4* filt, float2* z, float4* q, int* status, double inv_iin,
-                        int nb, hipStream_t s) {
+hipError_t half_spectra(const SpectraLaunch& a) {
   using S = FwdShape<M>;
-  hipLaunchKernelGGL(k_rows_fwd<M>, view_parts<S::WPV>(nb), dim3(S::RT), 0, s, images, z, status, inv_iin, nb);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_cols_fwd<M, OUT>), view_parts<S::G>(nb), dim3(S::CT), 0, s, z, filt, q, nb);
+  if (a.room < 1) return hipErrorInvalidValue;
+  const size_t per = OUT == kSlices ? size_t(2 * S::PAIRS) * S::HALF : OUT == kRows ? size_t(S::HALF) * M : size_t(M) * M;
+  const int step = int(std::min<size_t>(a.room, size_t(a.nb)));
+  for (int v = 0; v < a.nb; v += step) {
+    const int nb = std::min(step, a.nb - v);
+    hipLaunchKernelGGL(k_rows_fwd<M>, view_parts<S::WPV>(nb), dim3(S::RT), 0, a.s, a.images + size_t(v) * M * M,
+                       a.tw, a.z, a.status, a.inv_iin, nb);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_cols_fwd<M, OUT>), view_parts<S::G>(nb), dim3(S::CT), 0, a.s, a.z, a.tw,
+                       static_cast<const QValue<OUT>*>(a.filt) + size_t(v) * M * M,
+                       static_cast<QValue<OUT>*>(a.q) + size_t(v) * per, a.scale ? a.l1 + size_t(v) * S::G : nullptr, nb);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (!a.scale) return hipSuccess;
+  hipLaunchKernelGGL(k_plane_scale<S::G>, dim3(unsigned(a.nb + 255) / 256), dim3(256), 0, a.s, a.l1, a.scale, a.nb);
   return hipGetLastError();
 }
 

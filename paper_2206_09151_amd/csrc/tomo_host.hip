@@ -28,18 +28,18 @@ struct tomo_plan_s {
   ViewGeom* d_geom = nullptr;   // [n]
   float4* d_filt = nullptr;     // [n][M][M]
   float2* d_prop = nullptr;     // [npairs][M]
-  float2* d_tw_fwd = nullptr;   // [M]
   float2* d_tw_inv = nullptr;   // [M]
-  float2* d_tw2_fwd = nullptr;  // [H] twiddles of the block sub-transforms of split sizes (M = P H)
-  float2* d_tw2_inv = nullptr;  // [H]
-  float* d_l1part = nullptr;    // [n][P^2] block spectral bounds of split sizes (FP16 planes)
+  double2* d_tw64 = nullptr;    // [M] exp(-i 2 pi k / M)
+  float2* d_tw2_inv = nullptr;  // [H] twiddles of the block sub-transforms of split sizes (M = P H)
+  float* d_l1 = nullptr;        // [n][spectra_groups] parts of the views' spectral bounds
   float4* d_q = nullptr;        // [n][M][M]  filtered spectra of every view
-  void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type
+  void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type; before its planes, row spectra
+  size_t stack_bytes = 0;
   float* d_scale = nullptr;     // [n] FP16 plane scale per view (powers of two)
   int* d_status = nullptr;
   // Fourier-space form (params.fourier = 1: gridding operator, 2: atomic splat)
   int P = 0;                            // vertex-grid edge: N + 1 for even N, N for odd N
-  float4* d_ffilt = nullptr;            // [n][M][M] filter of the Fourier-space variant built last
+  float2* d_ffilt = nullptr;            // [n][M][M] filter of the Fourier-space variant built last
   int ffilt_variant = 0;                // 11, 12, or 0 before the first call
   float* d_fview = nullptr;             // [n] per-view spectral bound (power-of-two scale)
   double* d_ffix = nullptr;             // [2] fixed-point unit and its inverse
@@ -278,11 +278,10 @@ void free_plan(tomo_plan_s* pl) {
   (void)hipFree(pl->d_geom);
   (void)hipFree(pl->d_filt);
   (void)hipFree(pl->d_prop);
-  (void)hipFree(pl->d_tw_fwd);
   (void)hipFree(pl->d_tw_inv);
-  (void)hipFree(pl->d_tw2_fwd);
+  (void)hipFree(pl->d_tw64);
   (void)hipFree(pl->d_tw2_inv);
-  (void)hipFree(pl->d_l1part);
+  (void)hipFree(pl->d_l1);
   (void)hipFree(pl->d_q);
   (void)hipFree(pl->d_stack);
   (void)hipFree(pl->d_scale);
@@ -437,7 +436,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   }
 
   // propagator table: (cos, sin)(pi lambda z'_p q^2), z'_p = (p - (K-1)/2) dx; twiddles
-  std::vector<float2> prop(size_t(r.npairs) * r.M), twf(r.M), twi(r.M);
+  std::vector<float2> prop(size_t(r.npairs) * r.M), twi(r.M);
+  std::vector<double2> tw64(r.M);
   for (int pp = 0; pp < r.npairs; ++pp) {
     const double z = (pp - 0.5 * (r.K - 1)) * p->voxel_size;
     for (int k = 0; k < r.M; ++k) {
@@ -449,32 +449,32 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   }
   for (int k = 0; k < r.M; ++k) {
     const double a = 2.0 * kPi * k / r.M;
-    twf[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
     twi[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
+    tw64[k] = make_double2(std::cos(a), -std::sin(a));
   }
   // H-point twiddles of the P^2 block transforms of split sizes (M = P H)
   const int split = tomo::fft_split(r.M);
   const int hpts = split > 1 ? r.M / split : 1;
-  std::vector<float2> tw2f(hpts), tw2i(hpts);
+  std::vector<float2> tw2i(hpts);
   for (int k = 0; k < hpts; ++k) {
     const double a = 2.0 * kPi * k / hpts;
-    tw2f[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
     tw2i[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
   }
 
+  // (one view's row spectra at least: more than the stacks only of a single 16-bit plane)
+  pl->stack_bytes = std::max(size_t(r.batch) * stack_view_bytes(r.M, r.K, p->plane_dtype),
+                             tomo::spectra_scratch_bytes(r.M));
   hipError_t e = hipSuccess;
   const size_t mm = size_t(r.M) * r.M;
   if ((e = dev_alloc(&pl->d_geom, size_t(r.n))) != hipSuccess ||
       (e = dev_alloc(&pl->d_filt, mm * r.n)) != hipSuccess ||
       (e = dev_alloc(&pl->d_prop, prop.size())) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw_fwd, size_t(r.M))) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw_inv, size_t(r.M))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw2_fwd, size_t(hpts))) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw64, size_t(r.M))) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw2_inv, size_t(hpts))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_l1part, size_t(split * split) * r.n)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_l1, size_t(tomo::spectra_groups(r.M)) * r.n)) != hipSuccess ||
       (e = dev_alloc(&pl->d_q, mm * r.n)) != hipSuccess ||
-      (e = dev_alloc(reinterpret_cast<char**>(&pl->d_stack),
-                     size_t(r.batch) * stack_view_bytes(r.M, r.K, p->plane_dtype))) != hipSuccess ||
+      (e = dev_alloc(reinterpret_cast<char**>(&pl->d_stack), pl->stack_bytes)) != hipSuccess ||
       (e = dev_alloc(&pl->d_scale, size_t(r.n))) != hipSuccess ||
       (e = dev_alloc(&pl->d_status, size_t(1))) != hipSuccess) {
     free_plan(pl);
@@ -497,9 +497,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   };
   if ((e = hipMemcpyAsync(pl->d_geom, geo.data(), sizeof(ViewGeom) * r.n, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_prop, prop.data(), sizeof(float2) * prop.size(), hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw_fwd, twf.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
+      (e = hipMemcpyAsync(pl->d_tw64, tw64.data(), sizeof(double2) * r.M, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw_inv, twi.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw2_fwd, tw2f.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw2_inv, tw2i.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)) ||
       (e = hipMemsetAsync(pl->d_status, 0, sizeof(int), s)))
     return cleanup_fail(e, "upload");
@@ -684,9 +683,9 @@ static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t fi
   const size_t mm = size_t(pl->M) * pl->M;
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
   hipError_t e = timed(pl, 0, s, [&] {
-    return tomo::launch_spectra(pl->M, d_images, pl->d_filt + size_t(first) * mm, pl->d_tw_fwd,
-                                pl->d_q + size_t(first) * mm, pl->d_status, 1.0 / pl->p.i_in, scale, nb, s,
-                                pl->d_tw2_fwd, pl->d_l1part + size_t(pl->split * pl->split) * first);
+    return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, pl->d_q + size_t(first) * mm,
+                                pl->d_status, 1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
+                                pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   return TOMO_OK;
@@ -745,9 +744,9 @@ tomo_status tomo_backpropagate_noalloc(tomo_plan_t pl, const float* d_images, in
   const size_t mm = size_t(pl->M) * pl->M;
   float4* q = static_cast<float4*>(pl->scratch);
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
-  hipError_t e = tomo::launch_spectra(pl->M, d_images, pl->d_filt + size_t(first) * mm, pl->d_tw_fwd, q,
-                                      pl->d_status, 1.0 / pl->p.i_in, scale, nb, s, pl->d_tw2_fwd,
-                                      pl->d_l1part + size_t(pl->split * pl->split) * first);
+  hipError_t e = tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, q, pl->d_status,
+                                      1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
+                                      pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
   if (e != hipSuccess) return fail_fixed(pl, TOMO_EDEVICE, "spectra kernel: ", hipGetErrorString(e));
   e = tomo::launch_planes(pl->M, pl->p.plane_dtype, q, pl->d_prop, pl->d_tw_inv, d_planes, pl->K, pl->npairs, nb,
                           pl->d_scale + first, s, pl->d_tw2_inv);
@@ -799,7 +798,7 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
   if (pl->axis_blocks > 0) {
     float* part = static_cast<float*>(pl->d_stack);
     hipError_t e = timed(pl, 0, s, [&] {
-      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_filt, pl->d_q, pl->d_status, 1.0 / pl->p.i_in, pl->n, s);
+      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt, pl->d_q, pl->d_status, 1.0 / pl->p.i_in, pl->n, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "spectra kernels");
     e = timed(pl, 1, s, [&] {
@@ -808,7 +807,7 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
     });
     if (e != hipSuccess) return dev_fail(pl, e, "slice kernel");
     e = timed(pl, 2, s, [&] {
-      return tomo::launch_axis_columns(pl->M, part, d_volume, pl->N, pl->axis_blocks, s);
+      return tomo::launch_axis_columns(pl->M, part, pl->d_tw64, d_volume, pl->N, pl->axis_blocks, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "column kernel");
     return TOMO_OK;
@@ -925,8 +924,10 @@ static tomo_status enqueue_fourier(tomo_plan_t pl, const float* d_images, int32_
     pl->ffilt_variant = variant;
   }
   e = timed(pl, 0, s, [&] {
-    return tomo::launch_spectra(pl->M, d_images, pl->d_ffilt, pl->d_tw_fwd, pl->d_q, pl->d_status,
-                                1.0 / pl->p.i_in, pl->d_fview, pl->n, s, pl->d_tw2_fwd, pl->d_l1part);
+    return tomo::launch_spectra_complex(pl->M, d_images, pl->d_tw64, pl->d_ffilt, reinterpret_cast<float2*>(pl->d_q),
+                                        pl->d_status, 1.0 / pl->p.i_in,
+                                        pl->p.fourier == 2 ? pl->d_fview : nullptr, pl->n, s, pl->d_stack,
+                                        pl->stack_bytes, pl->d_l1);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   tomo::FourierNormArgs na{};
@@ -946,12 +947,14 @@ static tomo_status enqueue_fourier(tomo_plan_t pl, const float* d_images, int32_
   na.R = pl->R0;
   if (pl->p.fourier == 1) {
     e = timed(pl, 3, s, [&] {
-      return tomo::launch_fourier_gather(na, pl->d_oprow, pl->d_opent, pl->d_q, pl->d_fsmat, pl->d_fgrid, s);
+      return tomo::launch_fourier_gather(na, pl->d_oprow, pl->d_opent, reinterpret_cast<const float2*>(pl->d_q),
+                                         pl->d_fsmat, pl->d_fgrid, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "Fourier gridding-operator kernel");
   } else {
     e = timed(pl, 3, s, [&] {
-      return tomo::launch_fourier_splat(fa, pl->d_geom, pl->d_q, pl->d_fview, pl->d_ffix, pl->d_facc, pl->P, s);
+      return tomo::launch_fourier_splat(fa, pl->d_geom, reinterpret_cast<const float2*>(pl->d_q), pl->d_fview,
+                                         pl->d_ffix, pl->d_facc, pl->P, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "Fourier splat kernels");
     e = timed(pl, 4, s, [&] {

@@ -20,19 +20,22 @@ struct FilterArgs {
   int ewald, mode;  // mode: 0 axis ramp, 1 isotropic ramp, 2 sampling matrix
 };
 
-// Supported detector sizes of the LDS-resident 2D FFT (every 2,3,5-smooth M in [16, 256]),
-// threads per workgroup, and the block split P (1: direct; M = P H for M > 200).
+// Supported detector sizes (every 2,3,5-smooth M in [16, 256]) and the block split P of the plane
+// transforms that have one (M = P H; 1: none).
 bool fft_supported(int M);
-int fft_threads(int M);
 int fft_split(int M);
 
-// g = ln(I/I_in) -> 2D DFT -> (G1 G, G2 G) for nb views.  filt, q: [nb][M][M] float4.
-// scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb].
-// Split sizes (P > 1) also need the H-point twiddles, H = M / P (tw_half_fwd), and a
-// [nb][P^2] scratch for the block bounds (l1part, FP16 only).
-hipError_t launch_spectra(int M, const float* images, const float4* filt, const float2* tw_fwd,
-                          float4* q, int* status, double inv_iin, float* scale, int nb, hipStream_t s,
-                          const float2* tw_half_fwd, float* l1part);
+// g = ln(I/I_in) -> 2D DFT G -> (Q1, Q2) = filt G for nb views.  filt, q: [nb][M][M] float4.
+// scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb], with l1
+// [nb][spectra_groups(M)].  scratch: at least spectra_scratch_bytes(M), the more views it holds the
+// fewer launches.  tw: [M] exp(-i 2 pi k / M).  The complex form: filt, q float2.
+int spectra_groups(int M);
+size_t spectra_scratch_bytes(int M);
+hipError_t launch_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* q, int* status, double inv_iin,
+                          float* scale, int nb, hipStream_t s, void* scratch, size_t scratch_bytes, float* l1);
+hipError_t launch_spectra_complex(int M, const float* images, const double2* tw, const float2* filt, float2* q, int* status,
+                                  double inv_iin, float* scale, int nb, hipStream_t s, void* scratch,
+                                  size_t scratch_bytes, float* l1);
 // Plane pairs (p, K-1-p), p < npairs, of nb views -> stack [nb][M][K][M] of dtype
 // (0 FP32, 1 BF16, 2 FP16 scaled by scale[view]).
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -53,11 +56,11 @@ size_t axis_part_bytes(int M, int N);
 // Number of view blocks for n views on a device of `cus` compute units (at least 1).
 int axis_blocks(int M, int n, int cus);
 // Filtered spectra of nb views into work (16 M^2 bytes per view), in the slices' layout.
-hipError_t launch_axis_spectra(int M, const float* images, const float4* filt, float4* work, int* status,
+hipError_t launch_axis_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* work, int* status,
                                double inv_iin, int nb, hipStream_t s);
 hipError_t launch_axis_slices(int M, const float4* work, const float2* prop, const float2* tw_inv,
                               const ViewGeom* geom, float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s);
-hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s);
+hipError_t launch_axis_columns(int M, const float* part, const double2* tw, float* vol, int N, int blocks, hipStream_t s);
 // Plan-time tables.
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab,
                                float4* filt, hipStream_t s);
@@ -77,11 +80,11 @@ struct FourierNormArgs {
   double dx, lambda, sigma, epsilon, R;   // eq. 12 bracket
 };
 bool fourier_grid_supported(int N);
-// filt [n][M][M]: (H_n s, 0) (eq. 11) or (s, 0) (eq. 12), s = centring phase of the DFT.
-hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int eq12, float4* filt,
+// filt [n][M][M]: H_n s (eq. 11) or s (eq. 12), s = centring phase of the DFT.
+hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int eq12, float2* filt,
                                  hipStream_t s);
-// Fixed-point unit from view_scale [n] into fix[2], clear acc [P^3][2], splat q [n][M][M] (.xy).
-hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float4* q, const float* view_scale,
+// Fixed-point unit from view_scale [n] into fix[2], clear acc [P^3][2], splat q [n][M][M].
+hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* view_scale,
                                 double* fix, unsigned long long* acc, int P, hipStream_t s);
 // Hermitian fold + normalisation of the accumulator into grid [N^3] (FFT order).
 hipError_t launch_fourier_norm(const FourierNormArgs& a, const unsigned long long* acc, const unsigned long long* smat,
@@ -96,6 +99,6 @@ hipError_t launch_fourier_op_fill(const FilterArgs& fa, const ViewGeom* geom, in
                                  unsigned* cursor, int2* ent, hipStream_t s);
 // Gather through the operator, Hermitian fold and normalisation into grid [N^3] (FFT order).
 hipError_t launch_fourier_gather(const FourierNormArgs& a, const unsigned* row_ptr, const int2* ent,
-                                 const float4* q, const unsigned long long* smat, float2* grid, hipStream_t s);
+                                 const float2* q, const unsigned long long* smat, float2* grid, hipStream_t s);
 
 }  // namespace tomo

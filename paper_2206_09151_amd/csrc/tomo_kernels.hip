@@ -1,6 +1,7 @@
 // gfx950 kernels of the reconstruction hot path.
 //
-//   k_spectra, k_planes (fft_kernels.hpp, instantiated per size in fft_sizes_*.hip):
+//   k_rows_fwd, k_cols_fwd, k_planes (spectra_kernels.hpp, fft_kernels.hpp, instantiated per size in
+//               fft_sizes_*.hip):
 //               contrast, 2D DFT and the eq. 11 filter; depth propagation (eq. 3) and
 //               the inverse 2D FFTs that write the plane stacks.  This file keeps
 //               the size table that dispatches them.
@@ -1437,23 +1438,33 @@ const FftSize* fft_size(int M) {
 
 bool fft_supported(int M) { return fft_size(M) != nullptr; }
 
-int fft_threads(int M) {
-  const FftSize* f = fft_size(M);
-  return f ? f->threads : 0;
-}
-
 int fft_split(int M) {
   const FftSize* f = fft_size(M);
   return f ? f->P : 0;
 }
 
-hipError_t launch_spectra(int M, const float* images, const float4* filt, const float2* tw_fwd,
-                          float4* q, int* status, double inv_iin, float* scale, int nb, hipStream_t s,
-                          const float2* tw_half_fwd, float* l1part) {
+int spectra_groups(int M) { return (M / 2 + 1 + 15) / 16; }
+
+size_t spectra_scratch_bytes(int M) { return size_t((M + 1) / 2) * M * sizeof(float2); }
+
+hipError_t launch_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* q, int* status, double inv_iin,
+                          float* scale, int nb, hipStream_t s, void* scratch, size_t scratch_bytes, float* l1) {
   if (nb <= 0) return hipSuccess;
   const FftSize* f = fft_size(M);
   if (!f) return hipErrorInvalidValue;
-  return f->spectra(SpectraLaunch{images, filt, tw_fwd, tw_half_fwd, q, status, inv_iin, scale, l1part, nb, s});
+  return f->spectra(SpectraLaunch{images, tw, filt, q, static_cast<float2*>(scratch),
+                                  scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, scale, l1, nb, s});
+}
+
+hipError_t launch_spectra_complex(int M, const float* images, const double2* tw, const float2* filt, float2* q, int* status,
+                                  double inv_iin, float* scale, int nb, hipStream_t s, void* scratch,
+                                  size_t scratch_bytes, float* l1) {
+  if (nb <= 0) return hipSuccess;
+  const FftSize* f = fft_size(M);
+  if (!f) return hipErrorInvalidValue;
+  return f->spectra_complex(SpectraLaunch{images, tw, filt, q, static_cast<float2*>(scratch),
+                                          scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, scale, l1, nb,
+                                          s});
 }
 
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -1623,7 +1634,7 @@ int axis_blocks(int M, int n, int cus) {
   return best;
 }
 
-hipError_t launch_axis_spectra(int M, const float* images, const float4* filt, float4* work, int* status,
+hipError_t launch_axis_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* work, int* status,
                                double inv_iin, int nb, hipStream_t s) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return hipErrorInvalidValue;
@@ -1631,20 +1642,20 @@ hipError_t launch_axis_spectra(int M, const float* images, const float4* filt, f
   // the row pairs' spectra (4 M (M + 1) bytes at most) at their end
   const size_t mm = size_t(M) * M, pairs = size_t((M + 1) / 2) * M;
   float2* z = reinterpret_cast<float2*>(work + size_t(nb) * mm) - size_t(nb) * pairs;
-  return a->spectra(images, filt, z, work, status, inv_iin, nb, s);
+  return a->spectra(SpectraLaunch{images, tw, filt, work, z, size_t(nb), status, inv_iin, nullptr, nullptr, nb, s});
 }
 
 hipError_t launch_axis_slices(int M, const float4* work, const float2* prop, const float2* tw_inv,
                               const ViewGeom* geom, float* part, int N, int K, int npairs, int n, int blocks, hipStream_t s) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return hipErrorInvalidValue;
-  return a->slices(AxisLaunch{work, prop, tw_inv, geom, part, nullptr, N, K, npairs, n, blocks, s});
+  return a->slices(AxisLaunch{work, prop, tw_inv, nullptr, geom, part, nullptr, N, K, npairs, n, blocks, s});
 }
 
-hipError_t launch_axis_columns(int M, const float* part, float* vol, int N, int blocks, hipStream_t s) {
+hipError_t launch_axis_columns(int M, const float* part, const double2* tw, float* vol, int N, int blocks, hipStream_t s) {
   const AxisSize* a = axis_size_of(M);
   if (!a) return hipErrorInvalidValue;
-  return a->columns(AxisLaunch{nullptr, nullptr, nullptr, nullptr, const_cast<float*>(part), vol, N, 0, 0, 0, blocks, s});
+  return a->columns(AxisLaunch{nullptr, nullptr, nullptr, tw, nullptr, const_cast<float*>(part), vol, N, 0, 0, 0, blocks, s});
 }
 
 hipError_t launch_filter_table(const FilterArgs& fa, const ViewGeom* geom, const double* wtab, float4* filt,
