@@ -191,7 +191,8 @@ __global__ __launch_bounds__(FwdShape<M>::RT) void k_rows_fwd(const float* __res
     bad |= !ok;
     flat[((row >> 1) * S::P + col) * 2 + (row & 1)] = row < rows && ok ? log_positive(double(iv) * inv_iin) : 0.0;
   }
-  if (bad) atomicOr(status, 1);
+  // a host word: a store (every writer stores the same) rather than an atomic over the bus
+  if (bad) __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __syncthreads();
   const bool transforms = t < S::PB * S::R2;
   const int line = transforms ? t / S::R2 : 0, r = t % S::R2;

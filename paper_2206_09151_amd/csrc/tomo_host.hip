@@ -36,7 +36,8 @@ struct tomo_plan_s {
   void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type; before its planes, row spectra
   size_t stack_bytes = 0;
   float* d_scale = nullptr;     // [n] FP16 plane scale per view (powers of two)
-  int* d_status = nullptr;
+  int* status = nullptr;                // pinned host word that kernels set on a bad image value: read
+                                        // after a synchronisation without a copy
   // Fourier-space form (params.fourier = 1: gridding operator, 2: atomic splat)
   int P = 0;                            // vertex-grid edge: N + 1 for even N, N for odd N
   float2* d_ffilt = nullptr;            // [n][M][M] filter of the Fourier-space variant built last
@@ -285,7 +286,7 @@ void free_plan(tomo_plan_s* pl) {
   (void)hipFree(pl->d_q);
   (void)hipFree(pl->d_stack);
   (void)hipFree(pl->d_scale);
-  (void)hipFree(pl->d_status);
+  (void)hipHostFree(pl->status);
   (void)hipFree(pl->d_ffilt);
   (void)hipFree(pl->d_fview);
   (void)hipFree(pl->d_ffix);
@@ -476,7 +477,7 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
       (e = dev_alloc(&pl->d_q, mm * r.n)) != hipSuccess ||
       (e = dev_alloc(reinterpret_cast<char**>(&pl->d_stack), pl->stack_bytes)) != hipSuccess ||
       (e = dev_alloc(&pl->d_scale, size_t(r.n))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_status, size_t(1))) != hipSuccess) {
+      (e = hipHostMalloc(reinterpret_cast<void**>(&pl->status), sizeof(int), hipHostMallocDefault)) != hipSuccess) {
     free_plan(pl);
     delete pl;
     (void)hipGetLastError();
@@ -499,9 +500,9 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
       (e = hipMemcpyAsync(pl->d_prop, prop.data(), sizeof(float2) * prop.size(), hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw64, tw64.data(), sizeof(double2) * r.M, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw_inv, twi.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw2_inv, tw2i.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemsetAsync(pl->d_status, 0, sizeof(int), s)))
+      (e = hipMemcpyAsync(pl->d_tw2_inv, tw2i.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)))
     return cleanup_fail(e, "upload");
+  *pl->status = 0;
 
   tomo::FilterArgs fa{};
   fa.n_views = r.n;
@@ -684,7 +685,7 @@ static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t fi
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
   hipError_t e = timed(pl, 0, s, [&] {
     return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, pl->d_q + size_t(first) * mm,
-                                pl->d_status, 1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
+                                pl->status, 1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
                                 pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
@@ -744,7 +745,7 @@ tomo_status tomo_backpropagate_noalloc(tomo_plan_t pl, const float* d_images, in
   const size_t mm = size_t(pl->M) * pl->M;
   float4* q = static_cast<float4*>(pl->scratch);
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
-  hipError_t e = tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, q, pl->d_status,
+  hipError_t e = tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, q, pl->status,
                                       1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
                                       pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
   if (e != hipSuccess) return fail_fixed(pl, TOMO_EDEVICE, "spectra kernel: ", hipGetErrorString(e));
@@ -777,13 +778,9 @@ tomo_status tomo_sync(tomo_plan_t pl, void* stream) {
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = hipStreamSynchronize(s);
   if (e != hipSuccess) return dev_fail(pl, e, "synchronise");
-  int flag = 0;
-  if ((e = hipMemcpy(&flag, pl->d_status, sizeof(int), hipMemcpyDeviceToHost)) != hipSuccess)
-    return dev_fail(pl, e, "status read");
-  if (flag) {
-    const int zero = 0;
-    if ((e = hipMemcpy(pl->d_status, &zero, sizeof(int), hipMemcpyHostToDevice)) != hipSuccess)
-      return dev_fail(pl, e, "status reset");
+  volatile int* flag = pl->status;
+  if (*flag) {
+    *flag = 0;
     return fail(pl, TOMO_EDOMAIN, "an image value was <= 0 or not finite");
   }
   return TOMO_OK;
@@ -798,7 +795,7 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
   if (pl->axis_blocks > 0) {
     float* part = static_cast<float*>(pl->d_stack);
     hipError_t e = timed(pl, 0, s, [&] {
-      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt, pl->d_q, pl->d_status, 1.0 / pl->p.i_in, pl->n, s);
+      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt, pl->d_q, pl->status, 1.0 / pl->p.i_in, pl->n, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "spectra kernels");
     e = timed(pl, 1, s, [&] {
@@ -925,7 +922,7 @@ static tomo_status enqueue_fourier(tomo_plan_t pl, const float* d_images, int32_
   }
   e = timed(pl, 0, s, [&] {
     return tomo::launch_spectra_complex(pl->M, d_images, pl->d_tw64, pl->d_ffilt, reinterpret_cast<float2*>(pl->d_q),
-                                        pl->d_status, 1.0 / pl->p.i_in,
+                                        pl->status, 1.0 / pl->p.i_in,
                                         pl->p.fourier == 2 ? pl->d_fview : nullptr, pl->n, s, pl->d_stack,
                                         pl->stack_bytes, pl->d_l1);
   });
