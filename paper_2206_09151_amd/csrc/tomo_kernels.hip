@@ -951,17 +951,13 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
   }
 }
 
-// General view frames, cubic tiles: 8 x 8 x 8 voxels, two per thread (iz and iz + 4).
+// General view frames, cubic tiles, 16-bit stacks: 8 x 8 x 8 voxels, two per thread (iz and iz + 4).
 // The voxel centres of a cube of edge 8 span at most 7 (|a_x| + |a_y| + |a_z|) <= 7 sqrt(3)
 // < 12.2 along any unit vector a, so with the taps and the floor of the origin a box of
 // 16 rows x 16 planes x CW columns (column start rounded down to a 16-byte boundary) holds
 // the footprint for every view: no fallback path, whatever the orientation.
 template <class InT>
 struct CubeBox;
-template <>
-struct CubeBox<float> {
-  static constexpr int VEC = 4, CW = 20, CP = 20;
-};
 template <>
 struct CubeBox<__hip_bfloat16> {
   static constexpr int VEC = 8, CW = 24, CP = 24;
@@ -1046,8 +1042,7 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
         for (int kk = 0; kk < VEC; ++kk) {
           const int ce = min(max(cc + kk, 0), M - 1);
           const bool ek = unsigned(cc + kk) < unsigned(M);
-          if constexpr (VEC == 4) x.f[kk] = ek ? from_store<InT>(src[ce]) : 0.0f;
-          else x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
+          x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
         }
         v[i] = x.u;
         if (cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K)) valid |= (1u << i);
@@ -1123,56 +1118,74 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
   }
 }
 
-// The cube kernel for FP32 stacks with M a multiple of 4: the same tiles, box origins and
-// interpolation (bit for bit), with each view's footprint fetched straight into LDS by buffer
-// loads (no register staging, no per-chunk clamps: chunks outside the stack get an offset past
-// the buffer's range and read as zeros).  Per view only the footprint's own extent of the
-// 16 x 16 x 20 box is fetched (over random directions about 2.2 times fewer bytes than the
-// whole box), and the box origins and extents of 64 views are computed at once, one view per
-// lane.  Each staged row is followed by CD_XS spare 16-byte slots that are never fetched: at a
-// row pitch of 344 dwords the tap reads of a wave (an 8 x 8 voxel slice, rotated into the box)
-// meet 3.5 bank cycles per pair read in a count over random directions, against 5.3 at 320,
-// where taps in different rows fall on one bank.  One box and two barriers per view: a
-// second box (view n + 1 in flight while view n is interpolated) halves the workgroups per CU
-// and measured slower.
-constexpr int CD_QN = 5;                        // fetched 16-byte chunks per (row, plane)
-constexpr int CD_XS = 6;                        // spare slots per staged row
-constexpr int CD_SR = CB_R * CD_QN + CD_XS;     // slots per staged row
-constexpr int CD_NE = CB_R * CD_SR;             // slots per box
-constexpr int CD_RP = CD_SR * 4, CD_PP = CD_QN * 4;   // row and plane pitch, dwords
+// The cube kernel for FP32 stacks: the same tiles, box origins and interpolation
+// (one view group adds the views in the same order), with each view's footprint fetched straight into LDS by buffer loads
+// (no register staging, no per-chunk clamps: what lies outside the stack gets an offset past
+// the buffer's range and reads as zeros).  Per view only the footprint's own extent of the box
+// is fetched (over random directions about 2.2 times fewer bytes than the whole box), and the
+// box origins and extents of 64 views are computed at once, one view per lane.  One box and two
+// barriers per view: a second box (view n + 1 in flight while view n is interpolated) halves
+// the workgroups per CU and measured slower.
+//
+// CH is the fetch, in bytes per lane.  16: rows of whole 16-byte chunks (M a multiple of 4),
+// a box of 16 x 16 x 20 whose columns start at a chunk; each staged row is followed by XS
+// spare 16-byte slots that are never fetched, as at a row pitch of 344 dwords the tap reads of
+// a wave (an 8 x 8 voxel slice, rotated into the box) meet 3.5 bank cycles per pair read in a
+// count over random directions, against 5.3 at 320, where taps in different rows fall on one
+// bank.  4: rows of any length, a box of 16 x 16 x 16; one load of the view group fetches one
+// box row (lane = plane and column), so that the rows may lie at a pitch of 268 dwords (bank
+// cycles within 1 % of the best pitch, against twice as many at 256): 90^3, 60 views 225 us,
+// against 524 staged through registers value by value.
+//
+// G view groups of 256 threads take every G-th view of one tile, each with its own box, and
+// their sums are added through LDS in the order of the groups.
+template <int CH>
+struct CubeFetch;
+template <>
+struct CubeFetch<16> {
+  static constexpr int QN = 5, XS = 6, SR = CB_R * QN + XS, NE = CB_R * SR;   // chunks per (row, plane), spares, slots
+  static constexpr int CW = 20, PP = 20, RP = SR * 4, BOX = NE * 4;           // columns; pitches and box, dwords
+};
+template <>
+struct CubeFetch<4> {
+  static constexpr int CW = 16, PP = 16, RP = CB_R * PP + 12, BOX = CB_R * RP;
+};
 
-__global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__ stack,
-                                                       const ViewGeom* __restrict__ geom,
-                                                       float* __restrict__ vol, int N, int M, int K, int nb,
-                                                       int accumulate, int flat) {
-  constexpr int PER = (CD_NE + 255) / 256;
-  __shared__ __attribute__((aligned(16))) float box[CD_NE * 4];
+template <int CH, int G>
+__global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restrict__ stack,
+                                                           const ViewGeom* __restrict__ geom,
+                                                           float* __restrict__ vol, int N, int M, int K, int nb,
+                                                           int accumulate, int flat) {
+  using F = CubeFetch<CH>;
+  __shared__ __attribute__((aligned(16))) float boxes[G * F::BOX];
   const int ntc = (N + CB_E - 1) / CB_E;
   const int tiles = ntc * ntc * ntc;
   const int per = (tiles + 7) / 8;
   const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (tile >= tiles) return;                           // uniform
+  const int grp = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 8), tid = threadIdx.x & 255;
+  float* box = boxes + grp * F::BOX;
   const int tx0 = (tile % ntc) * CB_E, ty0 = ((tile / ntc) % ntc) * CB_E, tz0 = (tile / (ntc * ntc)) * CB_E;
-  const int ix = tx0 + (threadIdx.x % CB_E), iy = ty0 + (threadIdx.x / CB_E) % CB_E;
-  const int iz0 = tz0 + int(threadIdx.x) / (CB_E * CB_E);
+  const int ix = tx0 + (tid % CB_E), iy = ty0 + (tid / CB_E) % CB_E;
+  const int iz0 = tz0 + tid / (CB_E * CB_E);
   const bool live0 = ix < N && iy < N && iz0 < N, live1 = ix < N && iy < N && iz0 + 4 < N;
   const double c = 0.5 * (N - 1);
   const double rx = ix - c, ry = iy - c, rz0 = iz0 - c;
   const double hm = 0.5 * (M - 1), hk = 0.5 * (K - 1);
   const size_t view_sz = size_t(K) * M * M;
-  const int wbase = (threadIdx.x & ~63) * 4;           // this wave's first dword in the box, per load
   const int lane = threadIdx.x & 63;
 
-  // Box origin as in k_grid_cube and extent of a view, lane l of every wave for view
-  // obase + l; per view the workgroup-uniform values are read out of one lane into scalar
-  // registers.  Taps lie at most one past the floor of a voxel's coordinates, and one more
+  // Box origin as in k_grid_cube and extent of a view, lane l of every wave for step
+  // obase + l of its group; per view the workgroup-uniform values are read out of one lane into
+  // scalar registers.  Taps lie at most one past the floor of a voxel's coordinates, and one more
   // row, plane and column absorb a last-bit difference between the corner and the voxel
-  // arithmetic (at most 16 rows, 16 planes and 20 columns: a tile's footprint spans < 12.2).
+  // arithmetic (at most 16 rows, planes and columns past the rounding to chunks: a tile's
+  // footprint spans < 12.2).
   int obase = -64, lane_o = 0, lane_e = 0;
-  auto origin = [&](int n, int& r0, int& p0, int& c0, int& rh, int& ph, int& cw) {
-    if (n >= obase + 64) {
-      obase = n;
-      const int v = n + lane;
+  auto origin = [&](int step, int& r0, int& p0, int& c0, int& rh, int& ph, int& cw) {
+    if (step >= obase + 64) {
+      obase = step;
+      const int v = (step + lane) * G + grp;
       int o = 0, ex = 0;
       if (v < nb) {
         const double lo[3] = {opaque(tx0) - c, opaque(ty0) - c, opaque(tz0) - c};
@@ -1194,10 +1207,10 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
         extremes(g.u, hm, cmn, cmx);
         extremes(g.v, hm, rmn, rmx);
         extremes(g.d, hk, pmn, pmx);
-        const int cc = cmn & ~3;
+        const int cc = CH == 16 ? cmn & ~3 : cmn;
         const int rr = rmn;
         const int pp = flat ? 0 : pmn;
-        const int ww = min(4 * CD_QN, (cmx - cc + 3 + 3) & ~3);
+        const int ww = min(F::CW, CH == 16 ? (cmx - cc + 3 + 3) & ~3 : cmx - cc + 3);
         const int hh = min(CB_R, rmx - rr + 3);
         const int dd = flat ? 1 : min(CB_R, pmx - pp + 3);
         // packed in 12-bit fields, offset by 1024 (rows, planes) and 2048 (columns): a tile
@@ -1209,8 +1222,8 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
       lane_o = o;
       lane_e = ex;
     }
-    const int o = __builtin_amdgcn_readlane(lane_o, n - obase);
-    const int ex = __builtin_amdgcn_readlane(lane_e, n - obase);
+    const int o = __builtin_amdgcn_readlane(lane_o, step - obase);
+    const int ex = __builtin_amdgcn_readlane(lane_e, step - obase);
     r0 = (o & 4095) - 1024;
     p0 = ((o >> 12) & 4095) - 1024;
     c0 = (ex & 4095) - 2048;
@@ -1218,41 +1231,74 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
     rh = (ex >> 18) & 63;
     ph = (ex >> 24) & 63;
   };
-  // per slot: row, plane and column in the box (row CB_R, never below a row extent: spare
+  // (views are below 2^31 bytes, as M <= 256 and K <= 2048; CH = 16 is launched only for M a
+  // multiple of 4); what lies outside the view's extent is not fetched (its LDS words are
+  // never read)
+  constexpr int PER = CH == 16 ? (F::BOX / 4 + 255) / 256 : 1;
+  // 16-byte slots: row, plane and column in the box (row CB_R, never below a row extent: spare
   // slot or past the box) and the byte offset from the box origin
-  // (the host launches this kernel only for M a multiple of 4 and views below 2^31 bytes)
   unsigned cfo[PER];
   int crw[PER], cpl[PER], cq[PER];
+  if constexpr (CH == 16) {
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int e = threadIdx.x + 256 * i;
-    const int row = e / CD_SR, rem = e % CD_SR;
-    crw[i] = (e < CD_NE && rem < CB_R * CD_QN) ? row : CB_R;
-    cpl[i] = rem / CD_QN;
-    cq[i] = 4 * (rem % CD_QN);
-    cfo[i] = unsigned((row * K + cpl[i]) * M + cq[i]) * 4u;
+    for (int i = 0; i < PER; ++i) {
+      const int e = tid + 256 * i;
+      const int row = e / F::SR, rem = e % F::SR;
+      crw[i] = (e < F::NE && rem < CB_R * F::QN) ? row : CB_R;
+      cpl[i] = rem / F::QN;
+      cq[i] = 4 * (rem % F::QN);
+      cfo[i] = unsigned((row * K + cpl[i]) * M + cq[i]) * 4u;
+    }
+  } else {
+    crw[0] = 0;
+    cpl[0] = tid / F::PP;
+    cq[0] = tid % F::PP;
+    cfo[0] = unsigned(cpl[0] * M + cq[0]) * 4u;
   }
-  // slots outside the view's extent fetch nothing (their LDS words are never read)
+  float* dst = box + (tid & ~63) * (CH / 4);           // this wave's first dword of a load
   auto load = [&](int n, int r0, int p0, int c0, int rh, int ph, int cw) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<float*>(stack + size_t(n) * view_sz), short(0), int(view_sz * 4), 0x00020000);
-    if (r0 >= 0 && r0 + rh <= M && p0 >= 0 && p0 + ph <= K && c0 >= 0 && c0 + cw <= M) {
-      const int so = ((r0 * K + p0) * M + c0) * 4;
+    const bool inside = r0 >= 0 && r0 + rh <= M && p0 >= 0 && p0 + ph <= K && c0 >= 0 && c0 + cw <= M;
+    if constexpr (CH == 16) {
+      if (inside) {
+        const int so = ((r0 * K + p0) * M + c0) * 4;
 #pragma unroll
-      for (int i = 0; i < PER; ++i)
-        if (crw[i] < rh && cpl[i] < ph && cq[i] < cw)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(box + 1024 * i + wbase), 16, int(cfo[i]), so,
-                                                   0, 0);
+        for (int i = 0; i < PER; ++i)
+          if (crw[i] < rh && cpl[i] < ph && cq[i] < cw)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i), 16, int(cfo[i]), so, 0, 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          if (crw[i] < rh && cpl[i] < ph && cq[i] < cw) {
+            // c0 and M are multiples of 4: a chunk is wholly inside or wholly outside the columns
+            const int row = r0 + crw[i], pp = p0 + cpl[i], cc = c0 + cq[i];
+            const bool ok = unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
+            const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * 4u : kOutOfRange;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i), 16, int(off), 0, 0, 0);
+          }
+        }
+      }
     } else {
+      const int pp = p0 + cpl[0], cc = c0 + cq[0];
+      const bool need = cpl[0] < ph && cq[0] < cw;
+      if (inside) {
+        int so = ((r0 * K + p0) * M + c0) * 4;
+        if (need) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        if (crw[i] < rh && cpl[i] < ph && cq[i] < cw) {
-          // c0 and M are multiples of 4: a chunk is wholly inside or wholly outside the columns
-          const int row = r0 + crw[i], pp = p0 + cpl[i], cc = c0 + cq[i];
-          const bool ok = unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
-          const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * 4u : kOutOfRange;
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(box + 1024 * i + wbase), 16, int(off), 0, 0,
-                                                   0);
+          for (int i = 0; i < CB_R; ++i, so += 4 * K * M)
+            if (i < rh)
+              __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + F::RP * i), 4, int(cfo[0]), so, 0, 0);
+        }
+      } else if (need) {
+        const bool ok = unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
+#pragma unroll
+        for (int i = 0; i < CB_R; ++i) {
+          if (i < rh) {
+            const int row = r0 + i;
+            const unsigned off = ok && unsigned(row) < unsigned(M) ? unsigned((row * K + pp) * M + cc) * 4u : kOutOfRange;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + F::RP * i), 4, int(off), 0, 0, 0);
+          }
         }
       }
     }
@@ -1264,12 +1310,17 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
     asm volatile("" ::: "memory");
   };
   float acc0 = 0.0f, acc1 = 0.0f;
-  for (int n = 0; n < nb; ++n) {
-    int rr0, pp0, cc0, rh, ph, cw;
+  const int steps = (nb + G - 1) / G;
+  for (int step = 0; step < steps; ++step) {
+    const int n = step * G + grp;
+    int rr0 = 0, pp0 = 0, cc0 = 0, rh = 0, ph = 0, cw = 0;
     sync();                                            // every wave is done with the box
-    origin(n, rr0, pp0, cc0, rh, ph, cw);
-    load(n, rr0, pp0, cc0, rh, ph, cw);
+    if (G == 1 || n < nb) {
+      origin(step, rr0, pp0, cc0, rh, ph, cw);
+      load(n, rr0, pp0, cc0, rh, ph, cw);
+    }
     sync();                                            // every wave's share has landed
+    if (G > 1 && n >= nb) break;                       // the last step of this group: no barrier after it
     // interpolation as in k_grid_cube
     const ViewGeom& g = geom[n];
 #pragma unroll
@@ -1282,10 +1333,10 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
       const float tc = fc - fc0, tr = fr - fr0, tp = flat ? 0.0f : fp - fp0;
       const int lc = int(fc0), lr = int(fr0), lp = int(fp0);
       const int lp1 = flat ? lp : lp + 1;
-      const float* a0 = box + lr * CD_RP + lp * CD_PP + lc;
-      const float* a1 = box + lr * CD_RP + lp1 * CD_PP + lc;
-      const float* b0 = a0 + CD_RP;
-      const float* b1 = a1 + CD_RP;
+      const float* a0 = box + lr * F::RP + lp * F::PP + lc;
+      const float* a1 = box + lr * F::RP + lp1 * F::PP + lc;
+      const float* b0 = a0 + F::RP;
+      const float* b1 = a1 + F::RP;
       const float v0 = a0[0] + tc * (a0[1] - a0[0]);
       const float v1 = a1[0] + tc * (a1[1] - a1[0]);
       const float v2 = b0[0] + tc * (b0[1] - b0[0]);
@@ -1295,13 +1346,28 @@ __global__ __launch_bounds__(256) void k_grid_cube_dma(const float* __restrict__
       else acc1 += add;
     }
   }
+  if constexpr (G > 1) {
+    // a group's own box holds its sums: every wave of it has to be done with the taps
+    sync();
+    if (grp > 0) {
+      box[tid] = acc0;
+      box[256 + tid] = acc1;
+    }
+    sync();
+    if (grp > 0) return;
+#pragma unroll
+    for (int k = 1; k < G; ++k) {
+      acc0 += boxes[k * F::BOX + tid];
+      acc1 += boxes[k * F::BOX + 256 + tid];
+    }
+  }
   if (live0) {
-    float* dst = vol + (size_t(iz0) * N + iy) * N + ix;
-    *dst = accumulate ? *dst + acc0 : acc0;
+    float* dst0 = vol + (size_t(iz0) * N + iy) * N + ix;
+    *dst0 = accumulate ? *dst0 + acc0 : acc0;
   }
   if (live1) {
-    float* dst = vol + (size_t(iz0 + 4) * N + iy) * N + ix;
-    *dst = accumulate ? *dst + acc1 : acc1;
+    float* dst1 = vol + (size_t(iz0 + 4) * N + iy) * N + ix;
+    *dst1 = accumulate ? *dst1 + acc1 : acc1;
   }
 }
 
@@ -1523,21 +1589,43 @@ static hipError_t grid_dtype(bool axis_fast, int dtype, const void* stack, const
   }
 }
 
+static hipError_t grid_cube_f32(const float* stack, const ViewGeom* geom, float* vol, int N, int M, int K, int nb,
+                                int accumulate, int flat, hipStream_t s) {
+  const int ntc = (N + CB_E - 1) / CB_E;
+  const int tiles = ntc * ntc * ntc, per = (tiles + 7) / 8;
+  auto go = [&](auto ch, auto groups) {
+    constexpr int CH = decltype(ch)::value, G = decltype(groups)::value;
+    hipLaunchKernelGGL((k_grid_cube_dma<CH, G>), dim3(unsigned(8 * per)), dim3(256 * G), 0, s, stack, geom, vol, N, M,
+                       K, nb, accumulate, flat);
+    return hipGetLastError();
+  };
+  // One tile per workgroup and one view at a time leaves a small volume with one wave per SIMD
+  // and every fetch exposed.  Up to one tile per CU four view groups share a tile (45^3, 60
+  // views: 41 us, two groups 53, one 79), up to two per CU two do (64^3, 100 views: 106 us, one
+  // group 134, four 136; 50^3, 60 views: 74, 97, 82); beyond that the tiles fill the chip by
+  // themselves (72^3, 100 views: one group 164 us, two 184).
+  using std::integral_constant;
+  auto pick = [&](auto ch) {
+    if (tiles <= 256) return go(ch, integral_constant<int, 4>{});
+    if (tiles <= 512) return go(ch, integral_constant<int, 2>{});
+    return go(ch, integral_constant<int, 1>{});
+  };
+  // rows of whole 16-byte chunks take the wide fetch (96^3, 120 views: 383 us, by dwords 432)
+  return M % 4 == 0 ? pick(integral_constant<int, 16>{}) : pick(integral_constant<int, 4>{});
+}
+
 template <class InT>
 static hipError_t grid_cube_impl(const void* stack, const ViewGeom* geom, const float* scale, float* vol, int N,
                                  int M, int K, int nb, int accumulate, int flat, hipStream_t s) {
-  const int ntc = (N + CB_E - 1) / CB_E;
-  const int per = (ntc * ntc * ntc + 7) / 8;
   if constexpr (std::is_same<InT, float>::value) {
-    if (M % 4 == 0 && size_t(K) * M * M * sizeof(float) <= size_t(0x7fffffff)) {
-      hipLaunchKernelGGL(k_grid_cube_dma, dim3(unsigned(8 * per)), dim3(256), 0, s,
-                         static_cast<const float*>(stack), geom, vol, N, M, K, nb, accumulate, flat);
-      return hipGetLastError();
-    }
+    return grid_cube_f32(static_cast<const float*>(stack), geom, vol, N, M, K, nb, accumulate, flat, s);
+  } else {
+    const int ntc = (N + CB_E - 1) / CB_E;
+    const int per = (ntc * ntc * ntc + 7) / 8;
+    hipLaunchKernelGGL(k_grid_cube<InT>, dim3(unsigned(8 * per)), dim3(256), 0, s, static_cast<const InT*>(stack),
+                       geom, scale, vol, N, M, K, nb, accumulate, flat);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_grid_cube<InT>, dim3(unsigned(8 * per)), dim3(256), 0, s, static_cast<const InT*>(stack),
-                     geom, scale, vol, N, M, K, nb, accumulate, flat);
-  return hipGetLastError();
 }
 
 template <int YB, class InT>
