@@ -132,6 +132,54 @@ struct DmaBox<__half> {
 typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr unsigned kOutOfRange = 0x80000000u;      // beyond every buffer range: reads as zero
 
+// Detector coordinates of the general kernels in fixed point: adding kFixBias to an FP64
+// coordinate rounds it to 2^-23 and leaves it in the low word, modulo 512 = 2^32 steps.  Relative to a
+// box origin the word holds the tap index in its upper nine bits and the interpolation fraction in
+// the lower 23, so that the index costs a shift and the weight two operations, and a step to
+// the next voxel is an integer addition.
+constexpr double kFixBias = 805306368.0;           // 1.5 2^29
+__device__ __forceinline__ unsigned fix_of(double biased) { return unsigned(__double_as_longlong(biased)); }
+__device__ __forceinline__ unsigned fix_index(unsigned v) { return v >> 23; }
+// (the mask is kept in a scalar register: as a literal it would cost the and-or a second operation)
+__device__ __forceinline__ unsigned fix_mask() {
+  unsigned m = 0x7fffffu;
+  asm("" : "+s"(m));
+  return m;
+}
+__device__ __forceinline__ float fix_frac(unsigned v, unsigned mask) {
+  return __uint_as_float((v & mask) | 0x3f800000u) - 1.0f;
+}
+// low + t (high - low) of two packed 16-bit values; FP16 operands are widened inside the multiply-adds
+template <class InT>
+__device__ __forceinline__ float lerp_pair(unsigned pr, float t) {
+  if constexpr (std::is_same<InT, __half>::value) {
+    float d;
+    asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(pr));
+    return fmaf(t, d, __half2float(__ushort_as_half((unsigned short)(pr & 0xffffu))));
+  } else {
+    const float a = __uint_as_float(pr << 16);
+    return fmaf(t, __uint_as_float(pr & 0xffff0000u) - a, a);
+  }
+}
+// Slots of a box: row, plane and column offset packed as bytes of seven bits, so that one
+// subtraction compares all three with a view's extent (a byte's guard bit survives where the offset is
+// inside).  A slot that is never fetched has row 127.
+constexpr unsigned kSlotGuard = 0x808080u;
+__device__ __forceinline__ unsigned slot_pack(int row, int plane, int col) {
+  return unsigned(row) | unsigned(plane) << 8 | unsigned(col) << 16;
+}
+__device__ __forceinline__ unsigned slot_extent(int rows, int planes, int cols) {
+  return slot_pack(rows - 1, planes - 1, cols - 1) | kSlotGuard;
+}
+__device__ __forceinline__ bool slot_inside(unsigned extent, unsigned slot) {
+  return ((extent - slot) & kSlotGuard) == kSlotGuard;
+}
+// A box starts this far below the least corner coordinate, so that no rounding puts a voxel below
+// it.  The corners are summed in FP32: coordinates are below 2048 (N <= 1024, M <= 256, K <= 2048), three
+// products and three additions err by less than 2^-11; the extents keep a whole row, plane and
+// column beyond the last tap for the other side.
+constexpr float kBoxMargin = 0x1p-10f;
+
 template <int YB, class InT, int CH>
 __global__ __launch_bounds__(256) void k_grid_axis_dma(const InT* __restrict__ stack,
                                                        const ViewGeom* __restrict__ geom,
@@ -684,13 +732,15 @@ __global__ __launch_bounds__(256) void k_grid_box(const InT* __restrict__ stack,
 // barriers per view).  Per view the box origin, its extent and whether the footprint
 // fits are computed one view per lane (FP64, from the tile corners) and read out with readlane;
 // only the view's own extent is fetched, and a view whose footprint does not fit is gathered
-// for that tile straight from global memory.  The 4-row kernel is held to five waves per SIMD
-// (five workgroups per CU, which its LDS box allows): 360 against 385 us per 8-view launch at
-// 256^3 with FP32 stacks over a tilt-jittered scan (for directions far from the axis, whose
-// footprints often take the global gather, the bound costs time: the autotuner sees both); the
-// 8-row kernel would spill at that bound.
+// for that tile straight from global memory.  Bound by vector issue (79 % of the cycles with
+// FP64-to-FP32 coordinates of three conversions each; fixed point and taps widened inside the
+// multiply-adds take 30 % fewer instructions).  The 4-row kernel is held to six waves per SIMD (80
+// VGPRs): 256^3 with FP16 stacks over a tilt-jittered scan, per 8-view launch 318 us before, 296 with
+// fixed-point coordinates at five waves, 280 at six, 310 at seven (spills).  For directions far
+// from the axis, whose footprints often take the global gather, the bound costs time: the
+// autotuner sees both.  The 8-row kernel would spill at such a bound.
 template <int YB>
-constexpr int tilt_waves_per_eu() { return YB == 4 ? 5 : 1; }
+constexpr int tilt_waves_per_eu() { return YB == 4 ? 6 : 1; }
 template <int YB, class InT, bool ONE_BOX>
 __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(const InT* __restrict__ stack,
                                                        const ViewGeom* __restrict__ geom,
@@ -733,25 +783,32 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
       int cc = 0, rr = 0, pp = 0, ft = 0, ex = 0;
       if (v < nb) {
         const int t0 = opaque(tx0), z0 = opaque(tz0);
-        const double lo[3] = {t0 - c, ry0, z0 - c};
-        const double hi[3] = {t0 + GT - 1 - c, ry0 + (YB - 1), z0 + GT - 1 - c};
+        const float cf = float(c);
+        const float lo[3] = {float(t0) - cf, float(ry0), float(z0) - cf}, ed[3] = {GT - 1, YB - 1, GT - 1};
         const ViewGeom& g = geom[v];
-        double cmin = hm, cmax = hm, rmin = hm, rmax = hm, pmin = hk, pmax = hk;
+        // one detector coordinate at a time (fewer registers live at once)
+        auto extremes = [&](const double* w, double h0, int& fmn, int& fmx) {
+          float mn = float(h0), mx = mn;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          cmin += fmin(g.u[a] * lo[a], g.u[a] * hi[a]);
-          cmax += fmax(g.u[a] * lo[a], g.u[a] * hi[a]);
-          rmin += fmin(g.v[a] * lo[a], g.v[a] * hi[a]);
-          rmax += fmax(g.v[a] * lo[a], g.v[a] * hi[a]);
-          pmin += fmin(g.d[a] * lo[a], g.d[a] * hi[a]);
-          pmax += fmax(g.d[a] * lo[a], g.d[a] * hi[a]);
-        }
-        cc = int(floor(cmin)) & ~(VEC - 1);
-        rr = int(floor(rmin));
-        pp = flat ? 0 : int(floor(pmin));
-        // taps reach floor(max) + 1; one slot of slack for the FP32 rounding of the local coordinates
-        const int cn = int(floor(cmax)) + 3 - cc, rn = int(floor(rmax)) + 3 - rr;
-        const int pn = flat ? 2 : int(floor(pmax)) + 3 - pp;
+          for (int a = 0; a < 3; ++a) {
+            const float wa = float(w[a]), e = wa * lo[a], f = wa * (lo[a] + ed[a]);
+            mn += fminf(e, f);
+            mx += fmaxf(e, f);
+          }
+          fmn = int(floorf(mn - kBoxMargin));
+          fmx = int(floorf(mx));
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        int cmn, cmx, rmn, rmx, pmn, pmx;
+        extremes(g.u, hm, cmn, cmx);
+        extremes(g.v, hm, rmn, rmx);
+        extremes(g.d, hk, pmn, pmx);
+        cc = cmn & ~(VEC - 1);
+        rr = rmn;
+        pp = flat ? 0 : pmn;
+        // taps reach floor(max) + 1; one slot of slack for the rounding of the extremes
+        const int cn = cmx + 3 - cc, rn = rmx + 3 - rr;
+        const int pn = flat ? 2 : pmx + 3 - pp;
         ft = cn <= BOXW && rn <= BR && pn <= BH;
         if (ft) ex = ((cn + VEC - 1) & ~(VEC - 1)) | (rn << 10) | (pn << 20);
       }
@@ -769,40 +826,35 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
   };
   // per chunk slot: byte offset from the box origin, and its (row, plane, column) in the box
   // (the host launches this kernel only for M a multiple of VEC and views below 2^31 bytes)
-  unsigned cfo[PER];
-  int cj[PER], cpl[PER], cq[PER];
+  unsigned cfo[PER], slot[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int e = threadIdx.x + 256 * i;
     const int q = e % QP, pl = (e / QP) % BH, j = e / (QP * BH);
-    cq[i] = VEC * q;
-    cpl[i] = pl;
-    cj[i] = e < NE && q < QN ? j : -1;                  // the spare 16-bit slot is never fetched
+    const bool used = e < NE && q < QN;                 // the spare 16-bit slot is never fetched
+    slot[i] = slot_pack(used ? j : 127, used ? pl : 0, VEC * q);
     cfo[i] = unsigned((j * K + pl) * M + VEC * q) * unsigned(ES);
   }
-  auto has = [&](int i) {
-    return (NE % 256 == 0 || i < PER - 1 || int(threadIdx.x) + 256 * i < NE) && (QP == QN || cq[i] < BOXW);
-  };
   auto load = [&](int n, int c0, int r0, int p0, int ext, unsigned* dst) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<InT*>(stack + size_t(n) * view_sz), short(0), int(view_sz * ES), 0x00020000);
     // slots outside the view's extent fetch nothing (their LDS words are never read)
     const int cw = ext & 1023, rh = (ext >> 10) & 1023, bh = ext >> 20;
-    auto in_ext = [&](int i) { return cq[i] < cw && cj[i] < rh && cpl[i] < bh; };
+    const unsigned se = slot_extent(rh, bh, cw);
     if (r0 >= 0 && r0 + rh <= M && p0 >= 0 && p0 + bh <= K && c0 >= 0 && c0 + cw <= M) {
       const int so = ((r0 * K + p0) * M + c0) * ES;
 #pragma unroll
       for (int i = 0; i < PER; ++i)
-        if (has(i) && in_ext(i))
+        if (slot_inside(se, slot[i]))
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i + wbase), 16, int(cfo[i]), so,
                                                    0, 0);
     } else {
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        if (has(i) && in_ext(i)) {
-          const int row = r0 + cj[i], pp = p0 + cpl[i], cc = c0 + cq[i];
-          const bool ok = cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) &&
-                          unsigned(cc) < unsigned(M);
+        if (slot_inside(se, slot[i])) {
+          const int sl = opaque(int(slot[i]));
+          const int row = r0 + (sl & 255), pp = p0 + (sl >> 8 & 255), cc = c0 + (sl >> 16);
+          const bool ok = unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
           const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * unsigned(ES) : kOutOfRange;
           __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i + wbase), 16, int(off), 0,
                                                    0, 0);
@@ -811,6 +863,7 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
     }
   };
 
+  const unsigned mask = fix_mask();
   float acc[YB];
 #pragma unroll
   for (int j = 0; j < YB; ++j) acc[j] = 0.0f;
@@ -834,44 +887,30 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
     // second plane's (zero-filled) taps at weight 0
     const double d0 = flat ? 0.0 : g.d[0], d1 = flat ? 0.0 : g.d[1], d2 = flat ? 0.0 : g.d[2];
     if (fb) {
-      // box-local coordinates of the first voxel row in FP64, rounded once; the other rows
-      // step by (u_y, v_y, d_y) in FP32 (|local| < 32: error ~1e-6 voxel)
-      const float lc0 = float(g.u[0] * rx + g.u[1] * ry0 + g.u[2] * rz + (hm - cb));
-      const float lr0 = float(g.v[0] * rx + g.v[1] * ry0 + g.v[2] * rz + (hm - rb));
-      const float lp0 = float(d0 * rx + d1 * ry0 + d2 * rz + (hk - pb));
-      const float uy = float(g.u[1]), vy = float(g.v[1]), dy = float(d1);
+      // box-local coordinates of the first voxel row; the other rows step by (u_y, v_y, d_y)
+      unsigned vc = fix_of(g.u[0] * rx + g.u[1] * ry0 + g.u[2] * rz + (hm + kFixBias)) - (unsigned(cb) << 23);
+      unsigned vr = fix_of(g.v[0] * rx + g.v[1] * ry0 + g.v[2] * rz + (hm + kFixBias)) - (unsigned(rb) << 23);
+      unsigned vp = fix_of(d0 * rx + d1 * ry0 + d2 * rz + (hk + kFixBias)) - (unsigned(pb) << 23);
+      const unsigned uy = fix_of(g.u[1] + kFixBias), vy = fix_of(g.v[1] + kFixBias), dy = fix_of(d1 + kFixBias);
 #pragma unroll
-      for (int j = 0; j < YB; ++j) {
-        // fmax guards a rounding-level dip below the box origin; non-negative: truncation floors
-        const float fc = fmaxf(fmaf(float(j), uy, lc0), 0.0f);
-        const float fr = fmaxf(fmaf(float(j), vy, lr0), 0.0f);
-        const float fp = fmaxf(fmaf(float(j), dy, lp0), 0.0f);
-        const int lc = int(fc), lr = int(fr), lp = int(fp);
-        const float tc = fc - float(lc), tr = fr - float(lr), tp = fp - float(lp);
-        const int o = (lr * BH + lp) * PITCH;           // dwords to (row lr, plane lp)
-        float t[8];                                     // (row, plane, col) = (lr + a, lp + b, lc + e) at 4a + 2b + e
+      for (int j = 0; j < YB; ++j, vc += uy, vr += vy, vp += dy) {
+        const unsigned lc = fix_index(vc);
+        const float tc = fix_frac(vc, mask), tr = fix_frac(vr, mask), tp = fix_frac(vp, mask);
+        // dwords to (row, plane)
+        const int o = int(__umul24(fix_index(vr), unsigned(BH * PITCH)) + __umul24(fix_index(vp), unsigned(PITCH)));
+        float v[4];                                     // (row, plane) = (lr + a, lp + b) at 2 a + b, along the columns
 #pragma unroll
         for (int ab = 0; ab < 4; ++ab) {
           const int oo = o + (ab >> 1) * BH * PITCH + (ab & 1) * PITCH;
           if constexpr (ES == 4) {
             const float* r0 = reinterpret_cast<const float*>(bx) + oo + lc;
-            t[2 * ab] = r0[0];
-            t[2 * ab + 1] = r0[1];
+            v[ab] = fmaf(tc, r0[1] - r0[0], r0[0]);
           } else {
             const unsigned* r0 = bx + oo + (lc >> 1);
-            const unsigned pr = __builtin_amdgcn_alignbit(r0[1], r0[0], unsigned(lc & 1) * 16u);
-            if constexpr (std::is_same<InT, __half>::value) {
-              t[2 * ab] = __half2float(__ushort_as_half((unsigned short)(pr & 0xffffu)));
-              t[2 * ab + 1] = __half2float(__ushort_as_half((unsigned short)(pr >> 16)));
-            } else {
-              t[2 * ab] = __uint_as_float(pr << 16);
-              t[2 * ab + 1] = __uint_as_float(pr & 0xffff0000u);
-            }
+            v[ab] = lerp_pair<InT>(__builtin_amdgcn_alignbit(r0[1], r0[0], (lc & 1u) * 16u), tc);
           }
         }
-        const float v00 = fmaf(tc, t[1] - t[0], t[0]), v01 = fmaf(tc, t[3] - t[2], t[2]);
-        const float v10 = fmaf(tc, t[5] - t[4], t[4]), v11 = fmaf(tc, t[7] - t[6], t[6]);
-        const float w0 = fmaf(tp, v01 - v00, v00), w1 = fmaf(tp, v11 - v10, v10);
+        const float w0 = fmaf(tp, v[1] - v[0], v[0]), w1 = fmaf(tp, v[3] - v[2], v[2]);
         acc[j] = fmaf(inv, fmaf(tr, w1 - w0, w0), acc[j]);
       }
     } else {
@@ -951,11 +990,13 @@ __global__ __launch_bounds__(256, tilt_waves_per_eu<YB>()) void k_grid_tilt_dma(
   }
 }
 
-// General view frames, cubic tiles, 16-bit stacks: 8 x 8 x 8 voxels, two per thread (iz and iz + 4).
+// General view frames, cubic tiles: 8 x 8 x 8 voxels, two per thread (iz and iz + 4).
 // The voxel centres of a cube of edge 8 span at most 7 (|a_x| + |a_y| + |a_z|) <= 7 sqrt(3)
 // < 12.2 along any unit vector a, so with the taps and the floor of the origin a box of
 // 16 rows x 16 planes x CW columns (column start rounded down to a 16-byte boundary) holds
 // the footprint for every view: no fallback path, whatever the orientation.
+// k_grid_cube stages 16-bit rows of an odd number of values, which start at any halfword, value
+// by value through registers.
 template <class InT>
 struct CubeBox;
 template <>
@@ -968,6 +1009,28 @@ struct CubeBox<__half> {
 };
 constexpr int CB_E = 8;    // voxel tile edge
 constexpr int CB_R = 16;   // rows and planes staged per view
+
+// Tile t of the n^3 tiles of the cubic-tile kernels, octant by octant: consecutive tiles, and so
+// those of one XCD, lie in a compact block, whose footprint in a view touches fewer cache lines
+// than a slab's.
+__device__ __forceinline__ void cube_tile(int t, int n, int& tx, int& ty, int& tz) {
+  const int h = (n + 1) / 2;
+  int sx = h, sy = h, sz = h, ox = 0, oy = 0, oz = 0;
+#pragma unroll
+  for (int o = 0; o < 8; ++o) {
+    ox = o & 1 ? h : 0;
+    oy = o & 2 ? h : 0;
+    oz = o & 4 ? h : 0;
+    sx = o & 1 ? n - h : h;
+    sy = o & 2 ? n - h : h;
+    sz = o & 4 ? n - h : h;
+    if (o == 7 || t < sx * sy * sz) break;
+    t -= sx * sy * sz;
+  }
+  tx = ox + t % sx;
+  ty = oy + t / sx % sy;
+  tz = oz + t / (sx * sy);
+}
 
 template <class InT>
 __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack,
@@ -995,7 +1058,6 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
   const double rx = ix - c, ry = iy - c, rz0 = iz0 - c;
   const double hm = 0.5 * (M - 1), hk = 0.5 * (K - 1);
   const size_t plane_sz = size_t(K) * M;
-  const bool vec = (M % VEC) == 0;
   const double lo[3] = {tx0 - c, ty0 - c, tz0 - c};
   const double hi[3] = {tx0 + CB_E - 1 - c, ty0 + CB_E - 1 - c, tz0 + CB_E - 1 - c};
 
@@ -1029,24 +1091,17 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int row = r0 + cj[i], pp = p0 + cpl[i], cc = c0 + cq[i];
-      const bool ok = cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && cc >= 0 && cc < M;
-      valid |= ok ? (1u << i) : 0u;
       const int rowc = min(max(row, 0), M - 1), ppc = min(max(pp, 0), K - 1);
-      if (vec) {
-        const unsigned off = unsigned(rowc * K + ppc) * unsigned(M) + unsigned(min(max(cc, 0), M - VEC));
-        v[i] = *reinterpret_cast<const uint4*>(vbase + off);
-      } else {
-        const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
-        Chunk16 x;
+      const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
+      Chunk16 x;
 #pragma unroll
-        for (int kk = 0; kk < VEC; ++kk) {
-          const int ce = min(max(cc + kk, 0), M - 1);
-          const bool ek = unsigned(cc + kk) < unsigned(M);
-          x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
-        }
-        v[i] = x.u;
-        if (cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K)) valid |= (1u << i);
+      for (int kk = 0; kk < VEC; ++kk) {
+        const int ce = min(max(cc + kk, 0), M - 1);
+        const bool ek = unsigned(cc + kk) < unsigned(M);
+        x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
       }
+      v[i] = x.u;
+      valid |= cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) ? (1u << i) : 0u;
     }
   };
   auto stage = [&](const uint4 (&v)[PER], unsigned valid) {
@@ -1118,60 +1173,82 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
   }
 }
 
-// The cube kernel for FP32 stacks: the same tiles, box origins and interpolation
-// (one view group adds the views in the same order), with each view's footprint fetched straight into LDS by buffer loads
-// (no register staging, no per-chunk clamps: what lies outside the stack gets an offset past
-// the buffer's range and reads as zeros).  Per view only the footprint's own extent of the box
+// The cube kernel of every other stack: each view's footprint is fetched straight into LDS by
+// buffer loads (no register staging, no per-chunk clamps: what lies outside the stack gets an offset
+// past the buffer's range and reads as zeros).  Per view only the footprint's own extent of the box
 // is fetched (over random directions about 2.2 times fewer bytes than the whole box), and the
 // box origins and extents of 64 views are computed at once, one view per lane.  One box and two
 // barriers per view: a second box (view n + 1 in flight while view n is interpolated) halves
 // the workgroups per CU and measured slower.
 //
-// CH is the fetch, in bytes per lane.  16: rows of whole 16-byte chunks (M a multiple of 4),
-// a box of 16 x 16 x 20 whose columns start at a chunk; each staged row is followed by XS
-// spare 16-byte slots that are never fetched, as at a row pitch of 344 dwords the tap reads of
-// a wave (an 8 x 8 voxel slice, rotated into the box) meet 3.5 bank cycles per pair read in a
-// count over random directions, against 5.3 at 320, where taps in different rows fall on one
-// bank.  4: rows of any length, a box of 16 x 16 x 16; one load of the view group fetches one
-// box row (lane = plane and column), so that the rows may lie at a pitch of 268 dwords (bank
-// cycles within 1 % of the best pitch, against twice as many at 256): 90^3, 60 views 225 us,
-// against 524 staged through registers value by value.
+// Bound by the fetches' latency and what they miss in L2, and by vector issue (about 120
+// instructions per wave and view): hence FP32 box origins and packed slots (71 VGPRs, so seven
+// workgroups per CU, with 94 five), tiles of an XCD in octants (cube_tile), and fixed-point
+// coordinates.  96^3, 120 views: 310 us; with slabs, five workgroups and FP64 coordinates 384;
+// octants with five workgroups 358; slabs with six 416 (more views in flight than L2 holds).
+//
+// CH is the fetch, in bytes per lane.  16: rows of whole 16-byte chunks, a box of 16 x 16 x 20
+// (16-bit values: 24) whose columns start at a chunk; each staged row is followed by XS spare
+// slots that are never fetched: at a row pitch of 344 dwords the tap reads of a wave (an 8 x 8
+// voxel slice, rotated into the box) meet 3.5 bank cycles per pair read in a count over random
+// directions, against 5.3 at 320, where taps in different rows fall on one bank.  4: rows of
+// whole dwords, a box of 16 columns (16-bit values: 18); one load of the view group fetches one
+// box row (lane = plane and column), so that the rows may lie at a pitch of 268 or 260 dwords
+// (bank cycles within 1 % of the best pitch, against twice as many at 256): 90^3, 60 views
+// 185 us, against 524 staged through registers value by value.
 //
 // G view groups of 256 threads take every G-th view of one tile, each with its own box, and
 // their sums are added through LDS in the order of the groups.
-template <int CH>
-struct CubeFetch;
+template <int ES, int CH>
+struct CubeFetch;                                      // ES: bytes per stored value
 template <>
-struct CubeFetch<16> {
+struct CubeFetch<4, 16> {
   static constexpr int QN = 5, XS = 6, SR = CB_R * QN + XS, NE = CB_R * SR;   // chunks per (row, plane), spares, slots
   static constexpr int CW = 20, PP = 20, RP = SR * 4, BOX = NE * 4;           // columns; pitches and box, dwords
 };
 template <>
-struct CubeFetch<4> {
+struct CubeFetch<2, 16> {
+  static constexpr int QN = 3, XS = 2, SR = CB_R * QN + XS, NE = CB_R * SR;
+  static constexpr int CW = 24, PP = 12, RP = SR * 4, BOX = NE * 4;
+};
+template <>
+struct CubeFetch<4, 4> {
+  static constexpr int QN = 16, SR = 256, NE = 256;    // slots of one load
   static constexpr int CW = 16, PP = 16, RP = CB_R * PP + 12, BOX = CB_R * RP;
 };
+template <>
+struct CubeFetch<2, 4> {
+  static constexpr int QN = 16, SR = 256, NE = 256;
+  static constexpr int CW = 18, PP = 16, RP = CB_R * PP + 4, BOX = CB_R * RP;
+};
 
-template <int CH, int G>
-__global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restrict__ stack,
+template <class InT, int CH, int G>
+__global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const InT* __restrict__ stack,
                                                            const ViewGeom* __restrict__ geom,
+                                                           const float* __restrict__ scale,
                                                            float* __restrict__ vol, int N, int M, int K, int nb,
                                                            int accumulate, int flat) {
-  using F = CubeFetch<CH>;
-  __shared__ __attribute__((aligned(16))) float boxes[G * F::BOX];
+  constexpr int ES = int(sizeof(InT)), V = CH / ES;    // bytes per stored value, values per slot
+  using F = CubeFetch<ES, CH>;
+  __shared__ __attribute__((aligned(16))) unsigned boxes[G * F::BOX];
   const int ntc = (N + CB_E - 1) / CB_E;
   const int tiles = ntc * ntc * ntc;
   const int per = (tiles + 7) / 8;
   const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (tile >= tiles) return;                           // uniform
   const int grp = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 8), tid = threadIdx.x & 255;
-  float* box = boxes + grp * F::BOX;
-  const int tx0 = (tile % ntc) * CB_E, ty0 = ((tile / ntc) % ntc) * CB_E, tz0 = (tile / (ntc * ntc)) * CB_E;
+  unsigned* box = boxes + grp * F::BOX;
+  int tx0, ty0, tz0;
+  cube_tile(tile, ntc, tx0, ty0, tz0);
+  tx0 *= CB_E;
+  ty0 *= CB_E;
+  tz0 *= CB_E;
   const int ix = tx0 + (tid % CB_E), iy = ty0 + (tid / CB_E) % CB_E;
   const int iz0 = tz0 + tid / (CB_E * CB_E);
   const bool live0 = ix < N && iy < N && iz0 < N, live1 = ix < N && iy < N && iz0 + 4 < N;
   const double c = 0.5 * (N - 1);
   const double rx = ix - c, ry = iy - c, rz0 = iz0 - c;
-  const double hm = 0.5 * (M - 1), hk = 0.5 * (K - 1);
+  const double hm = 0.5 * (M - 1), hk = flat ? 0.0 : 0.5 * (K - 1);
   const size_t view_sz = size_t(K) * M * M;
   const int lane = threadIdx.x & 63;
 
@@ -1188,31 +1265,32 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restri
       const int v = (step + lane) * G + grp;
       int o = 0, ex = 0;
       if (v < nb) {
-        const double lo[3] = {opaque(tx0) - c, opaque(ty0) - c, opaque(tz0) - c};
-        const double hi[3] = {lo[0] + (CB_E - 1), lo[1] + (CB_E - 1), lo[2] + (CB_E - 1)};
+        const float cf = float(c);
+        const float lo[3] = {float(opaque(tx0)) - cf, float(opaque(ty0)) - cf, float(opaque(tz0)) - cf};
         const ViewGeom& g = geom[v];
         // one detector coordinate at a time (fewer registers live at once)
         auto extremes = [&](const double* w, double h0, int& fmn, int& fmx) {
-          double mn = h0, mx = h0;
+          float mn = float(h0), mx = mn;
 #pragma unroll
           for (int a = 0; a < 3; ++a) {
-            mn += fmin(w[a] * lo[a], w[a] * hi[a]);
-            mx += fmax(w[a] * lo[a], w[a] * hi[a]);
+            const float wa = float(w[a]), e = wa * lo[a], f = wa * (lo[a] + float(CB_E - 1));
+            mn += fminf(e, f);
+            mx += fmaxf(e, f);
           }
-          fmn = int(floor(mn));
-          fmx = int(floor(mx));
+          fmn = int(floorf(mn - kBoxMargin));
+          fmx = int(floorf(mx));
           __builtin_amdgcn_sched_barrier(0);
         };
         int cmn, cmx, rmn, rmx, pmn, pmx;
         extremes(g.u, hm, cmn, cmx);
         extremes(g.v, hm, rmn, rmx);
         extremes(g.d, hk, pmn, pmx);
-        const int cc = CH == 16 ? cmn & ~3 : cmn;
+        const int cc = cmn & ~(V - 1);
         const int rr = rmn;
         const int pp = flat ? 0 : pmn;
-        const int ww = min(F::CW, CH == 16 ? (cmx - cc + 3 + 3) & ~3 : cmx - cc + 3);
+        const int ww = min(F::CW, (cmx - cc + 3 + V - 1) & ~(V - 1));
         const int hh = min(CB_R, rmx - rr + 3);
-        const int dd = flat ? 1 : min(CB_R, pmx - pp + 3);
+        const int dd = flat ? 2 : min(CB_R, pmx - pp + 3);
         // packed in 12-bit fields, offset by 1024 (rows, planes) and 2048 (columns): a tile
         // corner is at most sqrt(3) (N - 1) / 2 < 887 from the volume centre (N <= 1024), so
         // every origin lies in [-890, 1024 + 887) (M <= 256, K <= 2048)
@@ -1231,72 +1309,63 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restri
     rh = (ex >> 18) & 63;
     ph = (ex >> 24) & 63;
   };
-  // (views are below 2^31 bytes, as M <= 256 and K <= 2048; CH = 16 is launched only for M a
-  // multiple of 4); what lies outside the view's extent is not fetched (its LDS words are
+  // (views are below 2^31 bytes, as M <= 256 and K <= 2048; M is a multiple of V); what lies outside the view's extent is not fetched (its LDS words are
   // never read)
   constexpr int PER = CH == 16 ? (F::BOX / 4 + 255) / 256 : 1;
-  // 16-byte slots: row, plane and column in the box (row CB_R, never below a row extent: spare
-  // slot or past the box) and the byte offset from the box origin
-  unsigned cfo[PER];
-  int crw[PER], cpl[PER], cq[PER];
-  if constexpr (CH == 16) {
+  // 16-byte slots: offsets in the box (spare slots and slots past the box are never fetched)
+  // and bytes from the box origin; dword loads: lane = plane and column, one load per row
+  unsigned cfo[PER], slot[PER];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int e = tid + 256 * i;
-      const int row = e / F::SR, rem = e % F::SR;
-      crw[i] = (e < F::NE && rem < CB_R * F::QN) ? row : CB_R;
-      cpl[i] = rem / F::QN;
-      cq[i] = 4 * (rem % F::QN);
-      cfo[i] = unsigned((row * K + cpl[i]) * M + cq[i]) * 4u;
-    }
-  } else {
-    crw[0] = 0;
-    cpl[0] = tid / F::PP;
-    cq[0] = tid % F::PP;
-    cfo[0] = unsigned(cpl[0] * M + cq[0]) * 4u;
+  for (int i = 0; i < PER; ++i) {
+    const int e = CH == 16 ? tid + 256 * i : tid;
+    const int row = CH == 16 ? e / F::SR : 0, rem = CH == 16 ? e % F::SR : e;
+    const int pl = rem / F::QN, q = rem % F::QN * V;
+    const bool used = CH == 4 || (e < F::NE && rem < CB_R * F::QN);
+    slot[i] = slot_pack(used ? row : 127, used ? pl : 0, q);
+    cfo[i] = unsigned((row * K + pl) * M + q) * unsigned(ES);
   }
-  float* dst = box + (tid & ~63) * (CH / 4);           // this wave's first dword of a load
+  unsigned* dst = box + (tid & ~63) * (CH / 4);           // this wave's first dword of a load
   auto load = [&](int n, int r0, int p0, int c0, int rh, int ph, int cw) {
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<float*>(stack + size_t(n) * view_sz), short(0), int(view_sz * 4), 0x00020000);
+        const_cast<InT*>(stack + size_t(n) * view_sz), short(0), int(view_sz * ES), 0x00020000);
     const bool inside = r0 >= 0 && r0 + rh <= M && p0 >= 0 && p0 + ph <= K && c0 >= 0 && c0 + cw <= M;
+    const unsigned ext = slot_extent(CH == 16 ? rh : 1, ph, cw);
     if constexpr (CH == 16) {
       if (inside) {
-        const int so = ((r0 * K + p0) * M + c0) * 4;
+        const int so = ((r0 * K + p0) * M + c0) * ES;
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-          if (crw[i] < rh && cpl[i] < ph && cq[i] < cw)
+          if (slot_inside(ext, slot[i]))
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i), 16, int(cfo[i]), so, 0, 0);
       } else {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-          if (crw[i] < rh && cpl[i] < ph && cq[i] < cw) {
-            // c0 and M are multiples of 4: a chunk is wholly inside or wholly outside the columns
-            const int row = r0 + crw[i], pp = p0 + cpl[i], cc = c0 + cq[i];
+          if (slot_inside(ext, slot[i])) {
+            // c0 and M are multiples of V: a slot is wholly inside or wholly outside the columns
+            const int sl = opaque(int(slot[i]));
+          const int row = r0 + (sl & 255), pp = p0 + (sl >> 8 & 255), cc = c0 + (sl >> 16);
             const bool ok = unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
-            const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * 4u : kOutOfRange;
+            const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * unsigned(ES) : kOutOfRange;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i), 16, int(off), 0, 0, 0);
           }
         }
       }
-    } else {
-      const int pp = p0 + cpl[0], cc = c0 + cq[0];
-      const bool need = cpl[0] < ph && cq[0] < cw;
+    } else if (slot_inside(ext, slot[0])) {
       if (inside) {
-        int so = ((r0 * K + p0) * M + c0) * 4;
-        if (need) {
+        int so = ((r0 * K + p0) * M + c0) * ES;
 #pragma unroll
-          for (int i = 0; i < CB_R; ++i, so += 4 * K * M)
-            if (i < rh)
-              __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + F::RP * i), 4, int(cfo[0]), so, 0, 0);
-        }
-      } else if (need) {
+        for (int i = 0; i < CB_R; ++i, so += ES * K * M)
+          if (i < rh)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + F::RP * i), 4, int(cfo[0]), so, 0, 0);
+      } else {
+        const int sl = opaque(int(slot[0]));
+        const int pp = p0 + (sl >> 8 & 255), cc = c0 + (sl >> 16);
         const bool ok = unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
 #pragma unroll
         for (int i = 0; i < CB_R; ++i) {
           if (i < rh) {
             const int row = r0 + i;
-            const unsigned off = ok && unsigned(row) < unsigned(M) ? unsigned((row * K + pp) * M + cc) * 4u : kOutOfRange;
+            const unsigned off = ok && unsigned(row) < unsigned(M) ? unsigned((row * K + pp) * M + cc) * unsigned(ES) : kOutOfRange;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + F::RP * i), 4, int(off), 0, 0, 0);
           }
         }
@@ -1309,6 +1378,7 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restri
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
+  const unsigned mask = fix_mask();
   float acc0 = 0.0f, acc1 = 0.0f;
   const int steps = (nb + G - 1) / G;
   for (int step = 0; step < steps; ++step) {
@@ -1321,44 +1391,56 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const float* __restri
     }
     sync();                                            // every wave's share has landed
     if (G > 1 && n >= nb) break;                       // the last step of this group: no barrier after it
-    // interpolation as in k_grid_cube
     const ViewGeom& g = geom[n];
+    float inv = 1.0f;
+    if constexpr (std::is_same<InT, __half>::value) inv = 1.0f / scale[n];   // exact: a power of two
+    // flat (one plane): a zero depth coordinate puts every tap on plane 0, with the second
+    // plane's (zero-filled) taps at weight 0
+    const double d0 = flat ? 0.0 : g.d[0], d1 = flat ? 0.0 : g.d[1], d2 = flat ? 0.0 : g.d[2];
+    unsigned vc = fix_of(g.u[0] * rx + g.u[1] * ry + g.u[2] * rz0 + (hm + kFixBias)) - (unsigned(cc0) << 23);
+    unsigned vr = fix_of(g.v[0] * rx + g.v[1] * ry + g.v[2] * rz0 + (hm + kFixBias)) - (unsigned(rr0) << 23);
+    unsigned vp = fix_of(d0 * rx + d1 * ry + d2 * rz0 + (hk + kFixBias)) - (unsigned(pp0) << 23);
+    const unsigned sc = fix_of(4.0 * g.u[2] + kFixBias), sr = fix_of(4.0 * g.v[2] + kFixBias);
+    const unsigned sp = fix_of(4.0 * d2 + kFixBias);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const double rz = rz0 + 4 * h;
-      const float fc = float(fmax(g.u[0] * rx + g.u[1] * ry + g.u[2] * rz + hm - cc0, 0.0));
-      const float fr = float(fmax(g.v[0] * rx + g.v[1] * ry + g.v[2] * rz + hm - rr0, 0.0));
-      const float fp = flat ? 0.0f : float(fmax(g.d[0] * rx + g.d[1] * ry + g.d[2] * rz + hk - pp0, 0.0));
-      const float fc0 = floorf(fc), fr0 = floorf(fr), fp0 = floorf(fp);
-      const float tc = fc - fc0, tr = fr - fr0, tp = flat ? 0.0f : fp - fp0;
-      const int lc = int(fc0), lr = int(fr0), lp = int(fp0);
-      const int lp1 = flat ? lp : lp + 1;
-      const float* a0 = box + lr * F::RP + lp * F::PP + lc;
-      const float* a1 = box + lr * F::RP + lp1 * F::PP + lc;
-      const float* b0 = a0 + F::RP;
-      const float* b1 = a1 + F::RP;
-      const float v0 = a0[0] + tc * (a0[1] - a0[0]);
-      const float v1 = a1[0] + tc * (a1[1] - a1[0]);
-      const float v2 = b0[0] + tc * (b0[1] - b0[0]);
-      const float v3 = b1[0] + tc * (b1[1] - b1[0]);
-      const float add = (1.0f - tr) * ((1.0f - tp) * v0 + tp * v1) + tr * ((1.0f - tp) * v2 + tp * v3);
-      if (h == 0) acc0 += add;
-      else acc1 += add;
+      const float tc = fix_frac(vc, mask), tr = fix_frac(vr, mask), tp = fix_frac(vp, mask);
+      const unsigned lc = fix_index(vc);
+      const unsigned* o = box + __umul24(fix_index(vr), F::RP) + __umul24(fix_index(vp), F::PP);
+      float v[4];                                      // (row, plane) = (lr + a, lp + b) at 2 a + b, along the columns
+#pragma unroll
+      for (int ab = 0; ab < 4; ++ab) {
+        const unsigned* oo = o + (ab >> 1) * F::RP + (ab & 1) * F::PP;
+        if constexpr (ES == 4) {
+          const float* r0 = reinterpret_cast<const float*>(oo) + lc;
+          v[ab] = fmaf(tc, r0[1] - r0[0], r0[0]);
+        } else {
+          const unsigned* r0 = oo + (lc >> 1);
+          v[ab] = lerp_pair<InT>(__builtin_amdgcn_alignbit(r0[1], r0[0], (lc & 1u) * 16u), tc);
+        }
+      }
+      const float w0 = fmaf(tp, v[1] - v[0], v[0]), w1 = fmaf(tp, v[3] - v[2], v[2]);
+      const float add = fmaf(tr, w1 - w0, w0);
+      if (h == 0) acc0 = fmaf(inv, add, acc0);
+      else acc1 = fmaf(inv, add, acc1);
+      vc += sc;
+      vr += sr;
+      vp += sp;
     }
   }
   if constexpr (G > 1) {
     // a group's own box holds its sums: every wave of it has to be done with the taps
     sync();
     if (grp > 0) {
-      box[tid] = acc0;
-      box[256 + tid] = acc1;
+      box[tid] = __float_as_uint(acc0);
+      box[256 + tid] = __float_as_uint(acc1);
     }
     sync();
     if (grp > 0) return;
 #pragma unroll
     for (int k = 1; k < G; ++k) {
-      acc0 += boxes[k * F::BOX + tid];
-      acc1 += boxes[k * F::BOX + 256 + tid];
+      acc0 += __uint_as_float(boxes[k * F::BOX + tid]);
+      acc1 += __uint_as_float(boxes[k * F::BOX + 256 + tid]);
     }
   }
   if (live0) {
@@ -1589,17 +1671,19 @@ static hipError_t grid_dtype(bool axis_fast, int dtype, const void* stack, const
   }
 }
 
-static hipError_t grid_cube_f32(const float* stack, const ViewGeom* geom, float* vol, int N, int M, int K, int nb,
-                                int accumulate, int flat, hipStream_t s) {
+template <class InT>
+static hipError_t grid_cube_impl(const InT* stack, const ViewGeom* geom, const float* scale, float* vol, int N, int M,
+                                 int K, int nb, int accumulate, int flat, hipStream_t s) {
+  constexpr int ES = int(sizeof(InT));
   const int ntc = (N + CB_E - 1) / CB_E;
   const int tiles = ntc * ntc * ntc, per = (tiles + 7) / 8;
   auto go = [&](auto ch, auto groups) {
     constexpr int CH = decltype(ch)::value, G = decltype(groups)::value;
-    hipLaunchKernelGGL((k_grid_cube_dma<CH, G>), dim3(unsigned(8 * per)), dim3(256 * G), 0, s, stack, geom, vol, N, M,
-                       K, nb, accumulate, flat);
+    hipLaunchKernelGGL((k_grid_cube_dma<InT, CH, G>), dim3(unsigned(8 * per)), dim3(256 * G), 0, s, stack, geom, scale,
+                       vol, N, M, K, nb, accumulate, flat);
     return hipGetLastError();
   };
-  // One tile per workgroup and one view at a time leaves a small volume with one wave per SIMD
+  // One tile per workgroup and one view at a time leave a small volume with one wave per SIMD
   // and every fetch exposed.  Up to one tile per CU four view groups share a tile (45^3, 60
   // views: 41 us, two groups 53, one 79), up to two per CU two do (64^3, 100 views: 106 us, one
   // group 134, four 136; 50^3, 60 views: 74, 97, 82); beyond that the tiles fill the chip by
@@ -1610,22 +1694,15 @@ static hipError_t grid_cube_f32(const float* stack, const ViewGeom* geom, float*
     if (tiles <= 512) return go(ch, integral_constant<int, 2>{});
     return go(ch, integral_constant<int, 1>{});
   };
-  // rows of whole 16-byte chunks take the wide fetch (96^3, 120 views: 383 us, by dwords 432)
-  return M % 4 == 0 ? pick(integral_constant<int, 16>{}) : pick(integral_constant<int, 4>{});
-}
-
-template <class InT>
-static hipError_t grid_cube_impl(const void* stack, const ViewGeom* geom, const float* scale, float* vol, int N,
-                                 int M, int K, int nb, int accumulate, int flat, hipStream_t s) {
-  if constexpr (std::is_same<InT, float>::value) {
-    return grid_cube_f32(static_cast<const float*>(stack), geom, vol, N, M, K, nb, accumulate, flat, s);
-  } else {
-    const int ntc = (N + CB_E - 1) / CB_E;
-    const int per = (ntc * ntc * ntc + 7) / 8;
-    hipLaunchKernelGGL(k_grid_cube<InT>, dim3(unsigned(8 * per)), dim3(256), 0, s, static_cast<const InT*>(stack),
-                       geom, scale, vol, N, M, K, nb, accumulate, flat);
+  // rows of whole 16-byte chunks take the wide fetch (96^3, 120 views: 384 us, by dwords 432)
+  if (M * ES % 16 == 0) return pick(integral_constant<int, 16>{});
+  if (M * ES % 4 == 0) return pick(integral_constant<int, 4>{});
+  if constexpr (ES == 2) {
+    hipLaunchKernelGGL(k_grid_cube<InT>, dim3(unsigned(8 * per)), dim3(256), 0, s, stack, geom, scale, vol, N, M, K,
+                       nb, accumulate, flat);
     return hipGetLastError();
   }
+  return hipErrorInvalidValue;
 }
 
 template <int YB, class InT>
@@ -1664,9 +1741,9 @@ hipError_t launch_grid(bool axis_fast, int dtype, const void* stack, const ViewG
     return grid_tilt_dtype<2>(dtype, stack, geom, scale, vol, N, M, K, nb, accumulate, flat, s);
   if (rows == 0 && !axis_fast) {
     switch (dtype) {
-      case 0: return grid_cube_impl<float>(stack, geom, nullptr, vol, N, M, K, nb, accumulate, flat, s);
-      case 1: return grid_cube_impl<__hip_bfloat16>(stack, geom, nullptr, vol, N, M, K, nb, accumulate, flat, s);
-      case 2: return grid_cube_impl<__half>(stack, geom, scale, vol, N, M, K, nb, accumulate, flat, s);
+      case 0: return grid_cube_impl(static_cast<const float*>(stack), geom, nullptr, vol, N, M, K, nb, accumulate, flat, s);
+      case 1: return grid_cube_impl(static_cast<const __hip_bfloat16*>(stack), geom, nullptr, vol, N, M, K, nb, accumulate, flat, s);
+      case 2: return grid_cube_impl(static_cast<const __half*>(stack), geom, scale, vol, N, M, K, nb, accumulate, flat, s);
       default: return hipErrorInvalidValue;
     }
   }

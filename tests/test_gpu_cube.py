@@ -54,7 +54,7 @@ def _reference(pb):
     return _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
 
 
-@pytest.mark.parametrize("n_vox,m", [(45, 48), (30, 30), (33, 45), (64, 64)])
+@pytest.mark.parametrize("n_vox,m", [(45, 48), (30, 30), (33, 45), (64, 64), (20, 16), (56, 50), (65, 72), (66, 54)])
 @pytest.mark.parametrize("dtype", [1, 2], ids=["bf16", "fp16"])
 def test_cubic_tiles_of_16_bit_planes(n_vox, m, dtype):
     pb = _general(n_vox, m, n_vox, 5)
