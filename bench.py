@@ -321,7 +321,7 @@ def main():
         plan.timing(False)
         k = plan.timing_read(reset=True)
         n_batches = -(-w.n_views // batch)
-        by_slices = not fourier and sliced(w, args.angle_batch)
+        by_slices = not fourier and args.plane_dtype == "f32" and sliced(w, args.angle_batch)
         kernels = {}
         for kind, (tot, cnt) in k.items():
             if cnt == 0:

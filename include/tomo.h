@@ -174,10 +174,9 @@ tomo_status tomo_grid(tomo_plan_t plan, const void* d_planes, int32_t first, int
 
 /* Whole reconstruction: d_volume (device float32 [N][N][N]) is overwritten with
  * the sum over all n views, processed in internal batches of the plan's batch
- * size; with angle_batch = 0, single-axis scans (ewald = 1, N and K at most M <= 192, M - N
- * and M - K even) run slice by slice instead, without plane stacks and so without the
- * rounding of 16-bit plane storage.  d_images: device float32 [n][M][M].  Synchronises the stream once at
- * the end to report TOMO_EDOMAIN. */
+ * size; with angle_batch = 0 and FP32 planes, single-axis scans (ewald = 1, N and K at most
+ * M <= 192, M - N and M - K even) run slice by slice instead, without plane stacks.  d_images:
+ * device float32 [n][M][M].  Synchronises the stream once at the end to report TOMO_EDOMAIN. */
 tomo_status tomo_reconstruct(tomo_plan_t plan, const float* d_images, float* d_volume, void* stream);
 
 /* tomo_reconstruct without the final synchronisation: every kernel of the reconstruction

@@ -69,6 +69,10 @@ template <> struct Shape<192> : Fft2Shape<192, 48, 4> {};
 template <int M>
 constexpr bool kSplit = (Shape<M>::LDS_BYTES > 80 * 1024);
 
+// The FP32 spectra kernel splits only where the full block would not fit in one CU's LDS.
+template <int M>
+constexpr bool kSplitSpectra = (Shape<M>::LDS_BYTES > 160 * 1024);
+
 // ------------------------------------------------------------------ plane storage types
 // FP32, BF16 (round to nearest even), FP16 (per-view power-of-two scale).
 template <class T>
@@ -468,6 +472,161 @@ __global__ __launch_bounds__(Shape<H>::T, H == 128 ? 8 : 1) void k_planes_split(
   }
 }
 
+// Filtered spectrum (Q1, Q2) of one coefficient: the filter table entry f times G.
+__device__ __forceinline__ float4 filtered(const float4 f, const float2 gg) {
+  float4 o;
+  o.x = f.x * gg.x - f.y * gg.y;
+  o.y = f.x * gg.y + f.y * gg.x;
+  o.z = f.z * gg.x - f.w * gg.y;
+  o.w = f.z * gg.y + f.w * gg.x;
+  return o;
+}
+
+// ------------------------------------------------------------------ spectra of 16-bit plans
+// One workgroup per view (or per block of a split size), the two-dimensional transform in FP32: 16-bit
+// stacks follow the last bits of their spectra by whole roundings, so these plans keep the
+// transforms whose results earlier stacks hold (128^2, 180 views: 80 us, the FP64 transforms 29).
+template <int M>
+__global__ __launch_bounds__(Shape<M>::T) void k_spectra(const float* __restrict__ images,
+                                                         const float4* __restrict__ filt,
+                                                         const float2* __restrict__ tw_fwd,
+                                                         float4* __restrict__ q, int* __restrict__ status,
+                                                         double inv_iin, float* __restrict__ scale) {
+  using S = Shape<M>;
+  __shared__ float2 lds[kSplitSpectra<M> ? (S::LDS_SPLIT_FLOATS + 1) / 2 : S::LDS_ELEMS];
+  __shared__ float red[(S::T + 63) / 64];
+  const int t = threadIdx.x;
+  const int view = blockIdx.x;
+  const int line = t % M, r = t / M;
+  const float* img = images + size_t(view) * M * M;
+  float2 x[S::XN];
+  int bad = 0;
+#pragma unroll
+  for (int m = 0; m < S::R1; ++m) {
+    const float iv = img[(r + S::R2 * m) * M + line];
+    const bool ok = (iv > 0.0f) && (iv < INFINITY);
+    bad |= !ok;
+    // contrast in FP64, rounded once: ln(I/I_in) of an FP32 intensity near I_in
+    const double g = ok ? log(double(iv) * inv_iin) : 0.0;
+    x[m] = make_float2(float(g), 0.0f);
+  }
+  if (bad) __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if constexpr (kSplitSpectra<M>) fft2_block_split<S, false>(x, reinterpret_cast<float*>(lds), tw_fwd);
+  else fft2_block<S, false>(x, lds, tw_fwd);
+  const int sg = t % S::R2, ky = t / S::R2;
+  const size_t row = (size_t(view) * M + ky) * M;
+  float l1 = 0.0f;
+#pragma unroll
+  for (int e = 0; e < S::E; ++e) {
+    if (!S::has_s(sg * S::E + e)) continue;
+#pragma unroll
+    for (int k2 = 0; k2 < S::R2; ++k2) {
+      const int kx = sg * S::E + e + S::R1 * k2;
+      const float4 o = filtered(filt[row + kx], x[e * S::R2 + k2]);
+      q[row + kx] = o;
+      l1 += fabsf(o.x) + fabsf(o.y) + fabsf(o.z) + fabsf(o.w);
+    }
+  }
+  if (scale) {
+    // FP16 plane storage: every plane value of this view is bounded by
+    // sum_k |cos Q1 + sin Q2| <= sum_k (|Q1| + |Q2|) <= l1; scale by the power of two that
+    // puts this bound at 2^14 (exact scaling, values stay below the FP16 maximum).
+    // Fixed-order reduction: wave sums, then the wave partials in order.
+    for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
+    if ((t & 63) == 0) red[t >> 6] = l1;
+    __syncthreads();
+    if (t == 0) {
+      float tot = 0.0f;
+      for (int w = 0; w < (S::T + 63) / 64; ++w) tot += red[w];
+      scale[view] = fp16_scale(tot);
+    }
+  }
+}
+
+// g = ln(I/I_in) of an M x M image -> filtered spectra (Q1, Q2) at the block's output
+// positions; l1part[view][block] = partial spectral bound for the FP16 scale.
+template <int H, int P>
+__global__ __launch_bounds__(Shape<H>::T) void k_spectra_split(const float* __restrict__ images,
+                                                              const float4* __restrict__ filt,
+                                                              const float2* __restrict__ tw_m,
+                                                              const float2* __restrict__ tw_h,
+                                                              float4* __restrict__ q, int* __restrict__ status,
+                                                              double inv_iin, float* __restrict__ l1part) {
+  using S = Shape<H>;
+  constexpr int M = P * H;
+  __shared__ float2 lds[(S::LDS_SPLIT_FLOATS + 1) / 2];
+  __shared__ float red[(S::T + 63) / 64];
+  const int t = threadIdx.x;
+  const int view = int(blockIdx.x / (P * P));
+  const unsigned blk = blockIdx.x % (P * P);
+  const int p1 = int(blk / P), p2 = int(blk % P);
+  const int n2 = t % H;
+  int r_;   // uniform across a wave when H is a multiple of the wave size
+  if constexpr (H % 64 == 0) r_ = __builtin_amdgcn_readfirstlane(t / H);
+  else r_ = t / H;
+  const int r = r_;
+  const float* img = images + size_t(view) * M * M;
+  float2 x[S::XN];
+  int bad = 0;
+#pragma unroll
+  for (int m = 0; m < S::R1; ++m) {
+    const int n1 = r + S::R2 * m;
+    float2 acc = make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int a = 0; a < P; ++a) {
+#pragma unroll
+      for (int b = 0; b < P; ++b) {
+        const float iv = img[(n1 + H * a) * M + n2 + H * b];
+        const bool ok = (iv > 0.0f) && (iv < INFINITY);
+        bad |= !ok;
+        const float g = ok ? float(log(double(iv) * inv_iin)) : 0.0f;
+        const float2 w = split_coef<P>(tw_m, H, (a * p1 + b * p2) % P);
+        acc.x += w.x * g;
+        acc.y += w.y * g;
+      }
+    }
+    const int ti = p1 * n1 + p2 * n2;   // < 2M
+    x[m] = cmul(acc, tw_m[ti >= M ? ti - M : ti]);
+  }
+  if (bad) __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  fft2_block_split<S, false>(x, reinterpret_cast<float*>(lds), tw_h);
+  const int sg = t % S::R2, yy = t / S::R2;
+  const int ky = P * yy + p1;
+  const size_t row = (size_t(view) * M + ky) * M;
+  float l1 = 0.0f;
+#pragma unroll
+  for (int e = 0; e < S::E; ++e) {
+    if (!S::has_s(sg * S::E + e)) continue;
+#pragma unroll
+    for (int k2 = 0; k2 < S::R2; ++k2) {
+      const int kx = P * (sg * S::E + e + S::R1 * k2) + p2;
+      const float4 o = filtered(filt[row + kx], x[e * S::R2 + k2]);
+      q[row + kx] = o;
+      l1 += fabsf(o.x) + fabsf(o.y) + fabsf(o.z) + fabsf(o.w);
+    }
+  }
+  if (l1part) {
+    for (int off = 32; off > 0; off >>= 1) l1 += __shfl_xor(l1, off, 64);
+    if ((t & 63) == 0) red[t >> 6] = l1;
+    __syncthreads();
+    if (t == 0) {
+      float tot = 0.0f;
+      for (int w = 0; w < (S::T + 63) / 64; ++w) tot += red[w];
+      l1part[blockIdx.x] = tot;
+    }
+  }
+}
+
+// FP16 plane scale of each view from its P^2 block bounds (fixed summation order).
+template <int P>
+__global__ void k_scale_split(const float* __restrict__ l1part, float* __restrict__ scale, int nb) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= nb) return;
+  float tot = 0.0f;
+  for (int b = 0; b < P * P; ++b) tot += l1part[P * P * v + b];
+  scale[v] = fp16_scale(tot);
+}
+
 // ------------------------------------------------------------------ launchers
 // Arguments of one planes launch, whatever the size.
 struct PlanesLaunch {
@@ -549,6 +708,38 @@ hipError_t planes_split(const PlanesLaunch& a) {
   }
 }
 
+// Arguments of one launch of FP32 spectra (16-bit plans).
+struct Spectra32Launch {
+  const float* images;
+  const float4* filt;
+  const float2* tw;        // M-point forward twiddles
+  const float2* tw_h;      // H-point forward twiddles (split sizes)
+  float4* q;
+  int* status;
+  double inv_iin;
+  float* scale;            // FP16 planes: per-view scale out, else null
+  float* l1part;           // split sizes with FP16 planes: [nb][P^2] partial bounds
+  int nb;
+  hipStream_t s;
+};
+
+template <int M>
+hipError_t spectra32_direct(const Spectra32Launch& a) {
+  hipLaunchKernelGGL(k_spectra<M>, dim3(a.nb), dim3(Shape<M>::T), 0, a.s, a.images, a.filt, a.tw, a.q, a.status,
+                     a.inv_iin, a.scale);
+  return hipGetLastError();
+}
+
+template <int H, int P>
+hipError_t spectra32_split(const Spectra32Launch& a) {
+  hipLaunchKernelGGL((k_spectra_split<H, P>), dim3(P * P * a.nb), dim3(Shape<H>::T), 0, a.s, a.images, a.filt, a.tw,
+                     a.tw_h, a.q, a.status, a.inv_iin, a.scale ? a.l1part : nullptr);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !a.scale) return e;
+  hipLaunchKernelGGL(k_scale_split<P>, dim3((a.nb + 255) / 256), dim3(256), 0, a.s, a.l1part, a.scale, a.nb);
+  return hipGetLastError();
+}
+
 // A size's launchers and the block split of its plane transform (P = 1: none).  The tables
 // of these are host data, filled at load time (not constant-initialised, so that the
 // device compilation does not take them, and the host launchers they point to, along).
@@ -556,30 +747,32 @@ struct FftSize {
   int M, P;
   hipError_t (*spectra)(const SpectraLaunch&);           // (Q1, Q2)
   hipError_t (*spectra_complex)(const SpectraLaunch&);   // times a complex filter
+  hipError_t (*spectra32)(const Spectra32Launch&);       // (Q1, Q2) of 16-bit plans
   hipError_t (*planes)(const PlanesLaunch&);
 };
 
 template <int M>
-__host__ FftSize size_of(int P, hipError_t (*planes)(const PlanesLaunch&)) {
-  return FftSize{M, P, &half_spectra<M, kFull>, &half_spectra<M, kComplex>, planes};
+__host__ FftSize size_of(int P, hipError_t (*spectra32)(const Spectra32Launch&),
+                         hipError_t (*planes)(const PlanesLaunch&)) {
+  return FftSize{M, P, &half_spectra<M, kFull>, &half_spectra<M, kComplex>, spectra32, planes};
 }
 template <int M>
 __host__ FftSize direct_size() {
-  return size_of<M>(1, &planes_direct<M>);
+  return size_of<M>(1, &spectra32_direct<M>, &planes_direct<M>);
 }
 // Row-split planes (the plan's tables are those of a direct size).
 template <int M>
 __host__ FftSize rows_size() {
-  return size_of<M>(1, &planes_rows<M>);
+  return size_of<M>(1, &spectra32_direct<M>, &planes_rows<M>);
 }
 // Row-split planes of a size whose direct shape does not exist (H = M / P).
 template <int H, int P>
 __host__ FftSize split_rows_size() {
-  return size_of<P * H>(P, &planes_rows<P * H>);
+  return size_of<P * H>(P, &spectra32_split<H, P>, &planes_rows<P * H>);
 }
 template <int H, int P>
 __host__ FftSize split_size() {
-  return size_of<P * H>(P, &planes_split<H, P>);
+  return size_of<P * H>(P, &spectra32_split<H, P>, &planes_split<H, P>);
 }
 
 }  // namespace tomo

@@ -30,8 +30,10 @@ struct tomo_plan_s {
   float2* d_prop = nullptr;     // [npairs][M]
   float2* d_tw_inv = nullptr;   // [M]
   double2* d_tw64 = nullptr;    // [M] exp(-i 2 pi k / M)
+  float2* d_tw_fwd = nullptr;   // [M] the same in FP32, and [H] of split sizes (spectra of 16-bit plans)
+  float2* d_tw2_fwd = nullptr;
   float2* d_tw2_inv = nullptr;  // [H] twiddles of the block sub-transforms of split sizes (M = P H)
-  float* d_l1 = nullptr;        // [n][spectra_groups] parts of the views' spectral bounds
+  float* d_l1 = nullptr;        // [n][spectra_groups or P^2] parts of the views' spectral bounds
   float4* d_q = nullptr;        // [n][M][M]  filtered spectra of every view
   void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type; before its planes, row spectra
   size_t stack_bytes = 0;
@@ -281,6 +283,8 @@ void free_plan(tomo_plan_s* pl) {
   (void)hipFree(pl->d_prop);
   (void)hipFree(pl->d_tw_inv);
   (void)hipFree(pl->d_tw64);
+  (void)hipFree(pl->d_tw_fwd);
+  (void)hipFree(pl->d_tw2_fwd);
   (void)hipFree(pl->d_tw2_inv);
   (void)hipFree(pl->d_l1);
   (void)hipFree(pl->d_q);
@@ -425,7 +429,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   // LDS and the caller left the batch to the library (an explicit angle_batch asks for stacks
   // of that many views).  The partial volumes live in the stack workspace: as many view blocks
   // as it holds, none if it holds not even one.
-  if (axis && p->ewald && p->angle_batch == 0 && tomo::axis_supported(r.M, r.N, r.K)) {
+  // 16-bit plans keep their stacks, and with them the rounding that they ask for.
+  if (axis && p->ewald && p->angle_batch == 0 && p->plane_dtype == TOMO_F32 && tomo::axis_supported(r.M, r.N, r.K)) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -437,7 +442,7 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   }
 
   // propagator table: (cos, sin)(pi lambda z'_p q^2), z'_p = (p - (K-1)/2) dx; twiddles
-  std::vector<float2> prop(size_t(r.npairs) * r.M), twi(r.M);
+  std::vector<float2> prop(size_t(r.npairs) * r.M), twf(r.M), twi(r.M);
   std::vector<double2> tw64(r.M);
   for (int pp = 0; pp < r.npairs; ++pp) {
     const double z = (pp - 0.5 * (r.K - 1)) * p->voxel_size;
@@ -452,13 +457,15 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
     const double a = 2.0 * kPi * k / r.M;
     twi[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
     tw64[k] = make_double2(std::cos(a), -std::sin(a));
+    twf[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
   }
   // H-point twiddles of the P^2 block transforms of split sizes (M = P H)
   const int split = tomo::fft_split(r.M);
   const int hpts = split > 1 ? r.M / split : 1;
-  std::vector<float2> tw2i(hpts);
+  std::vector<float2> tw2f(hpts), tw2i(hpts);
   for (int k = 0; k < hpts; ++k) {
     const double a = 2.0 * kPi * k / hpts;
+    tw2f[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
     tw2i[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
   }
 
@@ -472,8 +479,10 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
       (e = dev_alloc(&pl->d_prop, prop.size())) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw_inv, size_t(r.M))) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw64, size_t(r.M))) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw_fwd, size_t(r.M))) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw2_fwd, size_t(hpts))) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw2_inv, size_t(hpts))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_l1, size_t(tomo::spectra_groups(r.M)) * r.n)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_l1, size_t(std::max(tomo::spectra_groups(r.M), pl->split * pl->split)) * r.n)) != hipSuccess ||
       (e = dev_alloc(&pl->d_q, mm * r.n)) != hipSuccess ||
       (e = dev_alloc(reinterpret_cast<char**>(&pl->d_stack), pl->stack_bytes)) != hipSuccess ||
       (e = dev_alloc(&pl->d_scale, size_t(r.n))) != hipSuccess ||
@@ -499,6 +508,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   if ((e = hipMemcpyAsync(pl->d_geom, geo.data(), sizeof(ViewGeom) * r.n, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_prop, prop.data(), sizeof(float2) * prop.size(), hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw64, tw64.data(), sizeof(double2) * r.M, hipMemcpyHostToDevice, s)) ||
+      (e = hipMemcpyAsync(pl->d_tw_fwd, twf.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
+      (e = hipMemcpyAsync(pl->d_tw2_fwd, tw2f.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw_inv, twi.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
       (e = hipMemcpyAsync(pl->d_tw2_inv, tw2i.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)))
     return cleanup_fail(e, "upload");
@@ -679,14 +690,23 @@ static tomo_status check_range(tomo_plan_t pl, int32_t first, int32_t nb) {
   return TOMO_OK;
 }
 
+// Filtered spectra of views [first, first + nb) into q: transformed in FP64, in FP32 where the planes are
+// stored in 16 bits (see k_spectra).
+static hipError_t enqueue_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, float4* q, hipStream_t s) {
+  const float4* filt = pl->d_filt + size_t(first) * pl->M * pl->M;
+  const double inv_iin = 1.0 / pl->p.i_in;
+  if (pl->p.plane_dtype == TOMO_F32)
+    return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, filt, q, pl->status, inv_iin, nb, s, pl->d_stack,
+                                pl->stack_bytes);
+  float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
+  return tomo::launch_spectra32(pl->M, d_images, filt, pl->d_tw_fwd, pl->d_tw2_fwd, q, pl->status, inv_iin, scale,
+                                pl->d_l1 + size_t(pl->split * pl->split) * first, nb, s);
+}
+
 // Spectra of views [first, first+nb) into the plan's per-view slots of d_q.
 static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s) {
-  const size_t mm = size_t(pl->M) * pl->M;
-  float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
   hipError_t e = timed(pl, 0, s, [&] {
-    return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, pl->d_q + size_t(first) * mm,
-                                pl->status, 1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
-                                pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
+    return enqueue_spectra(pl, d_images, first, nb, pl->d_q + size_t(first) * pl->M * pl->M, s);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   return TOMO_OK;
@@ -742,12 +762,8 @@ tomo_status tomo_backpropagate_noalloc(tomo_plan_t pl, const float* d_images, in
     }
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  const size_t mm = size_t(pl->M) * pl->M;
   float4* q = static_cast<float4*>(pl->scratch);
-  float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
-  hipError_t e = tomo::launch_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt + size_t(first) * mm, q, pl->status,
-                                      1.0 / pl->p.i_in, scale, nb, s, pl->d_stack, pl->stack_bytes,
-                                      pl->d_l1 + size_t(tomo::spectra_groups(pl->M)) * first);
+  hipError_t e = enqueue_spectra(pl, d_images, first, nb, q, s);
   if (e != hipSuccess) return fail_fixed(pl, TOMO_EDEVICE, "spectra kernel: ", hipGetErrorString(e));
   e = tomo::launch_planes(pl->M, pl->p.plane_dtype, q, pl->d_prop, pl->d_tw_inv, d_planes, pl->K, pl->npairs, nb,
                           pl->d_scale + first, s, pl->d_tw2_inv);
@@ -795,7 +811,8 @@ static tomo_status enqueue_reconstruct(tomo_plan_t pl, const float* d_images, fl
   if (pl->axis_blocks > 0) {
     float* part = static_cast<float*>(pl->d_stack);
     hipError_t e = timed(pl, 0, s, [&] {
-      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt, pl->d_q, pl->status, 1.0 / pl->p.i_in, pl->n, s);
+      return tomo::launch_axis_spectra(pl->M, d_images, pl->d_tw64, pl->d_filt, pl->d_q, pl->status, 1.0 / pl->p.i_in,
+                                       pl->n, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "spectra kernels");
     e = timed(pl, 1, s, [&] {

@@ -26,13 +26,16 @@ bool fft_supported(int M);
 int fft_split(int M);
 
 // g = ln(I/I_in) -> 2D DFT G -> (Q1, Q2) = filt G for nb views.  filt, q: [nb][M][M] float4.
-// scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb], with l1
-// [nb][spectra_groups(M)].  scratch: at least spectra_scratch_bytes(M), the more views it holds the
+// scratch: at least spectra_scratch_bytes(M), the more views it holds the
 // fewer launches.  tw: [M] exp(-i 2 pi k / M).  The complex form: filt, q float2.
 int spectra_groups(int M);
 size_t spectra_scratch_bytes(int M);
-hipError_t launch_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* q, int* status, double inv_iin,
-                          float* scale, int nb, hipStream_t s, void* scratch, size_t scratch_bytes, float* l1);
+hipError_t launch_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* q, int* status,
+                          double inv_iin, int nb, hipStream_t s, void* scratch, size_t scratch_bytes);
+// The same of 16-bit plans, transformed in FP32: tw_fwd [M] and, for split sizes, tw_half_fwd [M / P].
+// scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb], with l1part [nb][P^2].
+hipError_t launch_spectra32(int M, const float* images, const float4* filt, const float2* tw_fwd, const float2* tw_half_fwd,
+                            float4* q, int* status, double inv_iin, float* scale, float* l1part, int nb, hipStream_t s);
 hipError_t launch_spectra_complex(int M, const float* images, const double2* tw, const float2* filt, float2* q, int* status,
                                   double inv_iin, float* scale, int nb, hipStream_t s, void* scratch,
                                   size_t scratch_bytes, float* l1);
