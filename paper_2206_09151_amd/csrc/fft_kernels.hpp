@@ -64,11 +64,36 @@ template <> struct Shape<150> : Fft2Shape<150, 30, 5> {};
 template <> struct Shape<160> : Fft2Shape<160, 40, 4> {};
 template <> struct Shape<192> : Fft2Shape<192, 48, 4> {};
 
-// Exchanges through half-size LDS (real, then imaginary parts) where the full block would
-// leave room for only one workgroup per CU (two fit then).
+// Shapes of the plane kernels of FP32 stacks where others than those above are faster (us per view over
+// general scans): 36 0.227 -> 0.217, 40 0.327 / 0.270, 45 0.346 / 0.336, 54 0.499 / 0.435, 60 0.575 / 0.511,
+// 90 2.41 / 1.89, 100 2.09 / 1.47, 120 4.20 / 4.05.  16-bit stacks keep the shapes above, as their spectra do:
+// another order of the sums flips roundings of 2^-9 or 2^-12, and their volumes would differ from
+// earlier ones by more than FP32 results of one method do.
 template <int M>
-constexpr bool kSplit = (Shape<M>::LDS_BYTES > 80 * 1024);
+struct FastShape : Shape<M> {};
+template <> struct FastShape<36> : Fft2Shape<36, 12, 3> {};
+template <> struct FastShape<40> : Fft2Shape<40, 8, 5> {};
+template <> struct FastShape<45> : Fft2Shape<45, 15, 3> {};
+template <> struct FastShape<54> : Fft2Shape<54, 18, 3> {};
+template <> struct FastShape<60> : Fft2Shape<60, 15, 4> {};
+template <> struct FastShape<90> : Fft2Shape<90, 18, 5> {};
+template <> struct FastShape<100> : Fft2Shape<100, 20, 5> {};
+template <> struct FastShape<120> : Fft2Shape<120, 15, 8> {};
 
+template <int M, class OutT>
+using PlaneShape = std::conditional_t<std::is_same<OutT, float>::value, FastShape<M>, Shape<M>>;
+// H x H blocks of the P x P split (k_planes_split), whose input stage reads P^2 blocks per value: 100
+// keeps more, smaller threads (200 x 200: 19.8 us per view, as 20 x 5 31.1).
+template <int H, class OutT>
+using BlockShape = std::conditional_t<H == 100, Shape<H>, PlaneShape<H, OutT>>;
+
+// Exchanges through half-size LDS (real, then imaginary parts) where the full block would leave
+// room for only one workgroup per CU, and of FP32 stacks where a third or fourth workgroup gains more
+// than the two extra barriers per exchange cost (us per view: 72 0.594 against 0.603, 75 0.684 / 0.729, 96
+// 1.63 / 1.89, 100 1.47 / 2.01; whole blocks stay ahead at 80 1.02 / 1.05 and 81 1.05 / 1.12).
+template <int M, class OutT>
+constexpr bool kSplit = Shape<M>::LDS_BYTES > 80 * 1024 ||
+                        (std::is_same<OutT, float>::value && (M == 72 || M == 75 || M == 96 || M == 100));
 // The FP32 spectra kernel splits only where the full block would not fit in one CU's LDS.
 template <int M>
 constexpr bool kSplitSpectra = (Shape<M>::LDS_BYTES > 160 * 1024);
@@ -93,18 +118,33 @@ __device__ __forceinline__ float from_store<__hip_bfloat16>(__hip_bfloat16 v) { 
 template <>
 __device__ __forceinline__ float from_store<__half>(__half v) { return __half2float(v); }
 
+// Twiddles and propagators in LDS.  Where the line length is not a multiple of the wave size,
+// lanes of one wave sit on different stage indices r, and tw[r s] and the propagators of the rows
+// are vector loads, two per value and pass, each waited for; out of LDS they take a fraction of
+// the latency and no address registers (96: 153 -> 88 VGPRs).  Plane kernels over general scans, us
+// per view before and after: 48 0.325 -> 0.295, 72 0.736 -> 0.602, 80 1.15 -> 1.02, 108 3.34 -> 2.22,
+// 144 10.2 -> 6.5, 160 13.1 -> 10.6, 216 49 -> 35.  Not for the 3 x 3 split, which reads nine input
+// blocks per value and loses workgroups to the tables (225: 67 -> 92).
+template <int LINE>
+constexpr bool kLdsTables = LINE % 64 != 0;
+
+template <int T, int N>
+__device__ __forceinline__ void to_lds(float2 (&dst)[N], const float2* __restrict__ src) {
+  for (int i = threadIdx.x; i < N; i += T) dst[i] = src[i];
+}
+
 // ------------------------------------------------------------------ K3: planes
 // Workgroup -> (view, pair) mapping keeps all pairs of one view on one XCD
 // (workgroups are dealt to the 8 XCDs round robin), so the view's Q block is
 // fetched into one L2 only.
 template <int M, class OutT>
-__global__ __launch_bounds__(Shape<M>::T) void k_planes(const float4* __restrict__ q,
+__global__ __launch_bounds__((PlaneShape<M, OutT>::T)) void k_planes(const float4* __restrict__ q,
                                                         const float2* __restrict__ prop,
                                                         const float2* __restrict__ tw_inv,
                                                         OutT* __restrict__ stack, int K, int npairs,
                                                         int nb, const float* __restrict__ scale) {
-  using S = Shape<M>;
-  __shared__ float2 lds[kSplit<M> ? (S::LDS_SPLIT_FLOATS + 1) / 2 : S::LDS_ELEMS];
+  using S = PlaneShape<M, OutT>;
+  __shared__ float2 lds[kSplit<M, OutT> ? (S::LDS_SPLIT_FLOATS + 1) / 2 : S::LDS_ELEMS];
   const int wg = blockIdx.x;
   const int xcd = wg & 7, k = wg >> 3;
   int view, p;
@@ -126,6 +166,16 @@ __global__ __launch_bounds__(Shape<M>::T) void k_planes(const float4* __restrict
   const int r = r_;
   const float4* qv = q + size_t(view) * M * M;
   const float2* pr = prop + size_t(p) * M;
+  const float2* tw = tw_inv;
+  // (not where whole-block exchanges and the tables leave one workgroup per CU)
+  if constexpr (kLdsTables<M> && (kSplit<M, OutT> || S::LDS_BYTES + 16 * M <= 80 * 1024)) {
+    __shared__ float2 tw_l[M], pr_l[M];
+    to_lds<S::T>(tw_l, tw);
+    to_lds<S::T>(pr_l, pr);
+    __syncthreads();
+    tw = tw_l;
+    pr = pr_l;
+  }
   const float2 cx = pr[line];
   float2 x[S::XN];
 #pragma unroll
@@ -146,8 +196,8 @@ __global__ __launch_bounds__(Shape<M>::T) void k_planes(const float4* __restrict
     sc = scale[view];
     asm volatile("" : "+v"(sc));
   }
-  if constexpr (kSplit<M>) fft2_block_split<S, true>(x, reinterpret_cast<float*>(lds), tw_inv);
-  else fft2_block<S, true>(x, lds, tw_inv);
+  if constexpr (kSplit<M, OutT>) fft2_block_split<S, true>(x, reinterpret_cast<float*>(lds), tw);
+  else fft2_block<S, true>(x, lds, tw);
   const int sg = t % S::R2, y = t / S::R2;
   const int pa = p, pb = K - 1 - p;
   OutT* rowa = stack + ((size_t(view) * M + y) * K + pa) * M;
@@ -224,7 +274,7 @@ __device__ __forceinline__ void rows_input(const float4* __restrict__ qv, const 
 template <int M, class OutT>
 __global__ __launch_bounds__(RowSplit<M>::T) void k_planes_rows(const float4* __restrict__ q,
                                                                  const float2* __restrict__ prop,
-                                                                 const float2* __restrict__ tw,
+                                                                 const float2* __restrict__ tw_g,
                                                                  OutT* __restrict__ stack, int K, int npairs,
                                                                  int nb, const float* __restrict__ scale) {
   using S = RowSplit<M>;
@@ -255,6 +305,15 @@ __global__ __launch_bounds__(RowSplit<M>::T) void k_planes_rows(const float4* __
   const int r = r_;
   const float4* qv = q + size_t(view) * M * M;
   const float2* pr = prop + size_t(p) * M;
+  const float2* tw = tw_g;
+  if constexpr (kLdsTables<M>) {
+    __shared__ float2 tw_l[M], pr_l[M];
+    to_lds<S::T>(tw_l, tw);
+    to_lds<S::T>(pr_l, pr);
+    __syncthreads();
+    tw = tw_l;
+    pr = pr_l;
+  }
   float2 x[S::XN];
   if constexpr (P == 4) {
     // the block's quarter turns as operand swaps: one instantiation per block
@@ -378,13 +437,13 @@ __device__ __forceinline__ void split2_input(const float4* __restrict__ qv, cons
 
 // Plane pairs of M x M spectra: workgroup (view, pair, block).
 template <int H, int P, class OutT>
-__global__ __launch_bounds__(Shape<H>::T, H == 128 ? 8 : 1) void k_planes_split(const float4* __restrict__ q,
+__global__ __launch_bounds__((BlockShape<H, OutT>::T), H == 128 ? 8 : 1) void k_planes_split(const float4* __restrict__ q,
                                                              const float2* __restrict__ prop,
-                                                             const float2* __restrict__ tw_m,
-                                                             const float2* __restrict__ tw_h,
+                                                             const float2* __restrict__ tw_mg,
+                                                             const float2* __restrict__ tw_hg,
                                                              OutT* __restrict__ stack, int K, int npairs, int nb,
                                                              const float* __restrict__ scale) {
-  using S = Shape<H>;
+  using S = BlockShape<H, OutT>;
   constexpr int M = P * H;
   __shared__ float2 lds[(S::LDS_SPLIT_FLOATS + 1) / 2];
   const int wg = blockIdx.x;
@@ -415,6 +474,17 @@ __global__ __launch_bounds__(Shape<H>::T, H == 128 ? 8 : 1) void k_planes_split(
   const int r = r_;
   const float4* qv = q + size_t(view) * M * M;
   const float2* pr = prop + size_t(p) * M;
+  const float2 *tw_m = tw_mg, *tw_h = tw_hg;
+  if constexpr (kLdsTables<H> && P == 2) {
+    __shared__ float2 twm_l[M], twh_l[H], pr_l[M];
+    to_lds<S::T>(twm_l, tw_m);
+    to_lds<S::T>(twh_l, tw_h);
+    to_lds<S::T>(pr_l, pr);
+    __syncthreads();
+    tw_m = twm_l;
+    tw_h = twh_l;
+    pr = pr_l;
+  }
   float2 x[S::XN];
   if constexpr (P == 2) {
     switch (blk) {   // uniform across the workgroup
@@ -648,7 +718,7 @@ hipError_t planes_direct_t(const PlanesLaunch& a, const float* scale) {
   const int nb = a.nb, npairs = a.npairs;
   const int reps = (nb == 1 || nb == 2 || nb == 4) ? 8 / nb : 0;
   const int rows = reps ? (npairs + reps - 1) / reps : npairs * ((nb + 7) / 8);
-  hipLaunchKernelGGL((k_planes<M, OutT>), dim3(8 * rows), dim3(Shape<M>::T), 0, a.s, a.q, a.prop, a.tw,
+  hipLaunchKernelGGL((k_planes<M, OutT>), dim3(8 * rows), dim3((PlaneShape<M, OutT>::T)), 0, a.s, a.q, a.prop, a.tw,
                      static_cast<OutT*>(a.stack), a.K, npairs, nb, scale);
   return hipGetLastError();
 }
@@ -693,7 +763,7 @@ hipError_t planes_split_t(const PlanesLaunch& a, const float* scale) {
   const int per_view = P * P * a.npairs;
   const int reps = (a.nb == 1 || a.nb == 2 || a.nb == 4) ? 8 / a.nb : 0;
   const int rows = reps ? (per_view + reps - 1) / reps : per_view * ((a.nb + 7) / 8);
-  hipLaunchKernelGGL((k_planes_split<H, P, OutT>), dim3(8 * rows), dim3(Shape<H>::T), 0, a.s, a.q,
+  hipLaunchKernelGGL((k_planes_split<H, P, OutT>), dim3(8 * rows), dim3((BlockShape<H, OutT>::T)), 0, a.s, a.q,
                      a.prop, a.tw, a.tw_h, static_cast<OutT*>(a.stack), a.K, a.npairs, a.nb, scale);
   return hipGetLastError();
 }
