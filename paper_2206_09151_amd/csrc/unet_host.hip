@@ -45,7 +45,7 @@ struct tomo_unet_s {
   float *g_e1b = nullptr, *g_e1a = nullptr;
   __hip_bfloat16* wbf = nullptr;
   unsigned short *wf = nullptr, *wd = nullptr;   // matrix-core weight layouts (same offsets as wbf)
-  float *pw = nullptr, *pb = nullptr, *q = nullptr;
+  float *pw = nullptr, *pb = nullptr;
   double* part = nullptr;
   std::vector<void*> allocs;
   std::string err;
@@ -86,12 +86,15 @@ const float* B(const tomo_unet_s* u, const float* th, int l) { return th + u->of
 hipError_t forward(tomo_unet_s* u, const float* th, const float* x, float* y, hipStream_t s) {
   const int n = u->n, h = n / 2, q = n / 4;
   hipError_t e;
-  const int P = u->off[kNL];
-  if ((e = unet::round_bf16(th, u->wbf, P, s))) return e;
-  for (int l = 0; l < kNL; ++l)
-    if (has_layout(l) &&
-        (e = unet::weight_layout(W(u, l), kLayers[l].cout, kLayers[l].cin, u->wf + u->off[l], u->wd + u->off[l], s)))
-      return e;
+  unet::MfmaLayers layers{};
+  for (int l = 0; l < kNL; ++l) {
+    if (!has_layout(l)) continue;
+    const int k = layers.count++;
+    layers.off[k] = u->off[l];
+    layers.cin[k] = kLayers[l].cin;
+    layers.cout[k] = kLayers[l].cout;
+  }
+  if ((e = unet::weights(th, u->off[kNL], layers, u->wbf, u->wf, u->wd, s))) return e;
   float* e1b = u->c1 + 32;   // channels 32..47 of the level-1 concatenation
   float* e2b = u->c2 + 64;   // channels 64..95 of the level-2 concatenation
   if ((e = unet::conv_fwd(3, x, 1, 1, W(u, E1A), WF(u, E1A), B(u, th, E1A), u->e1a, 16, 16, n, 1, nullptr, s))) return e;
@@ -116,7 +119,7 @@ hipError_t forward(tomo_unet_s* u, const float* th, const float* x, float* y, hi
 hipError_t layer_back(tomo_unet_s* u, int l, const float* in, int sin, const float* g, int sg, const float* yout,
                       int sy, int n, float* grad, float* gx, int sgx, hipStream_t s) {
   const Layer& L = kLayers[l];
-  hipError_t e = unet::conv_bwd_w(L.ks, in, sin, L.cin, g, sg, yout, sy, L.cout, n, u->pw, u->pb, u->q,
+  hipError_t e = unet::conv_bwd_w(L.ks, in, sin, L.cin, g, sg, yout, sy, L.cout, n, u->pw, u->pb,
                                   grad + u->off[l], grad + u->off[l] + weights_of(l), s);
   if (e != hipSuccess || !gx) return e;
   return unet::conv_bwd_data(L.ks, g, sg, yout, sy, L.cout, W(u, l), WD(u, l), gx, sgx, L.cin, n, s);
@@ -167,14 +170,13 @@ tomo_status tomo_unet_create(int32_t n, tomo_unet_t* out) {
   u->v3 = u->v2 / 8;
   u->off = offsets();
   // weight-gradient workspace: the largest any layer needs at its level's edge
-  size_t max_pw = 0, max_pb = 0, max_q = 0;
+  size_t max_pw = 0, max_pb = 0;
   const int level_n[kNL] = {n, n, n / 2, n / 2, n / 4, n / 4, n / 2, n / 2, n, n, n};
   for (int l = 0; l < kNL; ++l) {
-    size_t a, b, c;
-    unet::wgrad_workspace(kLayers[l].ks, kLayers[l].cin, kLayers[l].cout, level_n[l], a, b, c);
+    size_t a, b;
+    unet::wgrad_workspace(kLayers[l].ks, kLayers[l].cin, kLayers[l].cout, level_n[l], a, b);
     max_pw = std::max(max_pw, a);
     max_pb = std::max(max_pb, b);
-    max_q = std::max(max_q, c);
   }
   const size_t v1 = u->v1, v2 = u->v2, v3 = u->v3;
   hipError_t e;
@@ -189,7 +191,7 @@ tomo_status tomo_unet_create(int32_t n, tomo_unet_t* out) {
       (e = grab(u, &u->g_e2a, 32 * v2)) || (e = grab(u, &u->g_p1, 16 * v2)) || (e = grab(u, &u->g_e1b, 16 * v1)) ||
       (e = grab(u, &u->g_e1a, 16 * v1)) || (e = grab(u, &u->wbf, size_t(u->off[kNL]))) ||
       (e = grab(u, &u->wf, size_t(u->off[kNL]))) || (e = grab(u, &u->wd, size_t(u->off[kNL]))) ||
-      (e = grab(u, &u->pw, max_pw)) || (e = grab(u, &u->pb, max_pb)) || (e = grab(u, &u->q, max_q)) ||
+      (e = grab(u, &u->pw, max_pw)) || (e = grab(u, &u->pb, max_pb)) ||
       (e = grab(u, &u->part, (v1 + 255) / 256))) {
     release(u);
     delete u;
