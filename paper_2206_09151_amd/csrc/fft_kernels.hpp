@@ -1,5 +1,5 @@
-// Depth-plane kernels of the reconstruction for every supported detector
-// size M (all 2,3,5-smooth M in [16, 256]), as templates; each size is instantiated, with its
+// Depth-plane kernels of the reconstruction, and the spectra of 16-bit plans, for every supported
+// detector size M (all 2,3,5-smooth M in [16, 256]), as templates; each size is instantiated, with its
 // spectra kernels (spectra_kernels.hpp), in exactly one of the fft_sizes_*.hip translation units,
 // which register a launcher for it in the size table of tomo_kernels.hip.
 //
@@ -14,6 +14,8 @@
 //               for 162, 180 and 200, whose direct transforms would need R1 = 27 to 40
 //               values per thread in registers and spill at the 1000-thread workgroup.
 //   k_planes_rows: the planes of 160, 192 and 256 as P blocks of whole output rows.
+//   k_spectra, k_spectra_split: filtered spectra (Q1, Q2) of plans with 16-bit planes, and of the
+//               stacks of the smallest detectors.
 #pragma once
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
