@@ -143,6 +143,7 @@ __device__ __forceinline__ void put_line(const double2 (&x)[S::XN], double2* min
 // Natural logarithm of a positive finite double to about 1e-13 relative: x = 2^e m, m in
 // [1/sqrt 2, sqrt 2), ln m = 2 atanh(s) = 2 s (1 + s^2/3 + s^4/5 + ...), s = (m-1)/(m+1), |s| < 0.172.
 // A third of the library function's instructions (whose last bits the FP32 storage does not hold).
+// 0 (an I/I_in below FP64's range, from an extreme I_in) gives -infinity, infinity NaN.
 __device__ __forceinline__ double log_positive(double x) {
   double m = __builtin_amdgcn_frexp_mant(x);             // [1/2, 1)
   int e = __builtin_amdgcn_frexp_exp(x);
@@ -162,7 +163,8 @@ __device__ __forceinline__ double log_positive(double x) {
   p = fma(p, z, 1.0 / 7.0);
   p = fma(p, z, 1.0 / 5.0);
   p = fma(p, z, 1.0 / 3.0);
-  return fma(double(e), 0.69314718055994530942, 2.0 * fma(s * z, p, s));
+  const double ln = fma(double(e), 0.69314718055994530942, 2.0 * fma(s * z, p, s));
+  return x > 0.0 ? ln : -INFINITY;
 }
 
 template <int M>
