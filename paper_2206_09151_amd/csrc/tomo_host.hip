@@ -22,6 +22,7 @@ struct tomo_plan_s {
   tomo_params p{};
   int N = 0, M = 0, K = 0, n = 0, npairs = 0, batch = 0;
   int split = 1;                // block split of the detector-size FFT (M = P H for M > 200)
+  bool spectra64 = false;       // the stacks' spectra by two kernels in FP64
   bool axis_fast = false;
   int axis_blocks = 0;          // view blocks of the single-axis slice kernels (0: plane stacks)
   int grid_rows = 8;            // gridding variant: 8 or 4 voxel rows per thread, 0 cubic tiles (params.tune)
@@ -29,11 +30,11 @@ struct tomo_plan_s {
   float4* d_filt = nullptr;     // [n][M][M]
   float2* d_prop = nullptr;     // [npairs][M]
   float2* d_tw_inv = nullptr;   // [M]
-  double2* d_tw64 = nullptr;    // [M] exp(-i 2 pi k / M)
-  float2* d_tw_fwd = nullptr;   // [M] the same in FP32, and [H] of split sizes (spectra of 16-bit plans)
+  double2* d_tw64 = nullptr;    // [M] exp(-i 2 pi k / M) (spectra in FP64, slices)
+  float2* d_tw_fwd = nullptr;   // [M] the same in FP32, and [H] of split sizes (spectra in FP32)
   float2* d_tw2_fwd = nullptr;
   float2* d_tw2_inv = nullptr;  // [H] twiddles of the block sub-transforms of split sizes (M = P H)
-  float* d_l1 = nullptr;        // [n][spectra_groups or P^2] parts of the views' spectral bounds
+  float* d_l1 = nullptr;        // [n][spectra_groups or P^2] parts of the views' spectral bounds (FP16, fourier = 2)
   float4* d_q = nullptr;        // [n][M][M]  filtered spectra of every view
   void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type; before its planes, row spectra
   size_t stack_bytes = 0;
@@ -88,12 +89,24 @@ constexpr double kPi = 3.141592653589793238462643383279502884;
 
 struct Resolved {
   int N, M, K, n, npairs, batch, P;
-  size_t table_bytes, work_bytes;
+  int split, H;            // M = split H; H: points of the block transforms (0 without a split)
+  bool spectra64;          // FP32 planes: the stacks' spectra by the two kernels in FP64
+  // values of the arrays that only some plans have (tw64: double2, tw_fwd, tw2_*: float2, l1: float)
+  size_t tw64, tw_fwd, tw2_fwd, tw2_inv, l1;
+  size_t stack_bytes;      // plane stacks of a batch; before their planes, row spectra
+  size_t table_bytes, work_bytes;   // sums over every array of the plan on the device
 };
 
 size_t dtype_bytes(int dtype) { return dtype == TOMO_F32 ? 4 : 2; }
 
 size_t stack_view_bytes(int M, int K, int dtype) { return size_t(M) * K * M * dtype_bytes(dtype); }
+
+// Whether the stacks' spectra are transformed in FP64 by two kernels, or in FP32 by one: that is so where
+// the planes are stored in 16 bits (see k_spectra) and below M = 48, where a call of few views costs its
+// launches (8 views at a time, 160 in all: 24^2 375 us with one kernel, 451 with two; 36^2 434 / 440;
+// 48^2 475 / 470; 64^2 638 / 553; calls of one to eight views at 48^2 and 50^2 pay 0.8 to 1.4 us of 13 for
+// the second launch, from 54^2 on none).
+bool two_kernel_spectra(int M, int dtype) { return dtype == TOMO_F32 && M >= 48; }
 
 // Resolve defaults and sizes; returns an error message or "" and fills r.
 std::string resolve(const tomo_params* p, Resolved* r) {
@@ -133,13 +146,28 @@ std::string resolve(const tomo_params* p, Resolved* r) {
     b -= b % 8;
     r->batch = std::min(b, r->n);
   }
-  r->table_bytes = size_t(r->n) * sizeof(ViewGeom) + size_t(r->n) * qv + size_t(r->npairs) * r->M * 8 +
-                   4 * size_t(r->M) * 8 + size_t(r->n) * 4 * 10 + 256;
-  r->work_bytes = size_t(r->n) * qv + size_t(r->batch) * sv;
+  r->split = std::max(1, tomo::fft_split(r->M));
+  r->H = r->split > 1 ? r->M / r->split : 0;
+  r->spectra64 = two_kernel_spectra(r->M, p->plane_dtype);
+  const bool slices = p->plane_dtype == TOMO_F32 && p->ewald && p->angle_batch == 0 &&
+                      tomo::axis_supported(r->M, r->N, r->K);   // (of single-axis directions)
+  const bool rows = r->spectra64 || p->fourier;                 // row spectra in the stack workspace
+  r->tw64 = rows || slices ? size_t(r->M) : 0;
+  r->tw_fwd = r->spectra64 ? 0 : size_t(r->M);
+  r->tw2_fwd = r->spectra64 ? 0 : size_t(r->H);
+  r->tw2_inv = size_t(r->H);
+  r->l1 = std::max(p->plane_dtype == TOMO_F16 ? size_t(r->split * r->split) : 0,
+                   p->fourier == 2 ? size_t(tomo::spectra_groups(r->M)) : 0) * r->n;
+  // (one view's row spectra at least: more than the stacks only of a single plane)
+  r->stack_bytes = std::max(size_t(r->batch) * sv, rows ? tomo::spectra_scratch_bytes(r->M) : 0);
+  r->table_bytes = size_t(r->n) * (sizeof(ViewGeom) + qv) +
+                   (size_t(r->npairs) * r->M + r->M + r->tw_fwd + r->tw2_fwd + r->tw2_inv) * sizeof(float2) +
+                   r->tw64 * sizeof(double2) + (r->l1 + r->n) * sizeof(float);
+  r->work_bytes = size_t(r->n) * qv + r->stack_bytes;
   r->P = r->N + (r->N % 2 == 0 ? 1 : 0);
   if (p->fourier) {
     const size_t n3 = size_t(r->N) * r->N * r->N, p3 = size_t(r->P) * r->P * r->P;
-    r->table_bytes += size_t(r->n) * qv + n3 * 8 + size_t(r->N) * 8 + size_t(r->n) * 4 + 16;
+    r->table_bytes += size_t(r->n) * qv / 2 + n3 * 8 + size_t(r->N) * 8 + size_t(r->n) * 4 + 16;
     r->work_bytes += n3 * 8;
     if (p->fourier == 2) {
       r->work_bytes += p3 * 16;
@@ -400,7 +428,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   pl->npairs = r.npairs;
   pl->batch = r.batch;
   pl->P = r.P;
-  pl->split = tomo::fft_split(r.M);
+  pl->split = r.split;
+  pl->spectra64 = r.spectra64;
   pl->p.n_pix = r.M;
   pl->p.n_planes = r.K;
   if (pl->p.i_in == 0) pl->p.i_in = 1.0;
@@ -442,8 +471,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   }
 
   // propagator table: (cos, sin)(pi lambda z'_p q^2), z'_p = (p - (K-1)/2) dx; twiddles
-  std::vector<float2> prop(size_t(r.npairs) * r.M), twf(r.M), twi(r.M);
-  std::vector<double2> tw64(r.M);
+  std::vector<float2> prop(size_t(r.npairs) * r.M), twf(r.tw_fwd), twi(r.M);
+  std::vector<double2> tw64(r.tw64);
   for (int pp = 0; pp < r.npairs; ++pp) {
     const double z = (pp - 0.5 * (r.K - 1)) * p->voxel_size;
     for (int k = 0; k < r.M; ++k) {
@@ -456,33 +485,29 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   for (int k = 0; k < r.M; ++k) {
     const double a = 2.0 * kPi * k / r.M;
     twi[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
-    tw64[k] = make_double2(std::cos(a), -std::sin(a));
-    twf[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
+    if (r.tw64) tw64[k] = make_double2(std::cos(a), -std::sin(a));
+    if (r.tw_fwd) twf[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
   }
   // H-point twiddles of the P^2 block transforms of split sizes (M = P H)
-  const int split = tomo::fft_split(r.M);
-  const int hpts = split > 1 ? r.M / split : 1;
-  std::vector<float2> tw2f(hpts), tw2i(hpts);
-  for (int k = 0; k < hpts; ++k) {
-    const double a = 2.0 * kPi * k / hpts;
-    tw2f[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
+  std::vector<float2> tw2f(r.tw2_fwd), tw2i(r.tw2_inv);
+  for (int k = 0; k < r.H; ++k) {
+    const double a = 2.0 * kPi * k / r.H;
     tw2i[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
+    if (r.tw2_fwd) tw2f[k] = make_float2(float(std::cos(a)), float(-std::sin(a)));
   }
 
-  // (one view's row spectra at least: more than the stacks only of a single 16-bit plane)
-  pl->stack_bytes = std::max(size_t(r.batch) * stack_view_bytes(r.M, r.K, p->plane_dtype),
-                             tomo::spectra_scratch_bytes(r.M));
+  pl->stack_bytes = r.stack_bytes;
   hipError_t e = hipSuccess;
   const size_t mm = size_t(r.M) * r.M;
   if ((e = dev_alloc(&pl->d_geom, size_t(r.n))) != hipSuccess ||
       (e = dev_alloc(&pl->d_filt, mm * r.n)) != hipSuccess ||
       (e = dev_alloc(&pl->d_prop, prop.size())) != hipSuccess ||
       (e = dev_alloc(&pl->d_tw_inv, size_t(r.M))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw64, size_t(r.M))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw_fwd, size_t(r.M))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw2_fwd, size_t(hpts))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_tw2_inv, size_t(hpts))) != hipSuccess ||
-      (e = dev_alloc(&pl->d_l1, size_t(std::max(tomo::spectra_groups(r.M), pl->split * pl->split)) * r.n)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw64, r.tw64)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw_fwd, r.tw_fwd)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw2_fwd, r.tw2_fwd)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_tw2_inv, r.tw2_inv)) != hipSuccess ||
+      (e = dev_alloc(&pl->d_l1, r.l1)) != hipSuccess ||
       (e = dev_alloc(&pl->d_q, mm * r.n)) != hipSuccess ||
       (e = dev_alloc(reinterpret_cast<char**>(&pl->d_stack), pl->stack_bytes)) != hipSuccess ||
       (e = dev_alloc(&pl->d_scale, size_t(r.n))) != hipSuccess ||
@@ -505,13 +530,13 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
     return perr(err == hipErrorOutOfMemory ? TOMO_ENOMEM : TOMO_EDEVICE,
                 std::string(where) + ": " + hipGetErrorString(err));
   };
-  if ((e = hipMemcpyAsync(pl->d_geom, geo.data(), sizeof(ViewGeom) * r.n, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_prop, prop.data(), sizeof(float2) * prop.size(), hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw64, tw64.data(), sizeof(double2) * r.M, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw_fwd, twf.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw2_fwd, tw2f.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw_inv, twi.data(), sizeof(float2) * r.M, hipMemcpyHostToDevice, s)) ||
-      (e = hipMemcpyAsync(pl->d_tw2_inv, tw2i.data(), sizeof(float2) * hpts, hipMemcpyHostToDevice, s)))
+  auto upload = [&](void* to, const auto& from) {
+    if (from.empty()) return hipSuccess;
+    return hipMemcpyAsync(to, from.data(), from.size() * sizeof(from[0]), hipMemcpyHostToDevice, s);
+  };
+  if ((e = upload(pl->d_geom, geo)) || (e = upload(pl->d_prop, prop)) || (e = upload(pl->d_tw64, tw64)) ||
+      (e = upload(pl->d_tw_fwd, twf)) || (e = upload(pl->d_tw2_fwd, tw2f)) || (e = upload(pl->d_tw_inv, twi)) ||
+      (e = upload(pl->d_tw2_inv, tw2i)))
     return cleanup_fail(e, "upload");
   *pl->status = 0;
 
@@ -690,19 +715,17 @@ static tomo_status check_range(tomo_plan_t pl, int32_t first, int32_t nb) {
   return TOMO_OK;
 }
 
-// Filtered spectra of views [first, first + nb) into q: transformed in FP64 by two kernels, in FP32 by one
-// where the planes are stored in 16 bits (see k_spectra) and below M = 48, where a call of few views costs its
-// launches (8 views at a time, 160 in all: 24^2 375 us with one kernel, 451 with two; 36^2 434 / 440;
-// 48^2 475 / 470; 64^2 638 / 553).
+// Filtered spectra of views [first, first + nb) into q.
 static hipError_t enqueue_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, float4* q, hipStream_t s) {
   const float4* filt = pl->d_filt + size_t(first) * pl->M * pl->M;
   const double inv_iin = 1.0 / pl->p.i_in;
-  if (pl->p.plane_dtype == TOMO_F32 && pl->M >= 48)
+  if (pl->spectra64)
     return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, filt, q, pl->status, inv_iin, nb, s, pl->d_stack,
                                 pl->stack_bytes);
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
-  return tomo::launch_spectra32(pl->M, d_images, filt, pl->d_tw_fwd, pl->d_tw2_fwd, q, pl->status, inv_iin, scale,
-                                pl->d_l1 + size_t(pl->split * pl->split) * first, nb, s);
+  float* l1 = scale ? pl->d_l1 + size_t(pl->split * pl->split) * first : nullptr;
+  return tomo::launch_spectra32(pl->M, d_images, filt, pl->d_tw_fwd, pl->d_tw2_fwd, q, pl->status, inv_iin, scale, l1,
+                                nb, s);
 }
 
 // Spectra of views [first, first+nb) into the plan's per-view slots of d_q.

@@ -1,0 +1,51 @@
+"""tomo_workspace_bytes (what max_workspace_bytes is compared with) against the sum of the arrays that
+a plan keeps on the device, listed here one by one."""
+import itertools
+
+import pytest
+
+tomo = pytest.importorskip("paper_2206_09151_amd.tomo")
+
+# sizes of a direct, an odd, a row-split and a block-split plane transform: M, P
+DETECTORS = [(32, 1), (45, 1), (75, 1), (128, 1), (192, 1), (200, 2), (243, 3), (256, 2)]
+
+
+def _params(m, n, **kw):
+    return tomo.Params(n_vox=m, n_angles=n, voxel_size=1e-6, wavelength=1e-10, sigma=0.0, epsilon=1e-3, **kw)
+
+
+def _row_spectra(m):
+    return 8 * m * ((m + 1) // 2)
+
+
+def _arrays(m, p, n, k, batch, dtype, auto, fourier):
+    """Bytes of every device array of a plan with M = N = m, without those of the Fourier form's
+    operator and with one view's row spectra at the least."""
+    es, f32 = (4, True) if dtype == 0 else (2, False)
+    h = m // p if p > 1 else 0
+    two_kernels = f32 and m >= 48
+    slices = f32 and auto and k == m and m <= 192
+    a = {"geometry": 88 + 8, "filter": 16 * m * m, "spectra": 16 * m * m, "scale": 4}
+    a = {key: v * n for key, v in a.items()}
+    a["propagator"] = 8 * ((k + 1) // 2) * m
+    a["inverse twiddles"] = 8 * m + 8 * h
+    a["forward twiddles, FP32"] = 0 if two_kernels else 8 * m + 8 * h
+    a["forward twiddles, FP64"] = 16 * m if two_kernels or slices or fourier else 0
+    a["bounds"] = 4 * n * max(p * p if dtype == 2 else 0, (m // 2 + 16) // 16 if fourier == 2 else 0)
+    a["stacks"] = max(batch * m * k * m * es, _row_spectra(m) if two_kernels or fourier else 0)
+    if fourier:
+        e = m + 1 - m % 2
+        a["Fourier"] = n * (8 * m * m + 4) + 16 + m ** 3 * 16 + 8 * m + (16 * e ** 3 if fourier == 2 else 0)
+    return a
+
+
+@pytest.mark.parametrize("m,p", DETECTORS)
+def test_workspace_bytes_is_the_sum_of_the_arrays(m, p):
+    for dtype, ewald, batch, fourier in itertools.product((0, 1, 2), (1, 0), (1, 3), (0, 2)):
+        n, k = 5, m if ewald else 1
+        got = tomo.workspace_bytes(_params(m, n, plane_dtype=dtype, ewald=ewald, angle_batch=batch, fourier=fourier))
+        assert got == sum(_arrays(m, p, n, k, batch, dtype, False, fourier).values()), (dtype, ewald, batch, fourier)
+
+
+def test_automatic_batch_of_a_slice_sized_plan_counts_its_twiddles():
+    assert tomo.workspace_bytes(_params(32, 5)) == sum(_arrays(32, 1, 5, 32, 5, 0, True, 0).values())
