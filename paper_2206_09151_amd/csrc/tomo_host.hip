@@ -37,6 +37,7 @@ struct tomo_plan_s {
   float* d_l1 = nullptr;        // [n][spectra_groups or P^2] parts of the views' spectral bounds (FP16, fourier = 2)
   float4* d_q = nullptr;        // [n][M][M]  filtered spectra of every view
   void* d_stack = nullptr;      // [batch][M][K][M] of the plane storage type; before its planes, row spectra
+                                // (of all views where the workspace limit allows); slices: partial volumes
   size_t stack_bytes = 0;
   float* d_scale = nullptr;     // [n] FP16 plane scale per view (powers of two)
   int* status = nullptr;                // pinned host word that kernels set on a bad image value: read
@@ -158,12 +159,17 @@ std::string resolve(const tomo_params* p, Resolved* r) {
   r->tw2_inv = size_t(r->H);
   r->l1 = std::max(p->plane_dtype == TOMO_F16 ? size_t(r->split * r->split) : 0,
                    p->fourier == 2 ? size_t(tomo::spectra_groups(r->M)) : 0) * r->n;
-  // (one view's row spectra at least: more than the stacks only of a single plane)
-  r->stack_bytes = std::max(size_t(r->batch) * sv, rows ? tomo::spectra_scratch_bytes(r->M) : 0);
+  // Row spectra of all views, so that any call's spectra take one launch of each kernel, whatever the batch
+  // (60 views of 128^2, one plane each, in batches of one: 2093 us with a pair of launches per view): more
+  // than the stacks only of few planes or small batches.  A limit that does not allow that much gets
+  // as many views as fit, one at the least.
+  const size_t row_bytes = rows ? tomo::spectra_scratch_bytes(r->M) : 0;
+  const size_t least = std::max(size_t(r->batch) * sv, row_bytes);
+  r->stack_bytes = std::max(least, size_t(r->n) * row_bytes);
   r->table_bytes = size_t(r->n) * (sizeof(ViewGeom) + qv) +
                    (size_t(r->npairs) * r->M + r->M + r->tw_fwd + r->tw2_fwd + r->tw2_inv) * sizeof(float2) +
                    r->tw64 * sizeof(double2) + (r->l1 + r->n) * sizeof(float);
-  r->work_bytes = size_t(r->n) * qv + r->stack_bytes;
+  r->work_bytes = size_t(r->n) * qv;
   r->P = r->N + (r->N % 2 == 0 ? 1 : 0);
   if (p->fourier) {
     const size_t n3 = size_t(r->N) * r->N * r->N, p3 = size_t(r->P) * r->P * r->P;
@@ -177,6 +183,12 @@ std::string resolve(const tomo_params* p, Resolved* r) {
       r->table_bytes += (p3 + 1) * 4 + size_t(r->n) * r->M * r->M * 8 * 8;
     }
   }
+  if (p->max_workspace_bytes) {
+    const size_t others = r->table_bytes + r->work_bytes;
+    const size_t left = p->max_workspace_bytes > others ? p->max_workspace_bytes - others : 0;
+    r->stack_bytes = std::max(least, std::min(r->stack_bytes, left));
+  }
+  r->work_bytes += r->stack_bytes;
   return "";
 }
 

@@ -1,4 +1,6 @@
 """The two-kernel spectra (FP32 planes, slices, Fourier form) at the edges of their ranges."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -31,3 +33,31 @@ def test_contrast_beyond_fp64_shows_in_the_volume(m, kw, value, i_in):
     ball = torch.from_numpy(r[:, None, None] ** 2 + r[:, None] ** 2 + r ** 2 < (m / 2 - 2) ** 2)
     assert not torch.isfinite(vol.cpu()[ball]).any()
     plan.destroy()
+
+
+@pytest.mark.parametrize("m,kw", [(75, {"ewald": 0}), (125, {"ewald": 0}), (128, {"ewald": 0}), (48, {"n_planes": 4}),
+                                  (256, {"n_planes": 2}), (45, {"fourier": 1}), (36, {"fourier": 2})])
+def test_row_spectra_in_several_rounds_are_bitwise_those_of_one(m, kw):
+    """A workspace limit with room for one, two or four of nine views' row spectra (one plane of odd M
+    has room for less than one view in its stack): ragged rounds, the same bits."""
+    from paper_2206_09151_amd import tomo
+    base = dict(angle_batch=1, **kw)
+    img = torch.rand((9, m, m), generator=torch.Generator().manual_seed(m)).to("cuda:0") + 0.5
+    row = 8 * m * ((m + 1) // 2)
+    plan = _plan(m, 9, **base)
+    full = tomo.workspace_bytes(plan.params)
+    least = tomo.workspace_bytes(replace(plan.params, max_workspace_bytes=1))
+    vols = []
+    for rounds_of in (9, 4, 2, 1):
+        if rounds_of < 9:
+            plan = _plan(m, 9, max_workspace_bytes=max(full - (9 - rounds_of) * row, least), **base)
+        vol = torch.zeros((m,) * 3, dtype=torch.float32, device="cuda:0")
+        if "fourier" in kw:
+            plan.fourier_reconstruct(img, vol)
+        else:
+            plan.reconstruct(img, vol)
+        vols.append(vol.cpu())
+        plan.destroy()
+    assert torch.isfinite(vols[0]).all() and vols[0].abs().max() > 0
+    for v in vols[1:]:
+        assert torch.equal(v, vols[0])

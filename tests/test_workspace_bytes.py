@@ -20,7 +20,7 @@ def _row_spectra(m):
 
 def _arrays(m, p, n, k, batch, dtype, auto, fourier):
     """Bytes of every device array of a plan with M = N = m, without those of the Fourier form's
-    operator and with one view's row spectra at the least."""
+    operator."""
     es, f32 = (4, True) if dtype == 0 else (2, False)
     h = m // p if p > 1 else 0
     two_kernels = f32 and m >= 48
@@ -32,7 +32,7 @@ def _arrays(m, p, n, k, batch, dtype, auto, fourier):
     a["forward twiddles, FP32"] = 0 if two_kernels else 8 * m + 8 * h
     a["forward twiddles, FP64"] = 16 * m if two_kernels or slices or fourier else 0
     a["bounds"] = 4 * n * max(p * p if dtype == 2 else 0, (m // 2 + 16) // 16 if fourier == 2 else 0)
-    a["stacks"] = max(batch * m * k * m * es, _row_spectra(m) if two_kernels or fourier else 0)
+    a["stacks or row spectra"] = max(batch * m * k * m * es, n * _row_spectra(m) if two_kernels or fourier else 0)
     if fourier:
         e = m + 1 - m % 2
         a["Fourier"] = n * (8 * m * m + 4) + 16 + m ** 3 * 16 + 8 * m + (16 * e ** 3 if fourier == 2 else 0)
@@ -49,3 +49,13 @@ def test_workspace_bytes_is_the_sum_of_the_arrays(m, p):
 
 def test_automatic_batch_of_a_slice_sized_plan_counts_its_twiddles():
     assert tomo.workspace_bytes(_params(32, 5)) == sum(_arrays(32, 1, 5, 32, 5, 0, True, 0).values())
+
+
+@pytest.mark.parametrize("m", [75, 128])
+def test_row_spectra_give_way_to_a_workspace_limit(m):
+    """One plane per view in batches of one: all views' row spectra, as many as a limit leaves room
+    for, and one view's at the least."""
+    kw = dict(ewald=0, angle_batch=1)
+    full, one = tomo.workspace_bytes(_params(m, 9, **kw)), _row_spectra(m)
+    assert tomo.workspace_bytes(_params(m, 9, max_workspace_bytes=full - 4 * one, **kw)) == full - 4 * one
+    assert tomo.workspace_bytes(_params(m, 9, max_workspace_bytes=full - 20 * one, **kw)) == full - 8 * one
