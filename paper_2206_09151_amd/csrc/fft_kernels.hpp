@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "fft.hpp"
+#include "geom.hpp"
 #include "spectra_kernels.hpp"
 
 namespace tomo {

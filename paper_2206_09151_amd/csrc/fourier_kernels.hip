@@ -8,9 +8,8 @@
 //                kernel: (H_n(q) s(k), 0) for eq. 11 or (s(k), 0) for eq. 12, where
 //                s(k) = exp(i pi (M-1)(kx+ky)/M) moves the DFT phase origin to the
 //                detector centre (M-1)/2.  FP64, stored FP32.
-//   k_fbound     fixed-point unit 2^-e of the accumulator from the per-view spectral
-//                bounds: every vertex sum stays below 2^62 in magnitude.
-//   k_fclear     zero the accumulator.
+//   k_fclear     zero the accumulator, and its fixed-point unit 2^-e from the per-view
+//                spectral bounds: every vertex sum stays below 2^62 in magnitude.
 //   k_fsplat     every (view, ky, kx) value to the 8 vertices around its paraboloid
 //                point p (trilinear weights, text after eq. 11) as 64-bit fixed-point
 //                integer atomics: integer addition is order independent, so the sums
@@ -68,23 +67,36 @@ __global__ void k_ffilter(FilterArgs fa, const ViewGeom* __restrict__ geom, int 
   filt[i] = make_float2(float(fr), float(fi));
 }
 
-// ------------------------------------------------------------------ accumulator scale
-// view_scale[v] = 2^14 / (power of two >= the view's sum of |Re| + |Im|), from the spectra kernel.
-// A vertex sum is bounded by the sum over all samples of |Re| + |Im| (weights of one
-// sample add up to one), so B = sum_v 2^14 / view_scale[v] bounds it; the unit puts B
-// at 2^62.  Sequential FP64 sum: fixed order.
-__global__ void k_fbound(const float* __restrict__ view_scale, int n, double* __restrict__ fix) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// ------------------------------------------------------------------ accumulator
+// Clears the accumulator and, in its first workgroup, forms the fixed-point unit out of the views'
+// spectral bounds: l1[v][groups] are parts of view v's sum of |Re| + |Im| (k_cols_fwd).  A vertex
+// sum is bounded by the sum over all samples of |Re| + |Im| (weights of one sample add up to
+// one); with every view's sum rounded up to a power of two (2^14 over the view's FP16 scale) their
+// sum B bounds it, and the unit puts B at 2^62.  Sequential FP64 sum: fixed order.  One launch: per-view
+// scales, bound and clearing by three cost 5 us of small calls (16^3: 33.5 us).
+__global__ __launch_bounds__(256) void k_fclear(ulonglong2* __restrict__ acc, size_t count, const float* __restrict__ l1,
+                                                int groups, int n, double* __restrict__ fix) {
+  const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i < count) acc[i] = make_ulonglong2(0ull, 0ull);
+  if (blockIdx.x != 0) return;
+  __shared__ double bound[256];
   double b = 0.0;
-  for (int v = 0; v < n; ++v) b += 16384.0 / double(view_scale[v]);
+  for (int v0 = 0; v0 < n; v0 += 256) {
+    const int v = v0 + int(threadIdx.x);
+    if (v < n) {
+      float tot = 0.0f;
+      for (int g = 0; g < groups; ++g) tot += l1[groups * v + g];
+      bound[threadIdx.x] = 16384.0 / double(fp16_scale(tot));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int k = 0; k < min(256, n - v0); ++k) b += bound[k];
+    __syncthreads();
+  }
+  if (threadIdx.x != 0) return;
   const double e = b > 0.0 ? 62.0 - ceil(log2(b)) : 0.0;
   fix[0] = exp2(e);
   fix[1] = exp2(-e);
-}
-
-__global__ void k_fclear(ulonglong2* __restrict__ acc, size_t count) {
-  const size_t i = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < count) acc[i] = make_ulonglong2(0ull, 0ull);
 }
 
 // ------------------------------------------------------------------ splat
@@ -500,15 +512,13 @@ hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int
   return hipGetLastError();
 }
 
-hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* view_scale,
+hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* l1,
                                 double* fix, unsigned long long* acc, int P, hipStream_t s) {
-  hipLaunchKernelGGL(k_fbound, dim3(1), dim3(64), 0, s, view_scale, fa.n_views, fix);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const size_t cells = size_t(P) * P * P;
   hipLaunchKernelGGL(k_fclear, dim3(unsigned((cells + 255) / 256)), dim3(256), 0, s,
-                     reinterpret_cast<ulonglong2*>(acc), cells);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+                     reinterpret_cast<ulonglong2*>(acc), cells, l1, spectra_groups(fa.M), fa.n_views, fix);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   const size_t total = size_t(fa.M) * fa.M * fa.n_views;
   hipLaunchKernelGGL(k_fsplat, dim3(unsigned((total + 255) / 256)), dim3(256), 0, s, fa, geom, q, fix, acc, P);
   return hipGetLastError();

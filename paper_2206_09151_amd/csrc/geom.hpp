@@ -1,4 +1,4 @@
-// Frequency-grid geometry shared by the plan-time tables and the Fourier-space kernels.
+// Frequency-grid geometry and scales shared by the plan-time tables, the spectra and the Fourier-space kernels.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -24,6 +24,9 @@ __device__ __forceinline__ void sample_point(const FilterArgs& fa, const ViewGeo
 #pragma unroll
   for (int a = 0; a < 3; ++a) p[a] = (qx * g.u[a] + qy * g.v[a] + qz * g.d[a]) * sc;
 }
+
+// FP16 plane scale: the power of two that puts a view's spectral bound at 2^14.
+__device__ __forceinline__ float fp16_scale(float l1) { return l1 > 0.0f ? exp2f(14.0f - ceilf(log2f(l1))) : 1.0f; }
 
 // Sampling matrix fixed point: 2^-32 units.
 constexpr double kFix = 4294967296.0;

@@ -232,8 +232,7 @@ __device__ __forceinline__ float4 q_filtered(float4 f, double2 g) {
 //   kSlices  q[2 r + c][kx <= M/2], r <= M/2: the even (c = 0) and odd (c = 1) part of the rows +-r,
 //            (Q(r) + Q(-r)) / 2 and (Q(r) - Q(-r)) / 2i; pair r = 0 holds rows 0 and (even M) M/2.
 //   kRows    q[ky][kx], ky <= M/2.
-// l1 (kFull, kComplex; or NULL): [view][G] sums of the output's magnitudes (fixed order), from which
-// k_plane_scale forms a view's power-of-two scale.
+// l1 (kFull, kComplex; or NULL): [view][G] sums of the output's magnitudes (fixed order).
 enum ColsOut { kFull, kComplex, kSlices, kRows };
 template <ColsOut OUT>
 using QValue = std::conditional_t<OUT == kComplex, float2, float4>;
@@ -347,23 +346,8 @@ __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __re
   }
 }
 
-// FP16 plane scale: the power of two that puts a view's spectral bound at 2^14.
-__device__ __forceinline__ float fp16_scale(float l1) { return l1 > 0.0f ? exp2f(14.0f - ceilf(log2f(l1))) : 1.0f; }
-
-// Every plane value of a view is bounded by sum_k |cos Q1 + sin Q2| <= sum_k (|Q1| + |Q2|): scale by
-// the power of two that puts this bound at 2^14 (exact scaling, below the FP16 maximum).
-template <int G>
-__global__ void k_plane_scale(const float* __restrict__ l1, float* __restrict__ scale, int nb) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nb) return;
-  float tot = 0.0f;
-  for (int g = 0; g < G; ++g) tot += l1[G * v + g];
-  scale[v] = fp16_scale(tot);
-}
-
 // Spectra of nb views.  z: the row pairs' spectra, room for `room` views of (M + 1) / 2 M float2 (the
-// views are taken in turns of that many).  scale (kFull, kComplex; or NULL): per-view power-of-two
-// scale out, with l1 [nb][G].
+// views are taken in turns of that many).  l1 (or NULL): [nb][G] out.
 struct SpectraLaunch {
   const float* images;
   const double2* tw;       // [M] exp(-i 2 pi k / M)
@@ -373,7 +357,6 @@ struct SpectraLaunch {
   size_t room;
   int* status;
   double inv_iin;
-  float* scale;
   float* l1;
   int nb;
   hipStream_t s;
@@ -393,12 +376,10 @@ hipError_t half_spectra(const SpectraLaunch& a) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_cols_fwd<M, OUT>), view_parts<S::G>(nb), dim3(S::CT), 0, a.s, a.z, a.tw,
                        static_cast<const QValue<OUT>*>(a.filt) + size_t(v) * M * M,
-                       static_cast<QValue<OUT>*>(a.q) + size_t(v) * per, a.scale ? a.l1 + size_t(v) * S::G : nullptr, nb);
+                       static_cast<QValue<OUT>*>(a.q) + size_t(v) * per, a.l1 ? a.l1 + size_t(v) * S::G : nullptr, nb);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  if (!a.scale) return hipSuccess;
-  hipLaunchKernelGGL(k_plane_scale<S::G>, dim3(unsigned(a.nb + 255) / 256), dim3(256), 0, a.s, a.l1, a.scale, a.nb);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace tomo

@@ -46,7 +46,6 @@ struct tomo_plan_s {
   int P = 0;                            // vertex-grid edge: N + 1 for even N, N for odd N
   float2* d_ffilt = nullptr;            // [n][M][M] filter of the Fourier-space variant built last
   int ffilt_variant = 0;                // 11, 12, or 0 before the first call
-  float* d_fview = nullptr;             // [n] per-view spectral bound (power-of-two scale)
   double* d_ffix = nullptr;             // [2] fixed-point unit and its inverse
   unsigned long long* d_facc = nullptr; // [P][P][P][2] fixed-point accumulator
   unsigned long long* d_fsmat = nullptr;// [N][N][N] sampling matrix, 2^-32 units
@@ -173,7 +172,7 @@ std::string resolve(const tomo_params* p, Resolved* r) {
   r->P = r->N + (r->N % 2 == 0 ? 1 : 0);
   if (p->fourier) {
     const size_t n3 = size_t(r->N) * r->N * r->N, p3 = size_t(r->P) * r->P * r->P;
-    r->table_bytes += size_t(r->n) * qv / 2 + n3 * 8 + size_t(r->N) * 8 + size_t(r->n) * 4 + 16;
+    r->table_bytes += size_t(r->n) * qv / 2 + n3 * 8 + size_t(r->N) * 8 + 16;
     r->work_bytes += n3 * 8;
     if (p->fourier == 2) {
       r->work_bytes += p3 * 16;
@@ -332,7 +331,6 @@ void free_plan(tomo_plan_s* pl) {
   (void)hipFree(pl->d_scale);
   (void)hipHostFree(pl->status);
   (void)hipFree(pl->d_ffilt);
-  (void)hipFree(pl->d_fview);
   (void)hipFree(pl->d_ffix);
   (void)hipFree(pl->d_facc);
   (void)hipFree(pl->d_fsmat);
@@ -581,8 +579,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
       const double a = 2.0 * kPi * k / r.N;
       tw3[k] = make_float2(float(std::cos(a)), float(std::sin(a)));
     }
-    if ((e = dev_alloc(&pl->d_ffilt, mm * r.n)) != hipSuccess || (e = dev_alloc(&pl->d_fview, size_t(r.n))) ||
-        (e = dev_alloc(&pl->d_ffix, size_t(2))) || (p->fourier == 2 && (e = dev_alloc(&pl->d_facc, 2 * p3))) ||
+    if ((e = dev_alloc(&pl->d_ffilt, mm * r.n)) != hipSuccess || (e = dev_alloc(&pl->d_ffix, size_t(2))) ||
+        (p->fourier == 2 && (e = dev_alloc(&pl->d_facc, 2 * p3))) ||
         (e = dev_alloc(&pl->d_fsmat, n3)) || (e = dev_alloc(&pl->d_fgrid, n3)) ||
         (e = dev_alloc(&pl->d_tw3, size_t(r.N))))
       return cleanup_fail(e, "Fourier-space workspace allocation");
@@ -976,9 +974,8 @@ static tomo_status enqueue_fourier(tomo_plan_t pl, const float* d_images, int32_
   }
   e = timed(pl, 0, s, [&] {
     return tomo::launch_spectra_complex(pl->M, d_images, pl->d_tw64, pl->d_ffilt, reinterpret_cast<float2*>(pl->d_q),
-                                        pl->status, 1.0 / pl->p.i_in,
-                                        pl->p.fourier == 2 ? pl->d_fview : nullptr, pl->n, s, pl->d_stack,
-                                        pl->stack_bytes, pl->d_l1);
+                                        pl->status, 1.0 / pl->p.i_in, pl->n, s, pl->d_stack, pl->stack_bytes,
+                                        pl->p.fourier == 2 ? pl->d_l1 : nullptr);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   tomo::FourierNormArgs na{};
@@ -1004,8 +1001,8 @@ static tomo_status enqueue_fourier(tomo_plan_t pl, const float* d_images, int32_
     if (e != hipSuccess) return dev_fail(pl, e, "Fourier gridding-operator kernel");
   } else {
     e = timed(pl, 3, s, [&] {
-      return tomo::launch_fourier_splat(fa, pl->d_geom, reinterpret_cast<const float2*>(pl->d_q), pl->d_fview,
-                                         pl->d_ffix, pl->d_facc, pl->P, s);
+      return tomo::launch_fourier_splat(fa, pl->d_geom, reinterpret_cast<const float2*>(pl->d_q), pl->d_l1, pl->d_ffix,
+                                        pl->d_facc, pl->P, s);
     });
     if (e != hipSuccess) return dev_fail(pl, e, "Fourier splat kernels");
     e = timed(pl, 4, s, [&] {

@@ -36,9 +36,9 @@ hipError_t launch_spectra(int M, const float* images, const double2* tw, const f
 // scale (FP16 planes only, else NULL): per-view power-of-two plane scale, [nb], with l1part [nb][P^2].
 hipError_t launch_spectra32(int M, const float* images, const float4* filt, const float2* tw_fwd, const float2* tw_half_fwd,
                             float4* q, int* status, double inv_iin, float* scale, float* l1part, int nb, hipStream_t s);
+// l1 (or NULL): [nb][spectra_groups(M)] parts of every view's sum of |Re q| + |Im q|.
 hipError_t launch_spectra_complex(int M, const float* images, const double2* tw, const float2* filt, float2* q, int* status,
-                                  double inv_iin, float* scale, int nb, hipStream_t s, void* scratch,
-                                  size_t scratch_bytes, float* l1);
+                                  double inv_iin, int nb, hipStream_t s, void* scratch, size_t scratch_bytes, float* l1);
 // Plane pairs (p, K-1-p), p < npairs, of nb views -> stack [nb][M][K][M] of dtype
 // (0 FP32, 1 BF16, 2 FP16 scaled by scale[view]).
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -86,8 +86,8 @@ bool fourier_grid_supported(int N);
 // filt [n][M][M]: H_n s (eq. 11) or s (eq. 12), s = centring phase of the DFT.
 hipError_t launch_fourier_filter(const FilterArgs& fa, const ViewGeom* geom, int eq12, float2* filt,
                                  hipStream_t s);
-// Fixed-point unit from view_scale [n] into fix[2], clear acc [P^3][2], splat q [n][M][M].
-hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* view_scale,
+// Fixed-point unit from l1 [n][spectra_groups(M)] into fix[2], clear acc [P^3][2], splat q [n][M][M].
+hipError_t launch_fourier_splat(const FilterArgs& fa, const ViewGeom* geom, const float2* q, const float* l1,
                                 double* fix, unsigned long long* acc, int P, hipStream_t s);
 // Hermitian fold + normalisation of the accumulator into grid [N^3] (FFT order).
 hipError_t launch_fourier_norm(const FourierNormArgs& a, const unsigned long long* acc, const unsigned long long* smat,

@@ -1609,7 +1609,7 @@ hipError_t launch_spectra(int M, const float* images, const double2* tw, const f
   const FftSize* f = fft_size(M);
   if (!f) return hipErrorInvalidValue;
   return f->spectra(SpectraLaunch{images, tw, filt, q, static_cast<float2*>(scratch),
-                                  scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, nullptr, nullptr, nb, s});
+                                  scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, nullptr, nb, s});
 }
 
 hipError_t launch_spectra32(int M, const float* images, const float4* filt, const float2* tw_fwd, const float2* tw_half_fwd,
@@ -1621,14 +1621,12 @@ hipError_t launch_spectra32(int M, const float* images, const float4* filt, cons
 }
 
 hipError_t launch_spectra_complex(int M, const float* images, const double2* tw, const float2* filt, float2* q, int* status,
-                                  double inv_iin, float* scale, int nb, hipStream_t s, void* scratch,
-                                  size_t scratch_bytes, float* l1) {
+                                  double inv_iin, int nb, hipStream_t s, void* scratch, size_t scratch_bytes, float* l1) {
   if (nb <= 0) return hipSuccess;
   const FftSize* f = fft_size(M);
   if (!f) return hipErrorInvalidValue;
   return f->spectra_complex(SpectraLaunch{images, tw, filt, q, static_cast<float2*>(scratch),
-                                          scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, scale, l1, nb,
-                                          s});
+                                          scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, l1, nb, s});
 }
 
 hipError_t launch_planes(int M, int dtype, const float4* q, const float2* prop, const float2* tw_inv,
@@ -1823,7 +1821,7 @@ hipError_t launch_axis_spectra(int M, const float* images, const double2* tw, co
   // the row pairs' spectra (4 M (M + 1) bytes at most) at their end
   const size_t mm = size_t(M) * M, pairs = size_t((M + 1) / 2) * M;
   float2* z = reinterpret_cast<float2*>(work + size_t(nb) * mm) - size_t(nb) * pairs;
-  return a->spectra(SpectraLaunch{images, tw, filt, work, z, size_t(nb), status, inv_iin, nullptr, nullptr, nb, s});
+  return a->spectra(SpectraLaunch{images, tw, filt, work, z, size_t(nb), status, inv_iin, nullptr, nb, s});
 }
 
 hipError_t launch_axis_slices(int M, const float4* work, const float2* prop, const float2* tw_inv,

@@ -61,3 +61,21 @@ def test_row_spectra_in_several_rounds_are_bitwise_those_of_one(m, kw):
     assert torch.isfinite(vols[0]).all() and vols[0].abs().max() > 0
     for v in vols[1:]:
         assert torch.equal(v, vols[0])
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 300])
+def test_splat_bound_over_many_views(n):
+    """The splat's fixed-point unit comes from the views' bounds, 256 at a time: the volume of the atomic
+    splat against that of the operator gather (FP32 bar, 1e-5), with one view a thousand times brighter
+    last, so that a bound that left it out would overflow the accumulator."""
+    img = torch.rand((n, 16, 16), generator=torch.Generator().manual_seed(n)) + 0.5
+    img[-1] = torch.exp(1000.0 * torch.log(img[-1]).clamp(-0.08, 0.08))
+    img = img.to("cuda:0")
+    vols = []
+    for mode in (1, 2):
+        plan = _plan(16, n, fourier=mode)
+        vol = torch.zeros((16,) * 3, dtype=torch.float32, device="cuda:0")
+        plan.fourier_reconstruct(img, vol)
+        vols.append(vol.double().cpu())
+        plan.destroy()
+    assert torch.linalg.norm(vols[1] - vols[0]) <= 1e-5 * torch.linalg.norm(vols[0])

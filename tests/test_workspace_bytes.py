@@ -35,7 +35,7 @@ def _arrays(m, p, n, k, batch, dtype, auto, fourier):
     a["stacks or row spectra"] = max(batch * m * k * m * es, n * _row_spectra(m) if two_kernels or fourier else 0)
     if fourier:
         e = m + 1 - m % 2
-        a["Fourier"] = n * (8 * m * m + 4) + 16 + m ** 3 * 16 + 8 * m + (16 * e ** 3 if fourier == 2 else 0)
+        a["Fourier"] = n * 8 * m * m + 16 + m ** 3 * 16 + 8 * m + (16 * e ** 3 if fourier == 2 else 0)
     return a
 
 
