@@ -1702,10 +1702,12 @@ static hipError_t grid_cube_impl(const InT* stack, const ViewGeom* geom, const f
   // views: 41 us, two groups 53, one 79), up to two per CU two do (64^3, 100 views: 106 us, one
   // group 134, four 136; 50^3, 60 views: 74, 97, 82); beyond that the tiles fill the chip by
   // themselves (72^3, 100 views: one group 164 us, two 184).
+  // But no group without a view: its waves only delay the others' barriers (16^3, one view per
+  // launch: 9.4 us with four groups).  The sums are those of four or two groups, bit for bit.
   using std::integral_constant;
   auto pick = [&](auto ch) {
-    if (tiles <= 256) return go(ch, integral_constant<int, 4>{});
-    if (tiles <= 512) return go(ch, integral_constant<int, 2>{});
+    if (tiles <= 256 && nb > 2) return go(ch, integral_constant<int, 4>{});
+    if (tiles <= 512 && nb > 1) return go(ch, integral_constant<int, 2>{});
     return go(ch, integral_constant<int, 1>{});
   };
   // rows of whole 16-byte chunks take the wide fetch (96^3, 120 views: 384 us, by dwords 432)
