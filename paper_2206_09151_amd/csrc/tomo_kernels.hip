@@ -1800,11 +1800,14 @@ int axis_blocks(int M, int n, int cus) {
   // (and about two views' time of set-up); every block adds a partial volume to sum, a fifth of a
   // view's time.  Measured: 128^3 from 180 views takes 337 us with the 4 blocks of this rule (512
   // workgroups), 406 with 2 and 445 with 3; 64^3 from 90 views 36 + 6.6 us (slices + columns) with
-  // its 16, 49 + 5.4 with 8 and 35 + 8.0 with 24.  At least three views per block.
+  // its 16, 49 + 5.4 with 8 and 35 + 8.0 with 24.  At least three views per block, but down to single views
+  // where the workgroups leave CUs free (four views: 36^3 22.9 -> 16.8 us, 64^3 31.2 -> 22.9; with two
+  // workgroups per CU one-view blocks lose, 128^3 47.5 -> 53.4).
   const int slots = cus * std::max(1, std::min(2, 160 * 1024 / a->lds));
   int best = 1;
   double least = 0.0;
-  for (int b = 1; b <= std::max(1, n / 3); ++b) {
+  for (int b = 1; b <= n; ++b) {
+    if (b > std::max(1, n / 3) && 8 * a->units * b > 7 * cus) break;
     const int rounds = (a->units * b + slots - 1) / slots;
     const double cost = rounds * double((n + b - 1) / b + 2) + 0.2 * b;
     if (b == 1 || cost < least) {
