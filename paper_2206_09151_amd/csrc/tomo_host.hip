@@ -465,9 +465,9 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
   pl->axis_fast = axis && (p->plane_dtype == TOMO_F32 || r.M % 2 == 0 || !p->ewald);
   if (pl->axis_fast && p->ewald && r.M % vec != 0) pl->grid_rows = 4;   // the dword fetch has one shape
   // Whole reconstructions of single-axis scans run without plane stacks where a slice fits in
-  // LDS and the caller left the batch to the library (an explicit angle_batch asks for stacks
-  // of that many views).  The partial volumes live in the stack workspace: as many view blocks
-  // as it holds, none if it holds not even one.
+  // LDS, that is faster (axis_blocks) and the caller left the batch to the library (an explicit
+  // angle_batch asks for stacks of that many views).  The partial volumes live in the stack
+  // workspace: as many view blocks as it holds, none if it holds not even one.
   // 16-bit plans keep their stacks, and with them the rounding that they ask for.
   if (axis && p->ewald && p->angle_batch == 0 && p->plane_dtype == TOMO_F32 && tomo::axis_supported(r.M, r.N, r.K)) {
     int dev = 0, cus = 0;
@@ -476,8 +476,7 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
       cus = 256;
       (void)hipGetLastError();
     }
-    const size_t room = size_t(r.batch) * stack_view_bytes(r.M, r.K, p->plane_dtype) / tomo::axis_part_bytes(r.M, r.N);
-    pl->axis_blocks = int(std::min<size_t>(room, size_t(tomo::axis_blocks(r.M, r.n, cus))));
+    pl->axis_blocks = tomo::axis_blocks(r.M, r.N, r.K, r.n, cus, r.stack_bytes / tomo::axis_part_bytes(r.M, r.N));
   }
 
   // propagator table: (cos, sin)(pi lambda z'_p q^2), z'_p = (p - (K-1)/2) dx; twiddles

@@ -56,8 +56,9 @@ hipError_t launch_grid(bool axis_fast, int dtype, const void* stack, const ViewG
 // N <= M and K <= M, M - N and M - K even.  part: `blocks` partial volumes of axis_part_bytes each.
 bool axis_supported(int M, int N, int K);
 size_t axis_part_bytes(int M, int N);
-// Number of view blocks for n views on a device of `cus` compute units (at least 1).
-int axis_blocks(int M, int n, int cus);
+// Number of view blocks for n views on a device of `cus` compute units with room for `room` partial
+// volumes; 0 where plane stacks are faster.
+int axis_blocks(int M, int N, int K, int n, int cus, size_t room);
 // Filtered spectra of nb views into work (16 M^2 bytes per view), in the slices' layout.
 hipError_t launch_axis_spectra(int M, const float* images, const double2* tw, const float4* filt, float4* work, int* status,
                                double inv_iin, int nb, hipStream_t s);

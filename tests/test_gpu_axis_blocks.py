@@ -22,3 +22,23 @@ def test_view_blocks_match_oracle(m, n_vox, k, n):
     assert launches == 1
     ref = _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
     assert_close(got, ref, 1e-5, (m, n))
+
+
+@pytest.mark.parametrize("m,n_vox,k,n,slices", [
+    (16, 16, 16, 6, False), (16, 16, 16, 7, True), (36, 36, 36, 3, False), (36, 36, 36, 4, True),
+    (54, 54, 54, 1, False), (54, 54, 54, 2, True),                                         # the shortest scans
+    (32, 32, 2, 30, False), (32, 32, 4, 30, True), (64, 64, 8, 8, False),                  # room for few blocks
+    (160, 20, 20, 6, False), (160, 80, 80, 6, True), (192, 192, 24, 5, False), (192, 144, 144, 5, True)])
+def test_route_of_small_scans_and_volumes(m, n_vox, k, n, slices):
+    """Scans that plane stacks reconstruct faster take them: the volume is then bit for bit that of an
+    explicit batch of the same size; either route matches the oracle."""
+    from paper_2206_09151_amd import tomo
+    pb = _problem(m, n_vox, k, n)
+    plan = tomo.Plan(pb.params(), pb.dirs, pb.dist)
+    batch = plan.batch
+    plan.destroy()
+    got, stacks = _run(pb)[0], _run(pb, angle_batch=batch)[0]
+    assert np.array_equal(got, stacks) == (not slices)
+    ref = _oracle_par.reconstruct_views(pb.images.astype(np.float64), pb.dirs, pb.dist, pb.oracle_geometry())
+    assert_close(got, ref, 1e-5, (m, n))
+    assert_close(stacks, ref, 1e-5, (m, n))
