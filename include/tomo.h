@@ -139,7 +139,8 @@ tomo_status tomo_plan(const tomo_params* p, const double* dirs, const double* va
  * d_planes (device, [nb][M][K][M] of plane_dtype, fully overwritten).
  * d_images: device float32 [nb][M][M], the images of those views.  Asynchronous:
  * an invalid image value raises TOMO_EDOMAIN at the next tomo_sync/tomo_reconstruct.
- * Uses the plan's spectrum slots of those views (calls on one plan are serial). */
+ * Uses the plan's spectrum slots of those views and its stack workspace (calls on one plan
+ * are serial). */
 tomo_status tomo_backpropagate(tomo_plan_t plan, const float* d_images, int32_t first, int32_t nb,
                                void* d_planes, void* stream);
 
@@ -148,7 +149,9 @@ tomo_status tomo_backpropagate(tomo_plan_t plan, const float* d_images, int32_t 
  * kernels and the same output, bit for bit, but the filtered spectra of the nb views
  * (16 M^2 bytes per view) live in a static device workspace of
  * TOMO_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on (from the
- * first plan made there until the process ends) instead of the plan's workspace.  The call
+ * first plan made there until the process ends) instead of the plan's workspace.  (What they
+ * are formed from lies behind them, or in d_planes before the planes are written.)  Of the
+ * plan the call writes only the FP16 per-view scales and the domain-error flag.  The call
  * allocates no device or host memory on success: no hipMalloc, hipFree or allocating
  * library routine (plan timing is not recorded for it).  Arguments and layouts as
  * tomo_backpropagate; the plan (made beforehand) still provides its tables and the FP16

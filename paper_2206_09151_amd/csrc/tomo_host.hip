@@ -724,13 +724,14 @@ static tomo_status check_range(tomo_plan_t pl, int32_t first, int32_t nb) {
   return TOMO_OK;
 }
 
-// Filtered spectra of views [first, first + nb) into q.
-static hipError_t enqueue_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, float4* q, hipStream_t s) {
+// Filtered spectra of views [first, first + nb) into q; rows: row_bytes of scratch memory, room for one
+// view's row spectra at least (of no use to FP32 spectra).
+static hipError_t enqueue_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, float4* q, void* rows,
+                                  size_t row_bytes, hipStream_t s) {
   const float4* filt = pl->d_filt + size_t(first) * pl->M * pl->M;
   const double inv_iin = 1.0 / pl->p.i_in;
   if (pl->spectra64)
-    return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, filt, q, pl->status, inv_iin, nb, s, pl->d_stack,
-                                pl->stack_bytes);
+    return tomo::launch_spectra(pl->M, d_images, pl->d_tw64, filt, q, pl->status, inv_iin, nb, s, rows, row_bytes);
   float* scale = pl->p.plane_dtype == TOMO_F16 ? pl->d_scale + first : nullptr;
   float* l1 = scale ? pl->d_l1 + size_t(pl->split * pl->split) * first : nullptr;
   return tomo::launch_spectra32(pl->M, d_images, filt, pl->d_tw_fwd, pl->d_tw2_fwd, q, pl->status, inv_iin, scale, l1,
@@ -740,7 +741,8 @@ static hipError_t enqueue_spectra(tomo_plan_t pl, const float* d_images, int32_t
 // Spectra of views [first, first+nb) into the plan's per-view slots of d_q.
 static tomo_status run_spectra(tomo_plan_t pl, const float* d_images, int32_t first, int32_t nb, hipStream_t s) {
   hipError_t e = timed(pl, 0, s, [&] {
-    return enqueue_spectra(pl, d_images, first, nb, pl->d_q + size_t(first) * pl->M * pl->M, s);
+    return enqueue_spectra(pl, d_images, first, nb, pl->d_q + size_t(first) * pl->M * pl->M, pl->d_stack,
+                           pl->stack_bytes, s);
   });
   if (e != hipSuccess) return dev_fail(pl, e, "spectra kernel");
   return TOMO_OK;
@@ -797,7 +799,18 @@ tomo_status tomo_backpropagate_noalloc(tomo_plan_t pl, const float* d_images, in
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
   float4* q = static_cast<float4*>(pl->scratch);
-  hipError_t e = enqueue_spectra(pl, d_images, first, nb, q, s);
+  // row spectra: what the spectra leave of the workspace, or the planes where that holds more of the views
+  // (they are written afterwards).  One of the two holds a view: a single view leaves most of the
+  // workspace, and two or more views' planes hold one view's row spectra even of one plane each.
+  char* rows = reinterpret_cast<char*>(q + size_t(nb) * pl->M * pl->M);
+  size_t row_bytes = kScratchBytes - size_t(nb) * pl->M * pl->M * sizeof(float4);
+  const size_t planes = size_t(nb) * stack_view_bytes(pl->M, pl->K, pl->p.plane_dtype);
+  if (row_bytes < size_t(nb) * tomo::spectra_scratch_bytes(pl->M) && planes > row_bytes) {
+    const size_t skip = (16 - (reinterpret_cast<uintptr_t>(d_planes) & 15)) & 15;
+    rows = static_cast<char*>(d_planes) + skip;
+    row_bytes = planes - skip;
+  }
+  hipError_t e = enqueue_spectra(pl, d_images, first, nb, q, rows, row_bytes, s);
   if (e != hipSuccess) return fail_fixed(pl, TOMO_EDEVICE, "spectra kernel: ", hipGetErrorString(e));
   e = tomo::launch_planes(pl->M, pl->p.plane_dtype, q, pl->d_prop, pl->d_tw_inv, d_planes, pl->K, pl->npairs, nb,
                           pl->d_scale + first, s, pl->d_tw2_inv);

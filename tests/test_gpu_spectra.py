@@ -79,3 +79,41 @@ def test_splat_bound_over_many_views(n):
         vols.append(vol.double().cpu())
         plan.destroy()
     assert torch.linalg.norm(vols[1] - vols[0]) <= 1e-5 * torch.linalg.norm(vols[0])
+
+
+@pytest.mark.parametrize("m,k,nb", [(64, 64, 5), (125, 1, 1), (125, 1, 134), (135, 1, 115), (128, 1, 128), (256, 4, 32),
+                                    (75, 3, 372)])
+def test_noalloc_row_spectra_find_room(m, k, nb):
+    """tomo_backpropagate_noalloc's row spectra behind the spectra in the static workspace, or (calls that
+    fill the workspace) in the planes: bit for bit tomo_backpropagate's planes, and nothing written past them."""
+    plan = _plan(m, nb, angle_batch=8, **({"n_planes": k} if k > 1 else {"ewald": 0}))
+    img = torch.rand((nb, m, m), generator=torch.Generator().manual_seed(m)).to("cuda:0") + 0.5
+    want = torch.full(plan.stack_shape(nb), float("nan"), device="cuda:0")
+    got = torch.full(plan.stack_shape(nb + 1), float("nan"), device="cuda:0")
+    plan.backpropagate(img, 0, nb, want)
+    plan.backpropagate_noalloc(img, 0, nb, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got[:nb], want) and torch.isnan(got[nb]).all()
+    plan.destroy()
+
+
+def test_noalloc_leaves_the_plans_workspace_alone():
+    """Reconstructions on one stream while tomo_backpropagate_noalloc runs on another (FP32 planes: it only
+    reads the plan's tables): both give the bits that they give alone."""
+    for kw in ({}, {"angle_batch": 8}):
+        plan = _plan(96, 24, **kw)
+        img = torch.rand((24, 96, 96), generator=torch.Generator().manual_seed(3)).to("cuda:0") + 0.5
+        vol, alone = (torch.empty((96,) * 3, device="cuda:0") for _ in range(2))
+        st, st_alone = (torch.empty(plan.stack_shape(6), device="cuda:0") for _ in range(2))
+        plan.reconstruct(img, alone)
+        plan.backpropagate(img[4:10].contiguous(), 4, 6, st_alone)
+        part = img[4:10].contiguous()
+        torch.cuda.synchronize()
+        a, b = torch.cuda.Stream(), torch.cuda.Stream()
+        for _ in range(40):
+            plan.reconstruct_async(img, vol, stream=a)
+            plan.backpropagate_noalloc(part, 4, 6, st, stream=b)
+            plan.backpropagate_noalloc(part, 4, 6, st, stream=b)
+        torch.cuda.synchronize()
+        assert torch.equal(vol, alone) and torch.equal(st, st_alone)
+        plan.destroy()
