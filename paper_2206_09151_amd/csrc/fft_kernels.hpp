@@ -818,16 +818,18 @@ hipError_t spectra32_split(const Spectra32Launch& a) {
 // device compilation does not take them, and the host launchers they point to, along).
 struct FftSize {
   int M, P;
-  hipError_t (*spectra)(const SpectraLaunch&);           // (Q1, Q2)
+  hipError_t (*spectra)(const SpectraLaunch&);           // (Q1, Q2); null below kTwoKernelSpectra
   hipError_t (*spectra_complex)(const SpectraLaunch&);   // times a complex filter
-  hipError_t (*spectra32)(const Spectra32Launch&);       // (Q1, Q2) of 16-bit plans
+  hipError_t (*spectra32)(const Spectra32Launch&);       // (Q1, Q2) of 16-bit plans and of small detectors
   hipError_t (*planes)(const PlanesLaunch&);
 };
 
 template <int M>
 __host__ FftSize size_of(int P, hipError_t (*spectra32)(const Spectra32Launch&),
                          hipError_t (*planes)(const PlanesLaunch&)) {
-  return FftSize{M, P, &half_spectra<M, kFull>, &half_spectra<M, kComplex>, spectra32, planes};
+  hipError_t (*spectra)(const SpectraLaunch&) = nullptr;
+  if constexpr (M >= kTwoKernelSpectra) spectra = &half_spectra<M, kFull>;
+  return FftSize{M, P, spectra, &half_spectra<M, kComplex>, spectra32, planes};
 }
 template <int M>
 __host__ FftSize direct_size() {

@@ -232,7 +232,7 @@ __device__ __forceinline__ float4 q_filtered(float4 f, double2 g) {
 //   kSlices  q[2 r + c][kx <= M/2], r <= M/2: the even (c = 0) and odd (c = 1) part of the rows +-r,
 //            (Q(r) + Q(-r)) / 2 and (Q(r) - Q(-r)) / 2i; pair r = 0 holds rows 0 and (even M) M/2.
 //   kRows    q[ky][kx], ky <= M/2.
-// l1 (kFull, kComplex; or NULL): [view][G] sums of the output's magnitudes (fixed order).
+// l1 (kComplex; or NULL): [view][G] sums of the output's magnitudes (fixed order).
 enum ColsOut { kFull, kComplex, kSlices, kRows };
 template <ColsOut OUT>
 using QValue = std::conditional_t<OUT == kComplex, float2, float4>;
@@ -240,7 +240,6 @@ __device__ __forceinline__ float2 q_filtered(float2 f, double2 g) {
   return make_float2(float(f.x * g.x - f.y * g.y), float(f.x * g.y + f.y * g.x));
 }
 __device__ __forceinline__ float q_magnitude(float2 a) { return fabsf(a.x) + fabsf(a.y); }
-__device__ __forceinline__ float q_magnitude(float4 a) { return fabsf(a.x) + fabsf(a.y) + fabsf(a.z) + fabsf(a.w); }
 
 template <int M, ColsOut OUT>
 __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __restrict__ z,
@@ -293,15 +292,15 @@ __global__ __launch_bounds__(FwdShape<M>::CT) void k_cols_fwd(const float2* __re
       const double2 g = cells[cl * S::P + ky];
       const QValue<OUT> a = q_filtered(fv[ky * M + k], g);
       qv[ky * M + k] = a;
-      sum += q_magnitude(a);
+      if constexpr (OUT == kComplex) sum += q_magnitude(a);
       if (k > 0 && 2 * k < M) {
         const int o = (ky == 0 ? 0 : M - ky) * M + M - k;
         const QValue<OUT> b = q_filtered(fv[o], make_double2(g.x, -g.y));
         qv[o] = b;
-        sum += q_magnitude(b);
+        if constexpr (OUT == kComplex) sum += q_magnitude(b);
       }
     }
-    if (l1) {
+    if (OUT == kComplex && l1) {
       __shared__ float red[(S::CT + 63) / 64];
       for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
       if ((t & 63) == 0) red[t >> 6] = sum;

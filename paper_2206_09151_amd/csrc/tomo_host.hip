@@ -106,7 +106,7 @@ size_t stack_view_bytes(int M, int K, int dtype) { return size_t(M) * K * M * dt
 // launches (8 views at a time, 160 in all: 24^2 375 us with one kernel, 451 with two; 36^2 434 / 440;
 // 48^2 475 / 470; 64^2 638 / 553; calls of one to eight views at 48^2 and 50^2 pay 0.8 to 1.4 us of 13 for
 // the second launch, from 54^2 on none).
-bool two_kernel_spectra(int M, int dtype) { return dtype == TOMO_F32 && M >= 48; }
+bool two_kernel_spectra(int M, int dtype) { return dtype == TOMO_F32 && M >= tomo::kTwoKernelSpectra; }
 
 // Resolve defaults and sizes; returns an error message or "" and fills r.
 std::string resolve(const tomo_params* p, Resolved* r) {

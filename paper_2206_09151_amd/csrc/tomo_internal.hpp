@@ -25,6 +25,9 @@ struct FilterArgs {
 bool fft_supported(int M);
 int fft_split(int M);
 
+// The least detector size whose stacks' spectra are formed by two kernels in FP64.
+constexpr int kTwoKernelSpectra = 48;
+
 // g = ln(I/I_in) -> 2D DFT G -> (Q1, Q2) = filt G for nb views.  filt, q: [nb][M][M] float4.
 // scratch: at least spectra_scratch_bytes(M), the more views it holds the
 // fewer launches.  tw: [M] exp(-i 2 pi k / M).  The complex form: filt, q float2.

@@ -1058,7 +1058,6 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
   const double rx = ix - c, ry = iy - c, rz0 = iz0 - c;
   const double hm = 0.5 * (M - 1), hk = 0.5 * (K - 1);
   const size_t plane_sz = size_t(K) * M;
-  const bool vec = (M % VEC) == 0;
   const double lo[3] = {tx0 - c, ty0 - c, tz0 - c};
   const double hi[3] = {tx0 + CB_E - 1 - c, ty0 + CB_E - 1 - c, tz0 + CB_E - 1 - c};
 
@@ -1092,24 +1091,17 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int row = r0 + cj[i], pp = p0 + cpl[i], cc = c0 + cq[i];
-      const bool ok = cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && cc >= 0 && cc < M;
-      valid |= ok ? (1u << i) : 0u;
+      valid |= cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) ? (1u << i) : 0u;
       const int rowc = min(max(row, 0), M - 1), ppc = min(max(pp, 0), K - 1);
-      if (vec) {
-        const unsigned off = unsigned(rowc * K + ppc) * unsigned(M) + unsigned(min(max(cc, 0), M - VEC));
-        v[i] = *reinterpret_cast<const uint4*>(vbase + off);
-      } else {
-        const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
-        Chunk16 x;
+      const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
+      Chunk16 x;
 #pragma unroll
-        for (int kk = 0; kk < VEC; ++kk) {
-          const int ce = min(max(cc + kk, 0), M - 1);
-          const bool ek = unsigned(cc + kk) < unsigned(M);
-          x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
-        }
-        v[i] = x.u;
-        if (cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K)) valid |= (1u << i);
+      for (int kk = 0; kk < VEC; ++kk) {
+        const int ce = min(max(cc + kk, 0), M - 1);
+        const bool ek = unsigned(cc + kk) < unsigned(M);
+        x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
       }
+      v[i] = x.u;
     }
   };
   auto stage = [&](const uint4 (&v)[PER], unsigned valid) {
@@ -1607,7 +1599,7 @@ hipError_t launch_spectra(int M, const float* images, const double2* tw, const f
                           double inv_iin, int nb, hipStream_t s, void* scratch, size_t scratch_bytes) {
   if (nb <= 0) return hipSuccess;
   const FftSize* f = fft_size(M);
-  if (!f) return hipErrorInvalidValue;
+  if (!f || !f->spectra) return hipErrorInvalidValue;
   return f->spectra(SpectraLaunch{images, tw, filt, q, static_cast<float2*>(scratch),
                                   scratch_bytes / spectra_scratch_bytes(M), status, inv_iin, nullptr, nb, s});
 }
