@@ -118,40 +118,55 @@ def kernel_source_hash(method: str = "realspace") -> str:
     return h.hexdigest()[:16]
 
 
-def sliced(w, angle_batch: int = 0) -> bool:
-    """Whether tomo_reconstruct runs this workload by slices (no plane stacks): "planes" is then
-    the slice kernel (transforms along x and gridding) and "grid" the column kernel."""
-    return (w.geometry == "axis" and bool(w.ewald) and angle_batch == 0 and w.M <= 192 and w.n_vox <= w.M
-            and w.K <= w.M and (w.M - w.n_vox) % 2 == 0 and (w.M - w.K) % 2 == 0)
+def by_slices(plan, w, dirs, dist, img, vol, planes_launches: float) -> bool:
+    """Whether tomo_reconstruct ran this workload by slices (no plane stacks; vol is its result, from
+    planes_launches launches of kind "planes"): "planes" is then the slice kernel (transforms along x
+    and gridding) and "grid" the column kernel, one launch each for any number of batches.  A scan
+    of one batch took the stacks if those of an explicit batch give its bits."""
+    from dataclasses import replace
+    if w.geometry != "axis" or not w.ewald or plan.params.plane_dtype != 0 or plan.params.angle_batch:
+        return False
+    if plan.batch < w.n_views:
+        return planes_launches == 1
+    import torch
+    from paper_2206_09151_amd import tomo
+    stacks = tomo.Plan(replace(plan.params, angle_batch=plan.batch, tune=0), dirs, dist)
+    other = torch.empty_like(vol)
+    stacks.reconstruct(img, other)
+    stacks.destroy()
+    return not torch.equal(vol, other)
 
 
 def slice_bytes(kind: str, w) -> float:
-    """Compulsory HBM bytes of one step of the slice path: the images read and half of their spectra
-    written; those and half of the filter read by the slice kernel, which writes one partial volume;
-    the column kernel reads it and writes the volume."""
+    """Compulsory HBM bytes of one step of the slice path: the images and half of the filter read and half of
+    the filtered spectra (16 bytes per coefficient) written; those read by the slice kernel, which
+    writes one partial volume; the column kernel reads it and writes the volume."""
     half = (w.M // 2 + 1) * float(w.M)
-    return {"spectra": w.n_views * (4.0 * w.M * w.M + 8.0 * half), "planes": w.n_views * 24.0 * half + 4.0 * w.M * w.n_vox ** 2,
-            "grid": 4.0 * w.M * w.n_vox ** 2 + 4.0 * w.n_vox ** 3}[kind]
+    part = 4.0 * w.M * w.n_vox ** 2
+    return {"spectra": w.n_views * (4.0 * w.M * w.M + 32.0 * half), "planes": w.n_views * 16.0 * half + part,
+            "grid": part + 4.0 * w.n_vox ** 3}[kind]
 
 
-def algorithmic_bytes(kind: str, w, nb: int, first_batch: bool, sbytes: int = 4, fourier_mode: int = 1,
+def algorithmic_bytes(kind: str, w, nb: int, first_batch: bool, sbytes: int = 4, fourier_mode: int = 0,
                       entries: int = 0) -> float:
     """Compulsory HBM bytes of the launches of one kind in one step over nb views;
-    sbytes = bytes per stored plane value; entries = non-zeros of the Fourier-space
-    gridding operator."""
+    sbytes = bytes per stored plane value; fourier_mode = 0 for the real-space form (whose filter and
+    spectra take 16 bytes per coefficient, those of the Fourier form 8); entries = non-zeros
+    of the Fourier-space gridding operator."""
     N, M, K = w.n_vox, w.M, w.K
     P = N + (1 - N % 2)
     fft3 = 2 * (8.0 + 8.0) * N ** 3 + (8.0 + 4.0) * N ** 3     # three passes, the last writes the real part
     if kind == "fgrid":
         if fourier_mode == 1:   # operator entries + row offsets + spectra + S read, complex grid written
-            return 8.0 * entries + 4.0 * P ** 3 + nb * 16.0 * M * M + 8.0 * N ** 3 + 8.0 * N ** 3
-        return nb * 16.0 * M * M + 2 * 16.0 * P ** 3           # spectra read, accumulator cleared and updated
+            return 8.0 * entries + 4.0 * P ** 3 + nb * 8.0 * M * M + 8.0 * N ** 3 + 8.0 * N ** 3
+        return nb * 8.0 * M * M + 2 * 16.0 * P ** 3            # spectra read, accumulator cleared and updated
     if kind == "finverse":
         if fourier_mode == 1:
             return fft3
         return 16.0 * P ** 3 + 8.0 * N ** 3 + 8.0 * N ** 3 + fft3   # + normalisation pass
-    if kind == "spectra":   # image read + filter table read + Q write (16 B per coefficient each)
-        return nb * (4.0 * M * M + 16.0 * M * M + 16.0 * M * M)
+    if kind == "spectra":   # image read + filter table read + Q write
+        coefficient = 8.0 if fourier_mode else 16.0
+        return nb * (4.0 + 2.0 * coefficient) * M * M
     if kind == "planes":    # Q read once per view + plane stack write
         return nb * (16.0 * M * M + sbytes * M * K * M)
     if kind == "grid":      # plane stack read + volume write (+ read when accumulating)
@@ -308,6 +323,7 @@ def main():
 
     roofline = None
     kernels = None
+    slices = None
     if not args.no_kernel_timing:
         plan.timing(True)
         plan.timing_read(reset=True)
@@ -321,17 +337,17 @@ def main():
         plan.timing(False)
         k = plan.timing_read(reset=True)
         n_batches = -(-w.n_views // batch)
-        by_slices = not fourier and args.plane_dtype == "f32" and sliced(w, args.angle_batch)
+        slices = not fourier and by_slices(plan, w, dirs, dist, d_img, vol, k["planes"][1] / args.steps)
         kernels = {}
         for kind, (tot, cnt) in k.items():
             if cnt == 0:
                 continue
             # bytes of all launches of one step (the first batch writes V without reading it)
             sb = 4 if args.plane_dtype == "f32" else 2
-            if by_slices:                      # one launch of each kind per step
+            if slices:                         # one launch of each kind per step
                 per_launch = slice_bytes(kind, w)
             elif kind == "spectra" or fourier:   # launches over all views per step
-                step_bytes = algorithmic_bytes(kind, w, w.n_views, True, sb, args.fourier_mode,
+                step_bytes = algorithmic_bytes(kind, w, w.n_views, True, sb, args.fourier_mode if fourier else 0,
                                                plan.fourier_entries)
                 per_launch = step_bytes / cnt * args.steps
             else:
@@ -351,20 +367,20 @@ def main():
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": read_traffic(dom, src_hash, w.name, args.plane_dtype),
                     "ms_per_step_with_events": round(ms_timed, 4), "kernel_source_hash": src_hash}
-        if by_slices and dom == "planes":
+        if slices and dom == "planes":
             # planes stay in LDS: the vector arithmetic bounds the slice kernel, not its bytes
             fl = w.n_views * (plane_flops(w, 1) / 2 + 7.0 * w.n_vox ** 2 * w.M)
             tf = fl / (kernels[dom]["avg_ms"] * 1e-3) / 1e12
             roofline.update(bound="fp32_vector", achieved=round(tf, 2), peak=FP32_UNPACKED_PEAK, unit="TFLOP/s",
                             frac=round(tf / FP32_UNPACKED_PEAK, 4))
         if not fourier:
-            pb = path_bytes_per_update(w, sb, by_slices)
+            pb = path_bytes_per_update(w, sb, slices)
             roofline["path"] = {"bytes_per_update": round(pb, 3), "achieved": round(pb * value / 1e9, 1),
                                 "frac": round(pb * value / 1e9 / HBM_PEAK_GBS, 4)}
         if "planes" in kernels:
             # the plane kernel's FFT arithmetic beside its bytes: it is bound by vector
             # arithmetic and LDS exchanges more than by its HBM writes
-            if by_slices:   # transforms along x only, and 7 operations per update for the interpolation
+            if slices:   # transforms along x only, and 7 operations per update for the interpolation
                 fl = w.n_views * (plane_flops(w, 1) / 2 + 7.0 * w.n_vox ** 2 * w.M)
             else:
                 fl = sum(plane_flops(w, min(batch, w.n_views - b * batch)) for b in range(n_batches)) / n_batches
@@ -464,7 +480,7 @@ def main():
         "config": {"workload": w.name, "n_vox": w.n_vox, "n_pix": w.M, "n_planes": w.K, "grid_variant": plan.grid_rows,
                    "plane_storage": args.plane_dtype,
                    "n_views": w.n_views, "ewald": w.ewald, "weight_mode": w.weight_mode,
-                   "angle_batch": batch, "updates_per_step": updates,
+                   "angle_batch": None if slices else batch, "updates_per_step": updates,
                    **({"fourier_mode": args.fourier_mode, "operator_entries": plan.fourier_entries,
                        "variant": args.variant, "nsr": args.nsr} if fourier else {})},
         "rel_l2_vs_fp64": rel_l2,
@@ -529,16 +545,18 @@ def run_batch(args):
     kernels = roofline = None
     if not args.no_kernel_timing:
         tot = {}
-        for pl, w, im, v in zip(plans, jobs, imgs, vols):
+        for pl, w, (dirs, dist, _), im, v in zip(plans, jobs, data, imgs, vols):
             pl.timing(True)
             pl.timing_read(reset=True)
             pl.reconstruct(im, v, stream=stream)
             pl.timing(False)
             nb_all = -(-w.n_views // pl.batch)
-            for kind, (ms_k, cnt) in pl.timing_read(reset=True).items():
+            times = pl.timing_read(reset=True)
+            slices = by_slices(pl, w, dirs, dist, im, v, times["planes"][1])
+            for kind, (ms_k, cnt) in times.items():
                 if cnt == 0:
                     continue
-                if sliced(w):
+                if slices:
                     b = slice_bytes(kind, w)
                 elif kind == "spectra":
                     b = algorithmic_bytes(kind, w, w.n_views, True)
