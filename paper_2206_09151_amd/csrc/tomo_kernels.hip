@@ -730,11 +730,11 @@ __global__ __launch_bounds__(256) void k_grid_box(const InT* __restrict__ stack,
 // boxes alternating so that view n + 1 is in flight while view n is interpolated (trilinear:
 // eight LDS taps per voxel row; with ONE_BOX a single box, fetched and then interpolated, two
 // barriers per view).  Per view the box origin, its extent and whether the footprint
-// fits are computed one view per lane (FP64, from the tile corners) and read out with readlane;
-// only the view's own extent is fetched, and a view whose footprint does not fit is gathered
-// for that tile straight from global memory.  Bound by vector issue (79 % of the cycles with
-// FP64-to-FP32 coordinates of three conversions each; fixed point and taps widened inside the
-// multiply-adds take 30 % fewer instructions).  The 4-row kernel is held to six waves per SIMD (80
+// fits are computed one view per lane (FP32 with a margin, from the tile corners) and read out with
+// readlane; only the view's own extent is fetched, and a view whose footprint does not fit is gathered
+// for that tile straight from global memory.  Bound by vector issue (FP16, 4 rows: 79 % of the cycles;
+// FP64-to-FP32 coordinates of three conversions each took 30 % more instructions) and the fetch path
+// (texture data unit busy 88 %, two thirds of that waiting for L2).  The 4-row kernel is held to six waves per SIMD (80
 // VGPRs): 256^3 with FP16 stacks over a tilt-jittered scan, per 8-view launch 318 us before, 296 with
 // fixed-point coordinates at five waves, 280 at six, 310 at seven (spills).  For directions far
 // from the axis, whose footprints often take the global gather, the bound costs time: the
@@ -1058,6 +1058,9 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
   const double rx = ix - c, ry = iy - c, rz0 = iz0 - c;
   const double hm = 0.5 * (M - 1), hk = 0.5 * (K - 1);
   const size_t plane_sz = size_t(K) * M;
+  // (false for every stack that comes here, but a compiler that knows it reorders the loads: 125^3 from 40
+  // views 1.18 -> 1.34 ms, 27^3 from 223 views 0.67 -> 0.79)
+  const bool vec = (M % VEC) == 0;
   const double lo[3] = {tx0 - c, ty0 - c, tz0 - c};
   const double hi[3] = {tx0 + CB_E - 1 - c, ty0 + CB_E - 1 - c, tz0 + CB_E - 1 - c};
 
@@ -1091,17 +1094,24 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int row = r0 + cj[i], pp = p0 + cpl[i], cc = c0 + cq[i];
-      valid |= cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) ? (1u << i) : 0u;
+      const bool ok = cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && cc >= 0 && cc < M;
+      valid |= ok ? (1u << i) : 0u;
       const int rowc = min(max(row, 0), M - 1), ppc = min(max(pp, 0), K - 1);
-      const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
-      Chunk16 x;
+      if (vec) {
+        const unsigned off = unsigned(rowc * K + ppc) * unsigned(M) + unsigned(min(max(cc, 0), M - VEC));
+        v[i] = *reinterpret_cast<const uint4*>(vbase + off);
+      } else {
+        const InT* src = vbase + (size_t(rowc) * K + ppc) * M;
+        Chunk16 x;
 #pragma unroll
-      for (int kk = 0; kk < VEC; ++kk) {
-        const int ce = min(max(cc + kk, 0), M - 1);
-        const bool ek = unsigned(cc + kk) < unsigned(M);
-        x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
+        for (int kk = 0; kk < VEC; ++kk) {
+          const int ce = min(max(cc + kk, 0), M - 1);
+          const bool ek = unsigned(cc + kk) < unsigned(M);
+          x.h[kk] = ek ? reinterpret_cast<const unsigned short*>(src)[ce] : (unsigned short)0;
+        }
+        v[i] = x.u;
+        if (cj[i] >= 0 && unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K)) valid |= (1u << i);
       }
-      v[i] = x.u;
     }
   };
   auto stage = [&](const uint4 (&v)[PER], unsigned valid) {
@@ -1181,7 +1191,8 @@ __global__ __launch_bounds__(256) void k_grid_cube(const InT* __restrict__ stack
 // barriers per view: a second box (view n + 1 in flight while view n is interpolated) halves
 // the workgroups per CU and measured slower.
 //
-// Bound by the fetches' latency and what they miss in L2, and by vector issue (about 120
+// Bound by the fetches' latency and what they miss in L2 (a quarter of its reads; the texture data
+// unit is busy 70 % of the time, half of it waiting), and by vector issue (55 %; about 120
 // instructions per wave and view): hence FP32 box origins and packed slots (71 VGPRs, so seven
 // workgroups per CU, with 94 five), tiles of an XCD in octants (cube_tile), and fixed-point
 // coordinates.  96^3, 120 views: 310 us; with slabs, five workgroups and FP64 coordinates 384;
@@ -1309,8 +1320,8 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const InT* __restrict
     rh = (ex >> 18) & 63;
     ph = (ex >> 24) & 63;
   };
-  // (views are below 2^31 bytes, as M <= 256 and K <= 2048; M is a multiple of V); what lies outside the view's extent is not fetched (its LDS words are
-  // never read)
+  // (views are below 2^31 bytes, as M <= 256 and K <= 2048; M is a multiple of V); what lies outside the
+  // view's extent is not fetched (its LDS words are never read)
   constexpr int PER = CH == 16 ? (F::BOX / 4 + 255) / 256 : 1;
   // 16-byte slots: offsets in the box (spare slots and slots past the box are never fetched)
   // and bytes from the box origin; dword loads: lane = plane and column, one load per row
@@ -1343,7 +1354,7 @@ __global__ __launch_bounds__(256 * G) void k_grid_cube_dma(const InT* __restrict
           if (slot_inside(ext, slot[i])) {
             // c0 and M are multiples of V: a slot is wholly inside or wholly outside the columns
             const int sl = opaque(int(slot[i]));
-          const int row = r0 + (sl & 255), pp = p0 + (sl >> 8 & 255), cc = c0 + (sl >> 16);
+            const int row = r0 + (sl & 255), pp = p0 + (sl >> 8 & 255), cc = c0 + (sl >> 16);
             const bool ok = unsigned(row) < unsigned(M) && unsigned(pp) < unsigned(K) && unsigned(cc) < unsigned(M);
             const unsigned off = ok ? unsigned((row * K + pp) * M + cc) * unsigned(ES) : kOutOfRange;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + 1024 * i), 16, int(off), 0, 0, 0);
@@ -1719,9 +1730,9 @@ static hipError_t grid_tilt_impl(const void* stack, const ViewGeom* geom, const 
   if (M % DmaBox<InT>::VEC != 0 || size_t(K) * M * M * sizeof(InT) > size_t(0x7fffffff)) return hipErrorInvalidValue;
   const int ntx = (N + GT - 1) / GT;
   const int yblocks8 = ((N + YB - 1) / YB + 7) / 8 * 8;
-  // 4 and 8 rows: one box per workgroup, five / four workgroups per CU (at 88 / 118 VGPRs)
-  // instead of three / two with two boxes (at 256^3 per 8-view launch, before the five-wave
-  // bound on 4 rows: 376 vs 385 us, 363 vs 446 us); 2 rows keep two boxes
+  // 4 and 8 rows: one box per workgroup, six / four workgroups per CU instead of three / two with
+  // two boxes (256^3 FP32, per 8-view launch, with five / four: 376 vs 385 us, 363 vs 446 us); 2 rows
+  // keep two boxes
   hipLaunchKernelGGL((k_grid_tilt_dma<YB, InT, YB >= 4>), dim3(unsigned(ntx * ntx * yblocks8)), dim3(256), 0, s,
                      static_cast<const InT*>(stack), geom, scale, vol, N, M, K, nb, accumulate, flat, 0.5 * (M - 1),
                      flat ? 0.0 : 0.5 * (K - 1));
