@@ -170,16 +170,18 @@ tomo_status tomo_backpropagate_noalloc(tomo_plan_t plan, const float* d_images, 
 /* Grid plane stacks of views [first, first+nb) into the volume: for every voxel
  * the trilinear value of each view's stack at the voxel's view-frame position
  * (taps outside the stack count as zero) is added to d_volume (device float32
- * [N][N][N], accumulated: V += sum over the nb views, in ascending view order).
- * Deterministic: no atomics. */
+ * [N][N][N], accumulated: V += sum over the nb views).  Deterministic: no atomics, and the
+ * views are summed in a fixed order, ascending but for cubic tiles of at most 512 tiles of 8^3
+ * voxels, which sum every second or fourth view and then these sums (by N and nb alone). */
 tomo_status tomo_grid(tomo_plan_t plan, const void* d_planes, int32_t first, int32_t nb,
                       float* d_volume, void* stream);
 
 /* Whole reconstruction: d_volume (device float32 [N][N][N]) is overwritten with
  * the sum over all n views, processed in internal batches of the plan's batch
  * size; with angle_batch = 0 and FP32 planes, single-axis scans (ewald = 1, N and K at most
- * M <= 192, M - N and M - K even) run slice by slice instead, without plane stacks.  d_images:
- * device float32 [n][M][M].  Synchronises the stream once at the end to report TOMO_EDOMAIN. */
+ * M <= 192, M - N and M - K even) run slice by slice instead, without plane stacks, where that
+ * is faster (not the shortest scans of small detectors, nor few planes or small volumes of large
+ * ones).  d_images: device float32 [n][M][M].  Synchronises the stream once at the end to report TOMO_EDOMAIN. */
 tomo_status tomo_reconstruct(tomo_plan_t plan, const float* d_images, float* d_volume, void* stream);
 
 /* tomo_reconstruct without the final synchronisation: every kernel of the reconstruction
@@ -277,8 +279,10 @@ int32_t tomo_grid_rows(tomo_plan_t plan);
 /* Non-zero entries of the plan's Fourier-space gridding operator (0 unless fourier = 1). */
 size_t tomo_fourier_entries(tomo_plan_t plan);
 
-/* Bytes of plan tables + workspace that tomo_plan would allocate for p (0 if p is invalid;
- * with fourier = 1 an upper bound: the operator's exact size is known after planning). */
+/* Bytes of plan tables + workspace that tomo_plan would allocate on the device for p (0 if p is
+ * invalid; with fourier = 1 an upper bound: the operator's exact size is known after planning).
+ * With max_workspace_bytes set, of a plan that fits it where one does: the row spectra of FP32
+ * plans, 8 M ceil(M / 2) bytes per view, then take what the limit leaves (more launches). */
 size_t tomo_workspace_bytes(const tomo_params* p);
 
 /* Views per internal batch of tomo_reconstruct (plane stacks held at once). */

@@ -33,16 +33,17 @@
 // 376 with complex cells and one workgroup); up to M = 64 the complex slice is small enough for
 // four, and real cells would leave half of every wave's lanes without a plane pair.
 //
-// What bounds k_axis_slices at 128^3, 180 views (337 us): vector issue, 70-74 % of the time, and
-// LDS, 65 % (a quarter of it bank conflicts of the rotated taps), between three barriers per view
-// at four waves per SIMD.  27.6 TFLOP/s of transform and interpolation, of the 78.6 that FP32
+// What bounds k_axis_slices at 128^3, 180 views (329 us): vector issue, 69-73 % of the time, and
+// LDS, 64-68 % (30 % of it bank conflicts of the rotated taps), between three barriers per view
+// at four waves per SIMD.  28.1 TFLOP/s of transform and interpolation, of the 78.6 that FP32
 // reaches without packed instructions.  It replaces plane stacks of 8.4 MB per view: 452 us of 2D
 // plane transforms and 386 us of gridding per reconstruction.  What moved it: rows of the spectrum
 // fetched into LDS one view ahead (650 -> 393 us; as scalar loads their latency was exposed on
 // every view), the four voxels of a quarter-turn orbit sharing one set of weights (393 -> 376),
 // two workgroups per CU (376 -> 337).  From M = 135 on one workgroup fills a CU, and from 160 on
 // some of a thread's 40 to 60 transform and propagation values spill: 160^3 from 60 views takes
-// 391 us (plane stacks: 817 + 264), 192^3 869 us (882 + 474).
+// 391 us (plane stacks: 817 + 264), 192^3 869 us (882 + 474).  Where stacks are the faster way:
+// stacks_faster in tomo_kernels.hip.
 #pragma once
 #include <hip/hip_runtime.h>
 

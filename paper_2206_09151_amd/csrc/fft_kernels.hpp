@@ -69,9 +69,10 @@ template <> struct Shape<192> : Fft2Shape<192, 48, 4> {};
 
 // Shapes of the plane kernels of FP32 stacks where others than those above are faster (us per view over
 // general scans): 36 0.227 -> 0.217, 40 0.327 / 0.270, 45 0.346 / 0.336, 54 0.499 / 0.435, 60 0.575 / 0.511,
-// 90 2.41 / 1.89, 100 2.09 / 1.47, 120 4.20 / 4.05.  16-bit stacks keep the shapes above, as their spectra do:
-// another order of the sums flips roundings of 2^-9 or 2^-12, and their volumes would differ from
-// earlier ones by more than FP32 results of one method do.
+// 90 2.41 / 1.89, 100 2.09 / 1.47, 120 4.20 / 4.05.  16-bit stacks keep the shapes above and their spectra in
+// FP32 (k_spectra): another order of the sums flips some of the stored roundings of 2^-9 or 2^-12, which
+// moves a volume by 1e-5 (FP16) to 4e-5 (BF16) and brings it no nearer to the exact one (1.5e-4, 1e-3), so
+// that volumes of one scan made at different times could no longer be compared bit for bit.
 template <int M>
 struct FastShape : Shape<M> {};
 template <> struct FastShape<36> : Fft2Shape<36, 12, 3> {};
@@ -555,10 +556,10 @@ __device__ __forceinline__ float4 filtered(const float4 f, const float2 gg) {
   return o;
 }
 
-// ------------------------------------------------------------------ spectra of 16-bit plans
-// One workgroup per view (or per block of a split size), the two-dimensional transform in FP32: 16-bit
-// stacks follow the last bits of their spectra by whole roundings, so these plans keep the
-// transforms whose results earlier stacks hold (128^2, 180 views: 80 us, the FP64 transforms 29).
+// ------------------------------------------------------------------ spectra of 16-bit plans, small FP32 ones
+// One workgroup per view (or per block of a split size), the two-dimensional transform in FP32, whose
+// bits the stored 16-bit planes follow by whole roundings (see FastShape).  128^2, 180 views: 38 us (the FP64
+// transforms take 41 with their events); 256^2, 360 views: 728 (319), a logarithm P^2 times per pixel.
 template <int M>
 __global__ __launch_bounds__(Shape<M>::T) void k_spectra(const float* __restrict__ images,
                                                          const float4* __restrict__ filt,

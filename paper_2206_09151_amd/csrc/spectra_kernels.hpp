@@ -12,12 +12,13 @@
 // two roundings instead of one per butterfly (128^3 from 180 views by slices: relative error 1.5e-7
 // instead of 2.9e-7).
 //
-// Bound at M = 128, 180 views (16 us, and 11 by slices / 21 for the whole filtered plane): k_rows_fwd
-// by its logarithms and transforms (5.6 workgroups of two waves per CU), k_cols_fwd by its 60 MB (106
-// MB) of traffic, and small launches by the latency of their loads, which every thread of a workgroup
-// shares (transforming threads alone: 10 instead of 6 us for 60 views at M = 48).  The whole-image
-// kernel took 47 us (33 when only half of the rows were wanted), 71 instead of 25 at M = 160 with 60
-// views, 229 instead of 97 at M = 256 with 96, and 12 as now at M = 48 with 60.
+// Bound at M = 128, 180 views: k_rows_fwd (14 us) by its logarithms and transforms (vector issue a third of
+// the time, 5.6 workgroups of two waves per CU) and its loads; k_cols_fwd (13 us by slices, 29 for the
+// whole filtered plane) by its 60 MB (106 MB) of traffic; small launches by the latency of their loads, which
+// every thread of a workgroup shares (transforming threads alone: 10 instead of 6 us for 60 views at
+// M = 48).  The whole-image kernel of fft_kernels.hpp, us for the whole plane / these two: 60 views at 48^2
+// 14.3 / 14.8, 180 at 128^2 40 / 41 (27 for the half that slices take), 60 at 160^2 91 / 30, 96 at 256^2
+// 217 / 76, 360 at 256^2 728 / 319.
 #pragma once
 #include <hip/hip_runtime.h>
 
