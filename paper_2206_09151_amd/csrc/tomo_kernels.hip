@@ -1801,7 +1801,7 @@ size_t axis_part_bytes(int M, int N) {
 //  - the shortest scans of small detectors, which cost their launches and the latency of one workgroup
 //    each: one launch more by slices, or two (32^2: one view 15.5 / 13.0, three 16.2 / 15.0, four 15.9 /
 //    16.5; 36^2 three 17.0 / 15.3; 64^2 one 21.2 / 18.3, 80^2 one 25.2 / 25.2; rows that are not whole
-//    16-byte chunks cost stacks more: 54^2 two 20.4 / 21.7).
+//    16-byte chunks cost stacks more: 50^2 one 19.8 / 18.3, 54^2 one 18.8 / 20.0).
 //  - few planes, whose stacks leave room for fewer partial volumes than would fill the device, so that
 //    the blocks are long serial chains (32^2, 2 planes, 30 views: one block of 30, 70 / 47; 128^2, 2
 //    planes, 120 views 492 / 235; but 32^2, 4 planes, 30 views: three blocks of 10, 33 / 49).
@@ -1809,12 +1809,13 @@ size_t axis_part_bytes(int M, int N) {
 //    (192^2, 120 views: 24^3 from 24 planes 1270 / 477, 96^3 from 96 planes 1400 / 1257, 144^3 from 144
 //    planes faster by slices; 160^2: 20^3 538 / 382, 40^3 from 40 planes 549 / 568).
 static bool stacks_faster(const AxisSize* a, int M, int N, int K, int n, int cus, int blocks, int wanted) {
-  if (M <= 72 && size_t(n) * M <= size_t(M % 4 == 0 ? 108 : 54)) return true;
+  if (M <= 72 && size_t(n) * M <= size_t(M % 4 == 0 ? 108 : 50)) return true;
   if (blocks < wanted) {
     // a view of a block takes M / 16 us with complex and M / 28 with real cells, times the workgroups
     // that share a CU; a view by stacks 1.25 us and its share of the gridding and the transforms
     const double view = (M <= 64 ? std::max(M / 16.0, 1.5) : M / 28.0) * ((a->units * blocks + cus - 1) / cus);
-    const double stacks = 1.25 + 5e-7 * N * N * N + (M > 128 ? 2.2e-6 : 1.1e-6) * K * M * M;
+    // (a third more where rows are not whole 16-byte chunks: 90^2, 10 planes, 30 views 76 / 86)
+    const double stacks = (1.25 + 5e-7 * N * N * N + (M > 128 ? 2.2e-6 : 1.1e-6) * K * M * M) * (M % 4 == 0 ? 1.0 : 1.35);
     if (((n + blocks - 1) / blocks + 1) * view > n * stacks + 3.0) return true;
   }
   const double part = double(K) / M + 0.3 * N * N * N / (double(M) * M * M);

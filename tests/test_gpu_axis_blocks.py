@@ -26,8 +26,8 @@ def test_view_blocks_match_oracle(m, n_vox, k, n):
 
 @pytest.mark.parametrize("m,n_vox,k,n,slices", [
     (16, 16, 16, 6, False), (16, 16, 16, 7, True), (36, 36, 36, 3, False), (36, 36, 36, 4, True),
-    (54, 54, 54, 1, False), (54, 54, 54, 2, True),                                         # the shortest scans
-    (32, 32, 2, 30, False), (32, 32, 4, 30, True), (64, 64, 8, 8, False),                  # room for few blocks
+    (50, 50, 50, 1, False), (54, 54, 54, 1, True),                                         # the shortest scans
+    (32, 32, 2, 30, False), (32, 32, 4, 30, True), (90, 90, 10, 30, True),                 # room for few blocks
     (160, 20, 20, 6, False), (160, 80, 80, 6, True), (192, 192, 24, 5, False), (192, 144, 144, 5, True)])
 def test_route_of_small_scans_and_volumes(m, n_vox, k, n, slices):
     """Scans that plane stacks reconstruct faster take them: the volume is then bit for bit that of an
